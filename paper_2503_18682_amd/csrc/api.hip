@@ -43,7 +43,7 @@ struct Layout {
         offsets, block_sums;
     size_t crossing;          // quads with a vertex at z <= 0, awaiting frustum clipping
     uint32_t crossing_cap;    // entries of the crossing list
-    size_t inst_tiles_a, inst_tiles_b, inst_ids_a, inst_ids_b, hist, row_total, ranges, sched, tile_order;
+    size_t inst_tiles_a, inst_tiles_b, inst_ids_a, inst_ids_b, ranges, sched, tile_order;
     size_t row_offsets, row_owner, item_clock;
     size_t record_grads, total;
     int64_t nv_records, capacity, total_tiles;
@@ -340,12 +340,11 @@ rgs_status compute_layout(rgs_context *ctx, int64_t n, const rgs_camera *cams, i
     L.inst_tiles_b = take((size_t)capacity * 4);
     L.inst_ids_a = take((size_t)capacity * 4);
     L.inst_ids_b = take((size_t)capacity * 4);
-    L.hist = take(radix_hist_entries(std::max<int64_t>((int64_t)NV, capacity)) * 4);
-    L.row_total = take(256 * 4);
     L.ranges = take((size_t)tiles * 8);
     L.sched = take(sched_words() * 4);
     L.tile_order = take((size_t)tiles * 2 * 4);  // work items: up to two per tile
-    L.row_owner = take((size_t)capacity * 4);
+    // the row owners of the binning scan, whose place the tile sort's scratch takes after the emission
+    L.row_owner = take(std::max((size_t)capacity, radix_scratch_words(capacity, L.tile_bits, false)) * 4);
     L.item_clock = take((size_t)tiles * 2 * 8);  // per work item, for per-view completion clocks
     L.record_grads = (flags & RGS_WS_BACKWARD) ? take(NV * grad_floats(opts->mip) * sizeof(float)) : 0;
     L.total = off;
@@ -514,8 +513,6 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     uint2 *boxes = at<uint2>(ws, L.boxes);
     Conic *conics = at<Conic>(ws, L.conics);
     uint32_t *tile_counts = at<uint32_t>(ws, L.tile_counts);
-    uint32_t *hist = at<uint32_t>(ws, L.hist);
-    uint32_t *row_total = at<uint32_t>(ws, L.row_total);
     uint2 *ranges = at<uint2>(ws, L.ranges);
     uint32_t *sched = at<uint32_t>(ws, L.sched);
     const uint32_t *tile_order = at<uint32_t>(ws, L.tile_order);
@@ -524,15 +521,24 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     unsigned long long *item_clock = view_stamps ? at<unsigned long long>(ws, L.item_clock) : nullptr;
     Timer tm(ctx, stream, timing, ST_PRE);
     uint2 *bin_boxes = at<uint2>(ws, L.bin_boxes);
+    // largest depth keys by 64 Gaussians, in what becomes the binning offsets
+    uint32_t *part_max = at<uint32_t>(ws, L.offsets);
     RGS_HIP(ctx, launch_preprocess(g, views, n_views, dopt, records, keys_in, boxes, bin_boxes, conics, tile_counts,
-                                   at<double>(ws, L.crossing), counters + 5, L.crossing_cap, stream));
+                                   at<double>(ws, L.crossing), counters + 5, L.crossing_cap, part_max, stream));
     tm.mark(ST_PRE);
     // counters: [0] box instances, [1] capacity, [2] tile rows, [3] listed instances, [4] kept views,
-    // [5] quads with a vertex at z <= 0
+    // [5] quads with a vertex at z <= 0, [6] largest depth key
     int64_t *listed = counters + 3, *kept = counters + 4;
     // the values of the first pass are the Gaussian-view ids, not read
-    RGS_HIP(ctx, radix_sort(keys_in, ord_in, keys_alt, ord_alt, NV, nullptr, 32, true, 0xffffffffu, kept, hist,
-                            row_total, stream, true));
+    // (no kept centre is nearer than near_z, whose float32 bits the keys start from)
+    const float near_f = (float)opts.near_z;
+    uint32_t near_key;
+    std::memcpy(&near_key, &near_f, 4);
+    const RadixRange range{near_key, part_max, (int)((g.n + 63) / 64), reinterpret_cast<uint32_t *>(counters + 6)};
+    // its scratch is what the emission clears or the binning scan fills later
+    uint32_t *const dscratch = radix_scratch_words(NV, 32, true) <= sched_words() ? sched : at<uint32_t>(ws, L.sorted_boxes);
+    RGS_HIP(ctx, radix_sort(keys_in, ord_in, keys_alt, ord_alt, NV, nullptr, 32, &range, true, 0xffffffffu, kept,
+                            dscratch, stream, true));
     tm.mark(ST_DSORT);
     const uint32_t *order = at<uint32_t>(ws, L.order_a);
     uint32_t *offsets = at<uint32_t>(ws, L.offsets);
@@ -548,8 +554,8 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
                              L.capacity, s.w, s.h, empty_tile, tiles_in, ids_in, ranges, L.total_tiles, sched,
                              emit_grid(ctx->num_cus), stream));
     tm.mark(ST_EMIT);
-    RGS_HIP(ctx, radix_sort(tiles_in, ids_in, tiles_alt, ids_alt, L.capacity, counters, L.tile_bits, true, empty_tile,
-                            listed, hist, row_total, stream));
+    RGS_HIP(ctx, radix_sort(tiles_in, ids_in, tiles_alt, ids_alt, L.capacity, counters, L.tile_bits, nullptr, true,
+                            empty_tile, listed, row_owner, stream));
     tm.mark(ST_TSORT);
     const uint32_t *inst_tiles = at<uint32_t>(ws, L.inst_tiles_a);
     const uint32_t *inst_ids = at<uint32_t>(ws, L.inst_ids_a);

@@ -95,18 +95,21 @@ struct TileShape {
 // given the whole view; its parameters go to the crossing list (kCrossingDoubles
 // doubles per entry, at most crossing_cap entries, *crossing_count zero on
 // entry), and a second kernel bounds its box by the part of the quad inside
-// the view frustum.  Entries beyond the cap keep the whole view.
+// the view frustum.  Entries beyond the cap keep the whole view.  part_max[w]
+// receives the largest depth key of the views that the w-th 64 Gaussians keep
+// (0 for none; an upper bound where crossing quads are culled later).
 constexpr int kCrossingDoubles = 12;
 hipError_t launch_preprocess(const rgs_gaussians &g, const DevView *views, int n_views, const DevOptions &opt,
                              float4 *records, uint32_t *depth_keys, uint2 *boxes, uint2 *bin_boxes, Conic *conics,
                              uint32_t *tile_counts, double *crossing, int64_t *crossing_count,
-                             uint32_t crossing_cap, hipStream_t stream);
+                             uint32_t crossing_cap, uint32_t *part_max, hipStream_t stream);
 
-// Stable LSD radix sort of (key, value) pairs on bits [0, bits), 8-bit digits
-// (with `iota` the input values are not read: they are the positions 0, 1,
-// 2, ...)
-// (radix_passes(bits) passes of a per-workgroup digit histogram, a scan of
-// each digit's row over the workgroups, and a stable scatter).  n_dev (may
+// Stable LSD radix sort of (key, value) pairs on `bits` bits or, with `range`,
+// on the bits that key - range->base can have (bits = 32 then).  The bits are spread over
+// radix_passes(bits) passes of digits of up to 11 bits, each a
+// per-workgroup digit histogram, a scan of each digit over the workgroups (a
+// launch of its own for large sorts) and a stable scatter.  With `iota` the
+// input values are not read: they are the positions 0, 1, 2, ...  n_dev (may
 // be null) holds a device-side element count, clamped to n_max.  With
 // `drop`, elements whose key equals drop_key leave the sort in the first
 // pass; the kept elements end up sorted in [0, *kept_out) (int64, device,
@@ -114,10 +117,19 @@ hipError_t launch_preprocess(const rgs_gaussians &g, const DevView *views, int n
 // result lands in the primary buffers when the pass count is even, else in
 // the alternates.
 int radix_passes(int bits);
+// Range of the kept keys: none lies below base; the largest of
+// part_max[0, n_parts) (device) is at least the largest of them and is written to *kmax.
+struct RadixRange {
+    uint32_t base;
+    const uint32_t *part_max;
+    int n_parts;
+    uint32_t *kmax;
+};
 hipError_t radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, int64_t n_max,
-                      const int64_t *n_dev, int bits, bool drop, uint32_t drop_key, int64_t *kept_out,
-                      uint32_t *hist, uint32_t *row_total, hipStream_t stream, bool iota = false);
-size_t radix_hist_entries(int64_t n_max);
+                      const int64_t *n_dev, int bits, const RadixRange *range, bool drop, uint32_t drop_key,
+                      int64_t *kept_out, uint32_t *scratch, hipStream_t stream, bool iota = false);
+// Words of `scratch` that a sort of up to n_max items needs (16-byte aligned).
+size_t radix_scratch_words(int64_t n_max, int bits, bool ranged);
 
 // Binning scan over the depth order (Gaussian-view order[k] at position k,
 // sorted key keys[k], 0xffffffff when culled; positions k < *n_dev, at most

@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
                                                     Conic *__restrict__ conics, uint32_t *__restrict__ tile_counts,
                                                     double *__restrict__ crossing,
                                                     unsigned long long *__restrict__ crossing_count,
-                                                    uint32_t crossing_cap)
+                                                    uint32_t crossing_cap, uint32_t *__restrict__ part_max)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -184,6 +184,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
     const double kappa_o = -2.0 * log(opt.p_min / o);
     const float log2o_o = (float)log2(o);
 
+    uint32_t top_key = 0u;  // largest depth key of this thread's kept views
     for (int v = 0; v < n_views; ++v) {
         const DevView &V = views[v];
         const size_t idx = (size_t)v * n + i;
@@ -507,10 +508,22 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
         // culled views' records are never read
         if (cnt && !coloured) colour_view<DEG>(sh_lds, m, V, rc, slot);
         depth_keys[idx] = cnt ? key : 0xffffffffu;
+        if (cnt) top_key = max(top_key, key);
         tile_counts[idx] = cnt;
         boxes[idx] = box;
         bin_boxes[idx] = bin;
     }
+    // the wave's largest key (lanes past n have returned: an LDS maximum instead
+    // of a lane reduction)
+    __shared__ uint32_t wave_top[4];
+    const int wave = threadIdx.x >> 6;
+    wave_top[wave] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    atomicMax(&wave_top[wave], top_key);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if ((threadIdx.x & 63) == 0) part_max[i >> 6] = wave_top[wave];
 }
 
 // Box of a quad with a vertex at z <= 0 (Sec. 4.1 draws the quad unclipped;
@@ -634,7 +647,7 @@ __global__ __launch_bounds__(kClipBlock) void k_clip_crossing(const double *__re
 hipError_t launch_preprocess(const rgs_gaussians &g, const DevView *views, int n_views, const DevOptions &opt,
                              float4 *records, uint32_t *depth_keys, uint2 *boxes, uint2 *bin_boxes, Conic *conics,
                              uint32_t *tile_counts, double *crossing, int64_t *crossing_count,
-                             uint32_t crossing_cap, hipStream_t stream)
+                             uint32_t crossing_cap, uint32_t *part_max, hipStream_t stream)
 {
     const int n = (int)g.n;
     if (n == 0) return hipSuccess;
@@ -648,7 +661,8 @@ hipError_t launch_preprocess(const rgs_gaussians &g, const DevView *views, int n
                                                    views, n_views, opt, records, depth_keys, boxes, bin_boxes,    \
                                                    conics,                                                        \
                                                    tile_counts, crossing,                                         \
-                                                   reinterpret_cast<unsigned long long *>(crossing_count), crossing_cap)
+                                                   reinterpret_cast<unsigned long long *>(crossing_count), crossing_cap,      \
+                                                   part_max)
 #define RGS_PRE_DEG(M)                    \
     switch (g.sh_degree) {                \
     case 0: RGS_PRE(M, 0); break;         \

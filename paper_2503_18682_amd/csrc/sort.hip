@@ -24,13 +24,11 @@ constexpr int scan_tile(int items) { return kThreads * items; }
 constexpr int kScanSelfPrefixBlocks = 1024;
 // Scans of at least this many blocks write the row owner map in row order.
 constexpr int kScanRowOrderBlocks = 4096;
-// Radix sort: the keys per thread of a pass (ITEMS: 4, 8 or 16) are chosen
-// per sort from its size.  More keys per workgroup amortise a workgroup's
-// per-digit work on large sorts; fewer give small sorts enough workgroups to
-// fill the CUs and a shorter serial ranking chain.
-constexpr int kRadixItemsMin = 4;
-constexpr int radix_tile(int items) { return kThreads * items; }
-constexpr int kBins = 256;                         // 8-bit digits
+// Radix sort: digits of up to 11 bits, so that a 32-bit key takes 3 passes and a tile id one or two.
+constexpr int kMaxDigitBits = 11;
+constexpr int kMaxBins = 1 << kMaxDigitBits;
+constexpr int kHistWordsLog = 12;  // counters of a histogram block (all copies of all bins)
+constexpr int kHistWords = 1 << kHistWordsLog;
 
 // Element count of a device-sized array: a frame whose instance count
 // overflowed the capacity is treated as empty downstream (its status reports
@@ -42,9 +40,10 @@ __device__ __forceinline__ int64_t clamp_count(const int64_t *n_dev, int64_t n_m
     return n <= n_max ? n : 0;
 }
 
-// Inclusive scan across a 256-thread block (4 waves); returns the inclusive
+// Inclusive scan across a block of WAVES waves; returns the inclusive
 // prefix and writes the block total to *total.
-__device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t x, uint32_t *smem /*[kWaves]*/, uint32_t *total)
+template <int WAVES>
+__device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t x, uint32_t *smem /*[WAVES]*/, uint32_t *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t v = x;
@@ -57,7 +56,7 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t x, uint32_t *s
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         const uint32_t t = smem[w];
         if (w < wave) before += t;
         all += t;
@@ -68,160 +67,347 @@ __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t x, uint32_t *s
 }
 
 // ---------------------------------------------------------------- radix sort
-// Digit histogram of one block's items; with `drop`, keys equal to drop_key
-// are left out (they leave the sort in this pass).  Blocks past the
-// device-side count write nothing: the row scan and the scatter only look at
-// the first ceil(n / (256 ITEMS)) blocks.
-template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t n_max,
-                                                         const int64_t *__restrict__ n_dev, int shift, int bits,
-                                                         bool drop, uint32_t drop_key, uint32_t *__restrict__ hist,
-                                                         int nblocks)
+// Digit of one pass: `bits` sorted bits of key - base, spread evenly over the
+// passes.  With kmax (the largest key, on the device, known after the first
+// pass's histogram) the first pass takes kFirstBits bits and the other two share what
+// is left of the bits that key - base can have.
+struct RadixPass {
+    const uint32_t *kmax;  // device, may be null: then `bits` bits are sorted
+    uint32_t base;
+    int bits, pass, passes;
+};
+constexpr int kFirstBits = 9;
+
+struct Digit {
+    uint32_t base, mask;
+    int shift, bits;
+    __device__ __forceinline__ uint32_t of(uint32_t key) const { return ((key - base) >> shift) & mask; }
+};
+
+__device__ __forceinline__ Digit pass_digit(const RadixPass &P)
 {
-    __shared__ uint32_t cnt[kWaves][kBins];
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int64_t n = clamp_count(n_dev, n_max);
-    const int64_t base = (int64_t)blockIdx.x * radix_tile(ITEMS);
-    if (base >= n) return;  // uniform per block
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) cnt[w][tid] = 0;
-    __syncthreads();
-    const uint32_t mask = (1u << bits) - 1u;
-    {
-#pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-            const int64_t idx = base + (int64_t)j * kThreads + tid;
-            if (idx < n) {
-                const uint32_t key = keys[idx];
-                if (!(drop && key == drop_key)) atomicAdd(&cnt[wave][(key >> shift) & mask], 1u);
-            }
+    int shift = 0, bits = 0, total = P.bits, p = 0;
+    if (P.kmax) {
+        bits = kFirstBits;
+        p = 1;
+        if (P.pass > 0) {
+            const uint32_t top = *P.kmax;
+            total = top > P.base ? 32 - __builtin_clz(top - P.base) : 0;
+            total = max(total, kFirstBits);
         }
     }
+    for (; p <= P.pass; ++p) {
+        shift += bits;
+        bits = (total - shift + (P.passes - p) - 1) / (P.passes - p);
+    }
+    return Digit{P.base, (1u << bits) - 1u, shift, bits};
+}
+
+// Block of items of this workgroup: workgroups are dealt to the 8 XCDs in
+// turn, and each XCD takes a contiguous run of the nb blocks.  The blocks in
+// flight on one XCD then write next to each other in every digit's range, and
+// their short runs merge into whole lines in that XCD's L2 (blocks dealt in
+// order leave every line shared by several XCDs, each writing its part to
+// memory).  Returns nb or more when there is none.
+__device__ __forceinline__ int xcd_block(int nb)
+{
+    const int share = (nb + 7) >> 3, k = (int)(blockIdx.x >> 3);
+    return k < share ? (int)(blockIdx.x & 7u) * share + k : nb;
+}
+
+// Words of a block's histogram row in the block-major layout (whole uint4).
+__device__ __forceinline__ int hist_row(int bins) { return max(bins, 4); }
+
+// Digit histogram of one block's items; with `drop`, keys equal to drop_key
+// are left out (they leave the sort in this pass).  Blocks past the
+// device-side count write nothing.  All keys of a thread are loaded before the
+// first is counted.  Up to 8 interleaved copies of each counter (by lane)
+// keep equal digits of a wave off one LDS address.
+template <int THREADS, int ITEMS, bool SELF>
+__global__ __launch_bounds__(THREADS) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t n_max,
+                                                        const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
+                                                        uint32_t drop_key, uint32_t *__restrict__ hist, int nblocks,
+                                                        const uint32_t *__restrict__ part_max, int n_parts,
+                                                        uint32_t *__restrict__ kmax_out)
+{
+    constexpr int TILE = THREADS * ITEMS;
+    __shared__ uint32_t cnt[kHistWords];
+    const int tid = threadIdx.x;
+    if (kmax_out && blockIdx.x == gridDim.x - 1) {  // the extra workgroup: largest key
+        uint32_t top = 0u;
+        constexpr int kStep = 16;
+        for (int i = tid; i < n_parts; i += THREADS * kStep) {
+            uint32_t x[kStep];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) x[j] = part_max[min(i + j * THREADS, n_parts - 1)];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) top = max(top, x[j]);
+        }
+        if (tid == 0) cnt[0] = 0u;
+        __syncthreads();
+        atomicMax(&cnt[0], top);
+        __syncthreads();
+        if (tid == 0) *kmax_out = cnt[0];
+        return;
+    }
+    uint32_t key[ITEMS];
+    auto load = [&](int64_t base, int left) {
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) key[j] = (keys + base)[(uint32_t)min(j * THREADS + tid, left - 1)];
+    };
+    if constexpr (SELF) {  // loads by the launch's bounds do not wait for the count
+        const int64_t base = (int64_t)blockIdx.x * TILE;
+        if (base >= n_max) return;
+        load(base, (int)min(n_max - base, (int64_t)TILE));
+    }
+    const int64_t n = clamp_count(n_dev, n_max);
+    const int nb = (int)((n + TILE - 1) / TILE), block = SELF ? (int)blockIdx.x : xcd_block(nb);
+    if (block >= nb) return;  // uniform per block
+    const int64_t base = (int64_t)block * TILE;
+    const int left = (int)min(n - base, (int64_t)TILE);
+    if constexpr (!SELF) load(base, left);
+    const Digit D = pass_digit(pass);
+    const int bins = 1 << D.bits;
+    const int cshift = min(3, kHistWordsLog - D.bits);  // log2 of the copies
+    for (int i = tid; i < bins << cshift; i += THREADS) cnt[i] = 0u;
     __syncthreads();
-    hist[(size_t)tid * nblocks + blockIdx.x] = cnt[0][tid] + cnt[1][tid] + cnt[2][tid] + cnt[3][tid];
+    const uint32_t copy = tid & ((1u << cshift) - 1u);
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j)
+        if (j * THREADS + tid < left && !(drop && key[j] == drop_key))
+            atomicAdd(&cnt[(D.of(key[j]) << cshift) + copy], 1u);
+    __syncthreads();
+    const int row = SELF ? hist_row(bins) : bins;
+    for (int d = tid; d < row; d += THREADS) {
+        uint32_t x = 0;
+        if (d < bins)
+            for (int c = 0; c < 1 << cshift; ++c) x += cnt[(d << cshift) + c];
+        hist[SELF ? (size_t)block * row + d : (size_t)d * nblocks + block] = x;
+    }
 }
 
 // Exclusive scan of each digit's row hist[d][0..nb) (one block per digit)
 // over the nb = ceil(n / tile) blocks that hold items (tile = keys per block).
 __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks,
                                                               int64_t n_max, const int64_t *__restrict__ n_dev,
-                                                              int tile, uint32_t *__restrict__ row_total)
+                                                              RadixPass pass, int tile,
+                                                              uint32_t *__restrict__ row_total)
 {
     __shared__ uint32_t smem[kWaves];
+    if (blockIdx.x >> pass_digit(pass).bits) return;  // no such digit in this pass
     const int64_t n = clamp_count(n_dev, n_max);
     const int nb = (int)std::min<int64_t>((n + tile - 1) / tile, nblocks);
     uint32_t *row = hist + (size_t)blockIdx.x * nblocks;
+    constexpr int kPer = 8;  // entries per thread and step: a contiguous run, scanned in registers
     uint32_t carry = 0;
-    for (int base = 0; base < nb; base += kThreads) {
-        const int i = base + threadIdx.x;
-        const uint32_t x = i < nb ? row[i] : 0u;
+    for (int base = 0; base < nb; base += kThreads * kPer) {
+        uint32_t x[kPer], sum = 0;
+        const int i0 = base + threadIdx.x * kPer;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) x[j] = i0 + j < nb ? row[i0 + j] : 0u;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) sum += x[j];
         uint32_t tot;
-        const uint32_t inc = block_inclusive_scan(x, smem, &tot);
-        if (i < nb) row[i] = carry + inc - x;
+        uint32_t run = carry + block_inclusive_scan<kWaves>(sum, smem, &tot) - sum;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (i0 + j < nb) row[i0 + j] = run;
+            run += x[j];
+        }
         carry += tot;
     }
     if (threadIdx.x == 0) row_total[blockIdx.x] = carry;
 }
 
-// Stable scatter of one block's items by digit.  Each wave ranks 8 rounds of
-// 64 consecutive items: lanes holding the same digit are found with one ballot
+// Stable scatter of one block's items by digit.  A thread's keys and values
+// are all loaded first, with no branch around the loads, so that a wave waits
+// for memory once and not once per round; the digits' output positions are
+// summed up while they are in flight.  Each wave then ranks ITEMS rounds of 64
+// consecutive items: lanes holding the same digit are found with one ballot
 // per digit bit, ranked by popcount of the lower peers, and a per-wave LDS
-// counter per digit carries the rank across rounds.  Items are then staged in
+// counter per digit carries the rank across rounds.  Items are staged in
 // LDS in block-local sorted order and written out in runs of equal digits.
-// With `drop`, keys equal to drop_key are not written, and block 0 stores
-// the number of items kept (the sum of the digit totals) in *kept_out.
-template <int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_radix_scatter(
+// With `drop`, keys equal to drop_key are not written, and the first block
+// stores the number of items kept (the sum of the digit totals) in *kept_out.
+// SELF: hist is block-major and unscanned (rows of hist_row(bins) words); each
+// block sums the rows before its own (and all of them for the digit bases)
+// itself, so the pass needs no scan launch.  Otherwise hist is digit-major and
+// scanned, with row_total.
+template <int THREADS, int ITEMS, bool SELF>
+__global__ __launch_bounds__(THREADS, SELF ? 4 : 5) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
-    uint32_t *__restrict__ vals_out, int64_t n_max, const int64_t *__restrict__ n_dev, int shift, int bits,
-    bool drop, uint32_t drop_key, int64_t *__restrict__ kept_out, const uint32_t *__restrict__ hist,
+    uint32_t *__restrict__ vals_out, int64_t n_max, const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
+    uint32_t drop_key, int64_t *__restrict__ kept_out, const uint32_t *__restrict__ hist,
     const uint32_t *__restrict__ row_total, int nblocks)
 {
-    __shared__ uint32_t wave_cnt[kWaves][kBins];
-    __shared__ uint32_t block_start[kBins];
-    __shared__ uint32_t out_base[kBins];
-    __shared__ uint32_t s_keys[radix_tile(ITEMS)];
-    __shared__ uint32_t s_vals[radix_tile(ITEMS)];
-    __shared__ uint32_t smem[kWaves];
-    __shared__ uint32_t block_valid;
+    constexpr int TILE = THREADS * ITEMS, WAVES = THREADS / 64;
+    constexpr int kCntWords = WAVES * kMaxBins / 2, kSumWords = SELF ? 8 * THREADS : 0;
+    constexpr int kMemA = 2 * TILE > kCntWords ? 2 * TILE : kCntWords;
+    // partial sums of the histogram, per-wave digit counters (16 bits each) and
+    // staged items take turns
+    __shared__ uint4 s_mem4[(kMemA > kSumWords ? kMemA : kSumWords) / 4];
+    __shared__ uint32_t s_base[kMaxBins];   // digit: output position of its first item, later minus s_start
+    __shared__ uint16_t s_start[kMaxBins];  // digit: block-local position of its first item
+    __shared__ uint32_t smem[WAVES];
+    uint32_t *const s_mem = reinterpret_cast<uint32_t *>(s_mem4);
+    uint16_t *const wave_cnt = reinterpret_cast<uint16_t *>(s_mem);
+    uint32_t *const s_keys = s_mem, *const s_vals = s_mem + TILE;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int at0 = wave * (TILE / WAVES) + lane;
+    uint32_t key[ITEMS], val[ITEMS];
+    // small sorts load at once, by the launch's bounds; large ones know their block first
+    auto load = [&](int64_t base, int left) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) key[r] = (keys_in + base)[(uint32_t)min(at0 + r * 64, left - 1)];
+        if (vals_in) {
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) val[r] = (vals_in + base)[(uint32_t)min(at0 + r * 64, left - 1)];
+        } else {
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) val[r] = (uint32_t)(base + at0 + r * 64);
+        }
+    };
+    if constexpr (SELF) {
+        const int64_t base = (int64_t)blockIdx.x * TILE;
+        if (base >= n_max) return;
+        load(base, (int)min(n_max - base, (int64_t)TILE));
+    }
     const int64_t n = clamp_count(n_dev, n_max);
-    const int64_t base = (int64_t)blockIdx.x * radix_tile(ITEMS);
-    if (base >= n) {  // uniform per block
-        if (drop && blockIdx.x == 0 && tid == 0) *kept_out = 0;
+    const Digit D = pass_digit(pass);
+    const int nb = (int)((n + TILE - 1) / TILE), block = SELF ? (int)blockIdx.x : xcd_block(nb);
+    if (block >= nb) {  // uniform per block
+        if (drop && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
         return;
     }
-    const uint32_t mask = (1u << bits) - 1u;
+    const int64_t base = (int64_t)block * TILE;
+    const int left = (int)min(n - base, (int64_t)TILE);
+    if constexpr (!SELF) load(base, left);
+    const int bins = 1 << D.bits;
 
-    // digit bases: exclusive scan of the row totals (thread = digit)
-    uint32_t dig_total;
-    const uint32_t rt = row_total[tid];
-    const uint32_t dig_base = block_inclusive_scan(rt, smem, &dig_total) - rt;
-    if (drop && blockIdx.x == 0 && tid == 0) *kept_out = (int64_t)dig_total;
+    // output position of each digit's first item of this block
+    if constexpr (SELF) {
+        // each thread sums four neighbouring digits over every groups-th row
+        const int row = hist_row(bins), quads = row >> 2;
+        const int quad = tid & (quads - 1), group = tid / quads, groups = THREADS / quads;
+        uint4 all = make_uint4(0u, 0u, 0u, 0u), pre = all;
+        constexpr int kStep = 16;
+        const uint4 *src = reinterpret_cast<const uint4 *>(hist) + quad;
+        for (int r0 = group; r0 < nb; r0 += groups * kStep) {
+            uint4 x[kStep];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) wave_cnt[w][tid] = 0;
+            for (int j = 0; j < kStep; ++j) x[j] = src[(size_t)(min(r0 + j * groups, nb - 1) * quads)];
+#pragma unroll
+            for (int j = 0; j < kStep; ++j) {
+                const int r = r0 + j * groups;
+                const uint32_t in = r < nb ? ~0u : 0u, before = r < block ? ~0u : 0u;
+                all.x += x[j].x & in; all.y += x[j].y & in; all.z += x[j].z & in; all.w += x[j].w & in;
+                pre.x += x[j].x & before; pre.y += x[j].y & before; pre.z += x[j].z & before; pre.w += x[j].w & before;
+            }
+        }
+        s_mem4[tid] = all;
+        s_mem4[THREADS + tid] = pre;
+        __syncthreads();
+    }
+    uint32_t dig_carry = 0;
+#pragma unroll 1
+    for (int d0 = 0; d0 < bins; d0 += THREADS) {
+        const int d = d0 + tid;
+        uint32_t pre = 0, all = 0;
+        if (d < bins) {
+            if constexpr (SELF) {
+                const int row = hist_row(bins), groups = 4 * THREADS / row;
+                for (int g = 0; g < groups; ++g) {
+                    all += s_mem[g * row + d];
+                    pre += s_mem[4 * THREADS + g * row + d];
+                }
+            } else {
+                all = row_total[d];
+                pre = hist[(size_t)d * nblocks + block];
+            }
+        }
+        uint32_t dig_tot;
+        const uint32_t dig_base = dig_carry + block_inclusive_scan<WAVES>(all, smem, &dig_tot) - all;
+        dig_carry += dig_tot;
+        if (d < bins) s_base[d] = dig_base + pre;
+    }
+    if (drop && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
+    __syncthreads();
+    for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
     __syncthreads();
 
-    uint32_t my_key[ITEMS], my_val[ITEMS], my_rank[ITEMS];
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    // position of each item among the items of its digit in its wave
+    uint16_t *const cnt = wave_cnt + wave * bins;
+    uint32_t rank[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-        const int64_t idx = base + (int64_t)wave * (radix_tile(ITEMS) / kWaves) + r * 64 + lane;
-        const uint32_t key = idx < n ? keys_in[idx] : 0u;
-        const bool valid = idx < n && !(drop && key == drop_key);
-        my_key[r] = key;
-        my_val[r] = valid ? (vals_in ? vals_in[idx] : (uint32_t)idx) : 0u;
-        const uint32_t d = (key >> shift) & mask;
-        unsigned long long peers = __ballot(valid);
-        for (int b = 0; b < bits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const unsigned long long m = __ballot(bit);
-            peers &= bit ? m : ~m;
+        const bool valid = at0 + r * 64 < left && !(drop && key[r] == drop_key);
+        const uint32_t d = D.of(key[r]);
+        const uint64_t some = __ballot(valid);
+        uint32_t lo = (uint32_t)some, hi = (uint32_t)(some >> 32);  // lanes of the same digit
+        for (int b = 0; b < D.bits; ++b) {
+            const int32_t bit = (int32_t)(d << (31 - b)) >> 31;  // 0 or all ones
+            const uint64_t m = __ballot(bit != 0);
+            lo &= ~((uint32_t)m ^ (uint32_t)bit);
+            hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
         }
-        const uint32_t rank = __popcll(peers & lt_mask);
-        const uint32_t prior = valid ? wave_cnt[wave][d] : 0u;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        const uint32_t prior = cnt[d];
         __builtin_amdgcn_wave_barrier();
-        if (valid && rank == 0) wave_cnt[wave][d] = prior + (uint32_t)__popcll(peers);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (valid && below == 0) cnt[d] = (uint16_t)(prior + (uint32_t)(__popc(lo) + __popc(hi)));
         __builtin_amdgcn_wave_barrier();
-        my_rank[r] = valid ? prior + rank : 0xffffffffu;
+        rank[r] = valid ? prior + below : 0xffffffffu;
     }
     __syncthreads();
-    {
-        // prefix over waves for digit tid, then block-local digit starts
+
+    // per digit: prefix over the waves, block-local start
+    uint32_t carry = 0;
+#pragma unroll 1
+    for (int d0 = 0; d0 < bins; d0 += THREADS) {
+        const int d = d0 + tid;
         uint32_t run = 0;
+        if (d < bins)
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const uint32_t c = wave_cnt[w][tid];
-            wave_cnt[w][tid] = run;
-            run += c;
-        }
+            for (int w = 0; w < WAVES; ++w) {
+                const uint32_t c = wave_cnt[w * bins + d];
+                wave_cnt[w * bins + d] = (uint16_t)run;
+                run += c;
+            }
         uint32_t tot;
-        const uint32_t start = block_inclusive_scan(run, smem, &tot) - run;
-        block_start[tid] = start;
-        if (tid == 0) block_valid = tot;
-        out_base[tid] = dig_base + hist[(size_t)tid * nblocks + blockIdx.x] - start;
+        const uint32_t start = carry + block_inclusive_scan<WAVES>(run, smem, &tot) - run;
+        carry += tot;
+        if (d < bins) {
+            s_start[d] = (uint16_t)start;
+            s_base[d] -= start;
+        }
     }
+    const int count = (int)carry;  // items of this block that stay in the sort
+    const uint32_t n32 = (uint32_t)n;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (rank[r] != 0xffffffffu) {
+            const uint32_t d = D.of(key[r]);
+            rank[r] += (uint32_t)s_start[d] + cnt[d];
+        }
+    __syncthreads();  // the counters give way to the staged items
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r)
+        if (rank[r] != 0xffffffffu) {
+            s_keys[rank[r]] = key[r];
+            s_vals[rank[r]] = val[r];
+        }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-        if (my_rank[r] == 0xffffffffu) continue;
-        const uint32_t d = (my_key[r] >> shift) & mask;
-        const uint32_t pos = block_start[d] + wave_cnt[wave][d] + my_rank[r];
-        s_keys[pos] = my_key[r];
-        s_vals[pos] = my_val[r];
-    }
-    __syncthreads();
-    const int count = (int)block_valid;  // items of this block that stay in the sort
-    for (int p = tid; p < count; p += kThreads) {
-        const uint32_t key = s_keys[p];
-        const uint32_t d = (key >> shift) & mask;
-        const uint32_t dst = out_base[d] + (uint32_t)p;
-        if ((int64_t)dst < n) {
-            keys_out[dst] = key;
-            vals_out[dst] = s_vals[p];
+        const int p = r * THREADS + tid;
+        if (p < count) {
+            const uint32_t k = s_keys[p];
+            const uint32_t dst = s_base[D.of(k)] + (uint32_t)p;
+            if (dst < n32) {
+                keys_out[dst] = k;
+                vals_out[dst] = s_vals[p];
+            }
         }
     }
 }
@@ -420,8 +606,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const in
         lr += r[j];
     }
     uint32_t tot;
-    const uint32_t bt = block_inclusive_scan(lt, smem, &tot) - lt;
-    const uint32_t br = block_inclusive_scan(lr, smem, &tot) - lr;
+    const uint32_t bt = block_inclusive_scan<kWaves>(lt, smem, &tot) - lt;
+    const uint32_t br = block_inclusive_scan<kWaves>(lr, smem, &tot) - lr;
     unsigned long long pre[2], all[2];
     if (self_prefix) {
         block_prefix_pairs(block_sums, (int)gridDim.x, (int)blockIdx.x, pre, all);
@@ -642,7 +828,7 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     // buckets in decreasing order: bucket b starts after all items of buckets > b
     const uint32_t hb = hist[kSchedBuckets - 1 - threadIdx.x];
     uint32_t tot;
-    const uint32_t before = block_inclusive_scan(hb, smem, &tot) - hb;
+    const uint32_t before = block_inclusive_scan<kWaves>(hb, smem, &tot) - hb;
     base[kSchedBuckets - 1 - threadIdx.x] = before;
     cnt[threadIdx.x] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) *n_items = tot;
@@ -667,59 +853,81 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
 
 }  // namespace
 
-int radix_passes(int bits) { return bits <= 0 ? 0 : (bits + 7) / 8; }
-
-// sized for the smallest tile, so any choice of ITEMS fits
-size_t radix_hist_entries(int64_t n_max)
-{
-    const int64_t tile = radix_tile(kRadixItemsMin);
-    return (size_t)kBins * (size_t)((n_max + tile - 1) / tile + 1);
-}
+int radix_passes(int bits) { return bits <= 0 ? 0 : (bits + kMaxDigitBits - 1) / kMaxDigitBits; }
 
 namespace {
-// Keys per thread by sort size, from timings of the depth and tile sorts of a
-// 1080p frame (0.5M and 2.6M keys) and of an 8-view batch (24M and 91M).
-int radix_items_for(int64_t n_max) { return n_max <= (int64_t(1) << 20) ? 4 : n_max <= (int64_t(1) << 24) ? 8 : 16; }
+// Workgroup shapes, from timings of whole sorts (rocprofv3; graph replays).
+// Up to kSelfMax items a pass is two launches, and the shortest chain in a
+// workgroup wins: three passes over 0.5M depth keys took 34 us of scatter at
+// 512 x 4 and 37 at 1024 x 4 or 512 x 8.  Above it a pass has a scan launch of its
+// own and 512 x 8 is best: a sort of 22.5M depth keys and one of 66M tile ids (8 views)
+// took 0.93 ms of scatter and histograms of it, 1.10 ms at 256 x 16, 0.99 ms at 512 x 16.
+constexpr int kSelfThreads = 512, kSelfItems = 4;
+constexpr int kScanThreads = 512, kScanItems = 8;
+constexpr int64_t kSelfMax = int64_t(1) << 20;
+}  // namespace
 
-template <int ITEMS>
-void radix_pass(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *vo, int64_t n_max,
-                const int64_t *pn, int shift, int pbits, bool pdrop, uint32_t drop_key, int64_t *kept_out,
-                uint32_t *hist, uint32_t *row_total, hipStream_t stream)
+namespace {
+// The widest digit of any pass of a sort on `bits` bits; with a key range the
+// first pass has kFirstBits bits and the others up to the widest.
+int widest_digit(int bits, bool ranged, int pass)
 {
-    const int nblocks = (int)((n_max + radix_tile(ITEMS) - 1) / radix_tile(ITEMS));
-    k_radix_hist<ITEMS><<<nblocks, kThreads, 0, stream>>>(ki, n_max, pn, shift, pbits, pdrop, drop_key, hist, nblocks);
-    k_radix_scan_rows<<<kBins, kThreads, 0, stream>>>(hist, nblocks, n_max, pn, radix_tile(ITEMS), row_total);
-    k_radix_scatter<ITEMS><<<nblocks, kThreads, 0, stream>>>(ki, vi, ko, vo, n_max, pn, shift, pbits, pdrop, drop_key,
-                                                             kept_out, hist, row_total, nblocks);
+    if (ranged) return pass == 0 ? kFirstBits : kMaxDigitBits;
+    const int passes = radix_passes(bits);
+    return passes == 0 ? 0 : (bits + passes - 1) / passes;
 }
 }  // namespace
 
+// Histogram rows of every block, and the digit totals where they are scanned
+// in a launch of their own.
+size_t radix_scratch_words(int64_t n_max, int bits, bool ranged)
+{
+    const bool self = n_max <= kSelfMax;
+    const int64_t tile = self ? kSelfThreads * kSelfItems : kScanThreads * kScanItems;
+    const size_t row = std::max((size_t)1 << widest_digit(bits, ranged, 1), (size_t)4);
+    return row * (size_t)((n_max + tile - 1) / tile) + (self ? 0 : row);
+}
+
 hipError_t radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, int64_t n_max,
-                      const int64_t *n_dev, int bits, bool drop, uint32_t drop_key, int64_t *kept_out,
-                      uint32_t *hist, uint32_t *row_total, hipStream_t stream, bool iota)
+                      const int64_t *n_dev, int bits, const RadixRange *range, bool drop, uint32_t drop_key,
+                      int64_t *kept_out, uint32_t *scratch, hipStream_t stream, bool iota)
 {
     const int passes = radix_passes(bits);
-    const int items = radix_items_for(n_max);
     if (n_max <= 0 || passes == 0) {
         if (drop) k_fill_u32<<<1, kThreads, 0, stream>>>(reinterpret_cast<uint32_t *>(kept_out), 0u, 2);
         return hipGetLastError();
     }
     uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
-    int shift = 0;
     for (int p = 0; p < passes; ++p) {
-        // spread the bits evenly over the passes (each <= 8); the first pass
-        // drops, the later ones sort the kept items
-        const int pbits = (bits - shift + (passes - p) - 1) / (passes - p);
+        const int wide = 1 << widest_digit(bits, range != nullptr, p);
+        uint32_t *const hist = scratch;
+        // the first pass drops, the later ones sort the kept items
         const bool pdrop = drop && p == 0;
         const int64_t *pn = drop && p > 0 ? kept_out : n_dev;
         const uint32_t *pvi = iota && p == 0 ? nullptr : vi;
-        if (items == 4)
-            radix_pass<4>(ki, pvi, ko, vo, n_max, pn, shift, pbits, pdrop, drop_key, kept_out, hist, row_total, stream);
-        else if (items == 8)
-            radix_pass<8>(ki, pvi, ko, vo, n_max, pn, shift, pbits, pdrop, drop_key, kept_out, hist, row_total, stream);
-        else
-            radix_pass<16>(ki, pvi, ko, vo, n_max, pn, shift, pbits, pdrop, drop_key, kept_out, hist, row_total, stream);
-        shift += pbits;
+        const RadixPass pass{range ? range->kmax : nullptr, range ? range->base : 0u, bits, p, passes};
+        // the first histogram launch also finds the largest key, in one more workgroup
+        const bool top = range && p == 0;
+        const uint32_t *parts = top ? range->part_max : nullptr;
+        const int n_parts = top ? range->n_parts : 0;
+        uint32_t *kmax_out = top ? range->kmax : nullptr;
+        if (n_max <= kSelfMax) {
+            constexpr int TH = kSelfThreads, IT = kSelfItems, tile = TH * IT;
+            const int nblocks = (int)((n_max + tile - 1) / tile), grid = (nblocks + 7) & ~7;
+            k_radix_hist<TH, IT, true><<<grid + top, TH, 0, stream>>>(ki, n_max, pn, pass, pdrop, drop_key, hist,
+                                                                      nblocks, parts, n_parts, kmax_out);
+            k_radix_scatter<TH, IT, true><<<grid, TH, 0, stream>>>(ki, pvi, ko, vo, n_max, pn, pass, pdrop, drop_key,
+                                                                   kept_out, hist, nullptr, nblocks);
+        } else {
+            constexpr int TH = kScanThreads, IT = kScanItems, tile = TH * IT;
+            const int nblocks = (int)((n_max + tile - 1) / tile), grid = (nblocks + 7) & ~7;
+            uint32_t *const row_total = scratch + (size_t)wide * nblocks;
+            k_radix_hist<TH, IT, false><<<grid + top, TH, 0, stream>>>(ki, n_max, pn, pass, pdrop, drop_key, hist,
+                                                                       nblocks, parts, n_parts, kmax_out);
+            k_radix_scan_rows<<<wide, kThreads, 0, stream>>>(hist, nblocks, n_max, pn, pass, tile, row_total);
+            k_radix_scatter<TH, IT, false><<<grid, TH, 0, stream>>>(ki, pvi, ko, vo, n_max, pn, pass, pdrop, drop_key,
+                                                                    kept_out, hist, row_total, nblocks);
+        }
         uint32_t *t;
         t = ki; ki = ko; ko = t;
         t = vi; vi = vo; vo = t;

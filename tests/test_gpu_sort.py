@@ -1,0 +1,75 @@
+"""Depth and tile sorts of the binning at the sizes where a pass changes shape:
+one workgroup and its edges, the largest sort without a scan launch and the
+next one, depth ranges from one key to every exponent, and tile counts of
+one, two and three digits."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import instance_lists, listed_count, read, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def r():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_18682_amd import renderer as R
+
+    rr = R.Renderer(0)
+    yield rr
+    rr.close()
+
+
+def _scene(n, depths, seed):
+    """Gaussians of about a pixel spread over the view of an identity camera."""
+    rng = np.random.default_rng(seed)
+    if depths == "same":
+        z = np.full(n, 3.0)
+    elif depths == "wide":
+        z = np.exp(rng.uniform(np.log(0.21), np.log(1e30), n))
+    else:
+        z = rng.uniform(1.0, 20.0, n)
+    z = z.astype(np.float32)
+    z64 = z.astype(np.float64)
+    means = np.stack([rng.uniform(-0.55, 0.55, n) * z64, rng.uniform(-0.45, 0.45, n) * z64, z64])
+    scales = np.log(0.003 * z64)[None] + rng.normal(0, 0.2, (3, n))
+    g = dict(means=means, log_scales=scales, quats=rng.standard_normal((4, n)),
+             opacity_logits=rng.normal(0, 1, n), sh=rng.normal(0, 0.3, (1, 3, n)))
+    g = {k: torch.from_numpy(np.ascontiguousarray(v, dtype=np.float32)).cuda() for k, v in g.items()}
+    return dict(g, sh_degree=0), z
+
+
+CASES = [(1, "linear", 64, 48, 1), (2047, "same", 320, 240, 1), (2048, "wide", 8, 8, 1), (2049, "linear", 640, 480, 1),
+         (4097, "wide", 1000, 900, 2), (40000, "linear", 5000, 4300, 1), ((1 << 20) - 1, "linear", 640, 480, 1),
+         ((1 << 20) + 1, "wide", 640, 480, 1), (700_000, "wide", 1024, 1024, 3)]
+
+
+@pytest.mark.parametrize("n,depths,w,h,views", CASES)
+def test_sorted_order_and_lists(r, n, depths, w, h, views):
+    say(f"case sort n {n} depths {depths} {w}x{h} x{views}")
+    g, z = _scene(n, depths, 7)
+    cam = dict(w2c=np.eye(3, 4), fx=0.8 * w, fy=0.8 * w, cx=w / 2, cy=h / 2, width=w, height=h)
+    cams = [cam] * views
+    opts = dict(tile_w=8, tile_h=8)
+    outs, (buf, ws) = r.render(g, cams, opts, keep_workspace=True)
+    lay = r.layout(n, cams, ws.capacity, 0, opts)
+    counts = read(buf, lay.tile_counts, n * views, np.uint32)
+    kept = np.nonzero(counts)[0]
+    c = read(buf, lay.counters, 8, np.int64)
+    assert c[4] == len(kept) and c[0] == counts.astype(np.int64).sum()
+    key = z.view(np.uint32)[kept % n]
+    want = kept[np.argsort(key, kind="stable")]
+    order = read(buf, lay.order, len(kept), np.uint32)
+    assert np.array_equal(order, want)
+    assert np.array_equal(read(buf, lay.depth_keys, len(kept), np.uint32), np.sort(key))
+    tiles, ids = instance_lists(buf, lay)
+    assert listed_count(buf, lay) == len(tiles) and (len(tiles) > 0 or n == 1)
+    place = np.zeros(n * views, np.int64)
+    place[order] = np.arange(len(order))
+    # by tile, then by depth order; no instance twice
+    both = tiles * (n * views) + place[ids]
+    assert np.all(np.diff(both) > 0)
+    rng = read(buf, lay.tile_ranges, 2 * lay.total_tiles, np.uint32).reshape(-1, 2).astype(np.int64)
+    assert np.array_equal(rng[:, 1] - rng[:, 0], np.bincount(tiles, minlength=lay.total_tiles))
