@@ -44,7 +44,7 @@ struct Layout {
     size_t crossing;          // quads with a vertex at z <= 0, awaiting frustum clipping
     uint32_t crossing_cap;    // entries of the crossing list
     size_t inst_tiles_a, inst_tiles_b, inst_ids_a, inst_ids_b, ranges, sched, tile_order;
-    size_t row_offsets, row_owner, item_clock;
+    size_t bin_scratch, item_clock;
     size_t record_grads, total;
     int64_t nv_records, capacity, total_tiles;
     int tile_w, tile_h, tile_bits;
@@ -334,7 +334,6 @@ rgs_status compute_layout(rgs_context *ctx, int64_t n, const rgs_camera *cams, i
     L.crossing_cap = (uint32_t)std::min<int64_t>((int64_t)NV, kCrossingCap);
     L.crossing = take((size_t)L.crossing_cap * kCrossingDoubles * sizeof(double));
     L.offsets = take(NV * 4);
-    L.row_offsets = take(NV * 4);
     L.block_sums = take(scan_block_entries((int64_t)NV) * 8);
     L.inst_tiles_a = take((size_t)capacity * 4);
     L.inst_tiles_b = take((size_t)capacity * 4);
@@ -343,8 +342,7 @@ rgs_status compute_layout(rgs_context *ctx, int64_t n, const rgs_camera *cams, i
     L.ranges = take((size_t)tiles * 8);
     L.sched = take(sched_words() * 4);
     L.tile_order = take((size_t)tiles * 2 * 4);  // work items: up to two per tile
-    // the row owners of the binning scan, whose place the tile sort's scratch takes after the emission
-    L.row_owner = take(std::max((size_t)capacity, radix_scratch_words(capacity, L.tile_bits, false)) * 4);
+    L.bin_scratch = take(bin_scratch_words(capacity, L.tile_bits) * 4);
     L.item_clock = take((size_t)tiles * 2 * 8);  // per work item, for per-view completion clocks
     L.record_grads = (flags & RGS_WS_BACKWARD) ? take(NV * grad_floats(opts->mip) * sizeof(float)) : 0;
     L.total = off;
@@ -542,20 +540,17 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     tm.mark(ST_DSORT);
     const uint32_t *order = at<uint32_t>(ws, L.order_a);
     uint32_t *offsets = at<uint32_t>(ws, L.offsets);
-    uint32_t *row_offsets = at<uint32_t>(ws, L.row_offsets);
-    uint32_t *row_owner = at<uint32_t>(ws, L.row_owner);
+    uint32_t *bin_scratch = at<uint32_t>(ws, L.bin_scratch);
     uint2 *sorted_boxes = at<uint2>(ws, L.sorted_boxes);
     RGS_HIP(ctx, binning_scan(at<uint32_t>(ws, L.keys_a), bin_boxes, order, NV, kept, s.w, s.h, L.capacity, offsets,
-                              row_offsets, row_owner, sorted_boxes,
-                              at<unsigned long long>(ws, L.block_sums), counters, stream));
+                              bin_scratch, sorted_boxes, at<unsigned long long>(ws, L.block_sums), counters, stream));
     tm.mark(ST_SCAN);
-    const uint32_t empty_tile = (uint32_t)((int64_t(1) << L.tile_bits) - 1);
-    RGS_HIP(ctx, launch_emit(order, offsets, row_offsets, row_owner, sorted_boxes, conics, views, g.n, n_views, counters,
-                             L.capacity, s.w, s.h, empty_tile, tiles_in, ids_in, ranges, L.total_tiles, sched,
-                             emit_grid(ctx->num_cus), stream));
-    tm.mark(ST_EMIT);
-    RGS_HIP(ctx, radix_sort(tiles_in, ids_in, tiles_alt, ids_alt, L.capacity, counters, L.tile_bits, nullptr, true,
-                            empty_tile, listed, row_owner, stream));
+    for (const bool emit : {true, false}) {
+        RGS_HIP(ctx, emit_and_sort(order, offsets, bin_scratch, sorted_boxes, conics, views, g.n, counters, L.capacity,
+                                   s.w, s.h, L.tile_bits, tiles_in, ids_in, tiles_alt, ids_alt, listed, ranges,
+                                   L.total_tiles, sched, stream, emit));
+        if (emit) tm.mark(ST_EMIT);
+    }
     tm.mark(ST_TSORT);
     const uint32_t *inst_tiles = at<uint32_t>(ws, L.inst_tiles_a);
     const uint32_t *inst_ids = at<uint32_t>(ws, L.inst_ids_a);

@@ -49,6 +49,21 @@ struct ConicFrame {
     bool bounded;
 };
 
+// 1 / sqrt(x) for x > 0 well inside the double range: the hardware estimate and
+// two Newton steps (errors of a few units in the last place, as a chain of
+// library divisions and square roots has).
+__device__ inline double fast_rsqrt(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    const double h = 0.5 * x;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const double e = __builtin_fma(-h * y, y, 0.5);
+        y = __builtin_fma(y, e, y);
+    }
+    return y;
+}
+
 __device__ inline ConicFrame conic_frame(const Conic &C)
 {
 #pragma clang fp contract(off)
@@ -56,18 +71,21 @@ __device__ inline ConicFrame conic_frame(const Conic &C)
     const double det = C.P00 * C.P11 - C.P01 * C.P01;
     F.bounded = C.P00 > 0.0 && det > 0.0;
     if (!F.bounded) return F;
-    F.cx = (C.P11 * C.h0 - C.P01 * C.h1) / det;
-    F.cy = (C.P00 * C.h1 - C.P01 * C.h0) / det;
+    const double idet = 1.0 / det;
+    F.cx = (C.P11 * C.h0 - C.P01 * C.h1) * idet;
+    F.cy = (C.P00 * C.h1 - C.P01 * C.h0) * idet;
     const double R2 = C.f0 + C.h0 * F.cx + C.h1 * F.cy;
-    const double hx = sqrt(R2 * C.P11 / det), hy = sqrt(R2 * C.P00 / det);
-    const double sy = C.P01 * sqrt(R2 / (C.P11 * det));
+    // hx = sqrt(R2 P11 / det), hy = sqrt(R2 P00 / det), sy = P01 sqrt(R2 / (P11 det))
+    const double r = sqrt(R2 * idet);
+    const double i0 = fast_rsqrt(C.P00), i1 = fast_rsqrt(C.P11);
+    const double hx = r * (C.P11 * i1), hy = r * (C.P00 * i0), sy = C.P01 * (r * i1);
     F.xmin = F.cx - hx;
     F.xmax = F.cx + hx;
     F.ymin = F.cy - hy;
     F.ymax = F.cy + hy;
     F.yleft = F.cy + sy;
     F.yright = F.cy - sy;
-    F.inv_p00 = 1.0 / C.P00;
+    F.inv_p00 = i0 * i0;
     return F;
 }
 
@@ -197,47 +215,15 @@ __device__ inline void band_ranges(const Conic &C, const ConicFrame &F, const Pi
     }
 }
 
-// Is tile (tx, .) of the row listed: does its pixel-centre rectangle (clipped
-// to the box) overlap the row's x-extent?  *bands receives the slots whose
-// own pixel-centre rectangles overlap their slot row's extent (0 for a tile
-// not listed).
-__device__ inline bool tile_listed(const Conic &C, const BandRanges &B, const PixelBox &box, int tx, int TW, int TH,
-                                   uint32_t &bands)
-{
-#pragma clang fp contract(off)
-    bands = 0u;
-    const int cx0 = max(tx * TW, box.x0), cx1 = min(tx * TW + TW - 1, box.x1);
-    if (cx0 > cx1 || !B.row_valid) return false;
-    const double xa = (double)cx0 + 0.5 - C.u0, xb = (double)cx1 + 0.5 - C.u0;
-    if (!(xa <= B.row_xr && xb >= B.row_xl)) return false;
-    const SlotLayout S = slot_layout(TW, TH);
-    const int nslots = S.bits ? S.slots : 1, bx = S.bits ? S.bx : 1, cw = S.bits ? S.cw : TW;
-    // Slot row r and column c are loop constants, so B's arrays stay in
-    // registers (a run-time index would put them in scratch memory).
-#pragma unroll
-    for (int r = 0; r < kMaxBands; ++r) {
-#pragma unroll
-        for (int c = 0; c < kMaxBands; ++c) {
-            const int k = r * bx + c;
-            if (c >= bx || k >= nslots) continue;
-            const int sx0 = max(tx * TW + c * cw, box.x0), sx1 = min(tx * TW + c * cw + cw - 1, box.x1);
-            if (sx0 > sx1 || !((B.valid >> r) & 1u)) continue;
-            const double sa = (double)sx0 + 0.5 - C.u0, sb = (double)sx1 + 0.5 - C.u0;
-            if (sa <= B.xr[r] && sb >= B.xl[r]) bands |= 1u << k;
-        }
-    }
-    return true;
-}
+// A tile of the row is listed when its pixel-centre rectangle (clipped to the
+// box) overlaps the row's x-extent, and a slot of it is marked when the slot's own
+// rectangle overlaps its slot row's extent.  Both are interval tests on
+// columns: the emission takes the first and last column that pass.
 
 // Instance values carry the culling bits of their tile's slots in the top 4
 // bits (a tile with more slots carries none; its rows are then bounded by
 // the record's pixel rows).
 constexpr uint32_t kIdBits = 28;
 constexpr uint32_t kIdMask = (1u << kIdBits) - 1u;
-
-__device__ inline uint32_t pack_instance(uint32_t id, uint32_t bands, int TW, int TH)
-{
-    return slot_layout(TW, TH).bits ? id | (bands << kIdBits) : id;
-}
 
 }  // namespace rgs

@@ -133,30 +133,30 @@ size_t radix_scratch_words(int64_t n_max, int bits, bool ranged);
 
 // Binning scan over the depth order (Gaussian-view order[k] at position k,
 // sorted key keys[k], 0xffffffff when culled; positions k < *n_dev, at most
-// n): offsets[k] = box tiles and
-// row_offsets[k] = box tile rows of the positions before k; counters[0] =
+// n): offsets[k] = box tiles of the positions before k; counters[0] =
 // all box tiles (instances), counters[2] = all tile rows (int64);
-// row_owner[r] = k for each tile row r of position k, written when the
-// instances fit `capacity` (row_owner holds capacity entries);
 // sorted_boxes[k] = boxes[order[k]] (n entries).  block_sums holds
-// scan_block_entries(n) uint64.
+// scan_block_entries(n) uint64.  bin_scratch (bin_scratch_words() uint32)
+// receives the positions that the emission's segments start at, when the
+// instances fit `capacity`.
 hipError_t binning_scan(const uint32_t *keys, const uint2 *boxes, const uint32_t *order, int64_t n,
                         const int64_t *n_dev, int tile_w, int tile_h, int64_t capacity, uint32_t *offsets,
-                        uint32_t *row_offsets, uint32_t *row_owner, uint2 *sorted_boxes,
-                        unsigned long long *block_sums, int64_t *counters, hipStream_t stream);
+                        uint32_t *bin_scratch, uint2 *sorted_boxes, unsigned long long *block_sums,
+                        int64_t *counters, hipStream_t stream);
 size_t scan_block_entries(int64_t n);
+size_t bin_scratch_words(int64_t capacity, int tile_bits);
 
-// Instances of every tile row (one lane per row, `grid` workgroups looping
-// over counters[2] rows): (tile id, id | slot bits) for listed tiles and
-// (empty_tile, id) for the other tiles of the box.  Also zeroes `ranges`
-// (total_tiles entries) and `sched` (sched_words()) for the stages after the
-// tile sort; always launched, also for an empty scene.
-int emit_grid(int num_cus);
-hipError_t launch_emit(const uint32_t *order, const uint32_t *offsets, const uint32_t *row_offsets,
-                       const uint32_t *row_owner, const uint2 *sorted_boxes, const Conic *conics, const DevView *views,
-                       int64_t n, int n_views, const int64_t *counters, int64_t capacity, int tile_w, int tile_h,
-                       uint32_t empty_tile, uint32_t *inst_tiles, uint32_t *inst_ids, uint2 *ranges,
-                       int64_t total_tiles, uint32_t *sched, int grid, hipStream_t stream);
+// With `emit`: the listed instances (tile id, id | slot bits) of the box
+// instances counted by binning_scan, in depth order, in segments with gaps.
+// Also zeroes `ranges` (total_tiles entries) and `sched` (sched_words()) for
+// the stages after the tile sort; always launched, also for an empty scene.
+// Without: their stable sort by tile id, *listed their number; it ping-pongs
+// between (tiles, ids) and the alternates as radix_sort does.
+hipError_t emit_and_sort(const uint32_t *order, const uint32_t *offsets, uint32_t *bin_scratch,
+                         const uint2 *sorted_boxes, const Conic *conics, const DevView *views, int64_t n,
+                         const int64_t *counters, int64_t capacity, int tile_w, int tile_h, int tile_bits,
+                         uint32_t *tiles, uint32_t *ids, uint32_t *tiles_alt, uint32_t *ids_alt, int64_t *listed,
+                         uint2 *ranges, int64_t total_tiles, uint32_t *sched, hipStream_t stream, bool emit);
 
 // Compositing work queues: kQueues heads per pass, kQueueStride words apart
 // (separate memory lines, so their atomics do not serialise on one
@@ -170,7 +170,7 @@ constexpr int kQueueStride = 1024;
 // second half of its pixel rows, for tiles whose list is longer than
 // max(split_min, *counters / waves), split_min 0 = never split) by
 // decreasing list length, at most 2 * total_tiles of them.
-// `ranges` and `sched` must be zero (launch_emit clears them).  `sched` holds
+// `ranges` and `sched` must be zero (emit_and_sort clears them).  `sched` holds
 // sched_words() uint32: the forward queue heads from word 0, the backward
 // heads from sched_backward_heads(), bucket histograms, and the number of
 // work items at sched_item_count().

@@ -22,13 +22,12 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kScanItemsMin = 4;
 constexpr int scan_tile(int items) { return kThreads * items; }
 constexpr int kScanSelfPrefixBlocks = 1024;
-// Scans of at least this many blocks write the row owner map in row order.
-constexpr int kScanRowOrderBlocks = 4096;
 // Radix sort: digits of up to 11 bits, so that a 32-bit key takes 3 passes and a tile id one or two.
 constexpr int kMaxDigitBits = 11;
 constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kHistWordsLog = 12;  // counters of a histogram block (all copies of all bins)
 constexpr int kHistWords = 1 << kHistWordsLog;
+constexpr int kEmitThreads = 512;  // 8 waves (emit_plan)
 
 // Element count of a device-sized array: a frame whose instance count
 // overflowed the capacity is treated as empty downstream (its status reports
@@ -40,18 +39,66 @@ __device__ __forceinline__ int64_t clamp_count(const int64_t *n_dev, int64_t n_m
     return n <= n_max ? n : 0;
 }
 
+// Emission plan: the tile rows of all binning boxes, in depth order, are dealt
+// to blocks of 8 waves (the blocks of the tile sort's first pass) in runs of
+// `rows` rows, about a tile of box instances (a block may have any number).
+// The runs are as long as needed for no more blocks than the sort has.  A wave
+// takes `step` rows of its block at a time, one per lane.
+struct EmitPlan {
+    int64_t total, rows_all;  // box instances (0 when they exceed the capacity) and tile rows
+    int blocks, rows, step;   // rows = 8 step with step 8, 16 or 32 (wide rows), or a multiple of 512 with step 64
+};
+
+__device__ __forceinline__ EmitPlan emit_plan(const int64_t *counters, int64_t capacity, int tile_shift)
+{
+    EmitPlan P;
+    P.total = clamp_count(counters, capacity);
+    P.rows_all = P.total ? counters[2] : 0;
+    const int64_t most = ((capacity - 1) >> tile_shift) + 1;
+    // rows of a tile of box instances (in single precision: any choice is valid)
+    const float fit = (float)P.rows_all / (float)max(P.total, (int64_t)1) * (float)(1 << tile_shift);
+    int rows = 64;
+    while (rows < 512 && ((float)(2 * rows) <= fit || most * rows < P.rows_all)) rows *= 2;
+    if (rows == 512) {
+        rows = 512 * max(1, (int)(fit * (1.0f / 512.0f)));
+        while (most * rows < P.rows_all) rows += 512;
+    }
+    P.rows = rows;
+    P.step = min(rows / 8, 64);
+    P.blocks = (int)((P.rows_all + rows - 1) / rows);
+    return P;
+}
+
+// Orders the LDS accesses of a wave's lanes (which run in step).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inclusive scan across a wave (all lanes active): row shifts inside the
+// 16-lane rows, then each row's last lane broadcast to the rows behind it.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x)
+{
+#define RGS_DPP(CTRL, ROWS) (uint32_t) __builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false)
+    x += RGS_DPP(0x111, 0xf);  // row_shr:1, 2, 4, 8
+    x += RGS_DPP(0x112, 0xf);
+    x += RGS_DPP(0x114, 0xf);
+    x += RGS_DPP(0x118, 0xf);
+    x += RGS_DPP(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+    x += RGS_DPP(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef RGS_DPP
+    return x;
+}
+
 // Inclusive scan across a block of WAVES waves; returns the inclusive
 // prefix and writes the block total to *total.
 template <int WAVES>
 __device__ __forceinline__ uint32_t block_inclusive_scan(uint32_t x, uint32_t *smem /*[WAVES]*/, uint32_t *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t v = x;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(v, d, 64);
-        if (lane >= d) v += y;
-    }
+    const uint32_t v = wave_inclusive_scan(x);
     if (lane == 63) smem[wave] = v;
     __syncthreads();
     uint32_t before = 0, all = 0;
@@ -103,20 +150,33 @@ __device__ __forceinline__ Digit pass_digit(const RadixPass &P)
     return Digit{P.base, (1u << bits) - 1u, shift, bits};
 }
 
-// Block of items of this workgroup: workgroups are dealt to the 8 XCDs in
-// turn, and each XCD takes a contiguous run of the nb blocks.  The blocks in
+// Block of items of this workgroup, of nb: workgroups are dealt to the 8 XCDs
+// in turn, and each XCD takes runs of neighbouring blocks.  The blocks in
 // flight on one XCD then write next to each other in every digit's range, and
 // their short runs merge into whole lines in that XCD's L2 (blocks dealt in
 // order leave every line shared by several XCDs, each writing its part to
-// memory).  Returns nb or more when there is none.
+// memory).  At least 8 runs per XCD even out blocks of different work: the first in
+// depth order have the widest tile rows.  Returns nb or more when there is none.
 __device__ __forceinline__ int xcd_block(int nb)
 {
-    const int share = (nb + 7) >> 3, k = (int)(blockIdx.x >> 3);
-    return k < share ? (int)(blockIdx.x & 7u) * share + k : nb;
+    const int lrun = nb >= 4096 ? 6 : nb >= 64 ? 25 - __builtin_clz((unsigned)nb) : 0;  // log2 of the run: nb / 64, up to 64
+    const int k = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7u);
+    return ((((k >> lrun) << 3) + xcd) << lrun) + (k & ((1 << lrun) - 1));
 }
 
-// Words of a block's histogram row in the block-major layout (whole uint4).
-__device__ __forceinline__ int hist_row(int bins) { return max(bins, 4); }
+// Entries of a block's histogram row in the block-major layout: 16-bit counts
+// (a block has fewer items than that), whole uint4 of them.
+__device__ __forceinline__ int hist_row(int bins) { return max(bins, 8); }
+
+// Writes digit d's count of a block's histogram.
+template <bool SELF>
+__device__ __forceinline__ void put_count(uint32_t *hist, int bins, int nblocks, int block, int d, uint32_t count)
+{
+    if (SELF)
+        reinterpret_cast<uint16_t *>(hist)[(size_t)block * hist_row(bins) + d] = (uint16_t)count;
+    else
+        hist[(size_t)d * nblocks + block] = count;
+}
 
 // Digit histogram of one block's items; with `drop`, keys equal to drop_key
 // are left out (they leave the sort in this pass).  Blocks past the
@@ -182,21 +242,23 @@ __global__ __launch_bounds__(THREADS) void k_radix_hist(const uint32_t *__restri
         uint32_t x = 0;
         if (d < bins)
             for (int c = 0; c < 1 << cshift; ++c) x += cnt[(d << cshift) + c];
-        hist[SELF ? (size_t)block * row + d : (size_t)d * nblocks + block] = x;
+        put_count<SELF>(hist, bins, nblocks, block, d, x);
     }
 }
 
 // Exclusive scan of each digit's row hist[d][0..nb) (one block per digit)
-// over the nb = ceil(n / tile) blocks that hold items (tile = keys per block).
+// over the nb = ceil(n / tile) blocks that hold items (tile = keys per block),
+// or over the emission's blocks.
 __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restrict__ hist, int nblocks,
                                                               int64_t n_max, const int64_t *__restrict__ n_dev,
-                                                              RadixPass pass, int tile,
+                                                              RadixPass pass, int tile, bool segments,
                                                               uint32_t *__restrict__ row_total)
 {
     __shared__ uint32_t smem[kWaves];
     if (blockIdx.x >> pass_digit(pass).bits) return;  // no such digit in this pass
     const int64_t n = clamp_count(n_dev, n_max);
-    const int nb = (int)std::min<int64_t>((n + tile - 1) / tile, nblocks);
+    const int nb = segments ? emit_plan(n_dev, n_max, __builtin_ctz((unsigned)tile)).blocks
+                            : (int)std::min<int64_t>((n + tile - 1) / tile, nblocks);
     uint32_t *row = hist + (size_t)blockIdx.x * nblocks;
     constexpr int kPer = 8;  // entries per thread and step: a contiguous run, scanned in registers
     uint32_t carry = 0;
@@ -227,21 +289,24 @@ __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restri
 // per digit bit, ranked by popcount of the lower peers, and a per-wave LDS
 // counter per digit carries the rank across rounds.  Items are staged in
 // LDS in block-local sorted order and written out in runs of equal digits.
-// With `drop`, keys equal to drop_key are not written, and the first block
-// stores the number of items kept (the sum of the digit totals) in *kept_out.
-// SELF: hist is block-major and unscanned (rows of hist_row(bins) words); each
+// With `drop`, keys equal to drop_key are not written; the first block
+// stores the number of items kept (the sum of the digit totals) in *kept_out (may be null).
+// SELF: hist is block-major and unscanned (rows of hist_row(bins) entries); each
 // block sums the rows before its own (and all of them for the digit bases)
 // itself, so the pass needs no scan launch.  Otherwise hist is digit-major and
 // scanned, with row_total.
-template <int THREADS, int ITEMS, bool SELF>
-__global__ __launch_bounds__(THREADS, SELF ? 4 : 5) void k_radix_scatter(
+// SEG: the items are the emission's: those of block b are the
+// seg[b].y from seg[b].x on, any number of them, taken a tile at a time; the
+// number of items sorted goes to *kept_out.
+template <int THREADS, int ITEMS, bool SELF, bool SEG>
+__global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
     uint32_t *__restrict__ vals_out, int64_t n_max, const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
     uint32_t drop_key, int64_t *__restrict__ kept_out, const uint32_t *__restrict__ hist,
-    const uint32_t *__restrict__ row_total, int nblocks)
+    const uint32_t *__restrict__ row_total, int nblocks, const uint2 *__restrict__ seg)
 {
     constexpr int TILE = THREADS * ITEMS, WAVES = THREADS / 64;
-    constexpr int kCntWords = WAVES * kMaxBins / 2, kSumWords = SELF ? 8 * THREADS : 0;
+    constexpr int kCntWords = WAVES * kMaxBins / 2, kSumWords = SELF ? 16 * THREADS : 0;
     constexpr int kMemA = 2 * TILE > kCntWords ? 2 * TILE : kCntWords;
     // partial sums of the histogram, per-wave digit counters (16 bits each) and
     // staged items take turns
@@ -256,57 +321,75 @@ __global__ __launch_bounds__(THREADS, SELF ? 4 : 5) void k_radix_scatter(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int at0 = wave * (TILE / WAVES) + lane;
     uint32_t key[ITEMS], val[ITEMS];
-    // small sorts load at once, by the launch's bounds; large ones know their block first
     auto load = [&](int64_t base, int left) {
 #pragma unroll
-        for (int r = 0; r < ITEMS; ++r) key[r] = (keys_in + base)[(uint32_t)min(at0 + r * 64, left - 1)];
+        for (int r = 0; r < ITEMS; ++r) key[r] = (keys_in + base)[(uint32_t)min(at0 + r * 64, max(left - 1, 0))];
         if (vals_in) {
 #pragma unroll
-            for (int r = 0; r < ITEMS; ++r) val[r] = (vals_in + base)[(uint32_t)min(at0 + r * 64, left - 1)];
+            for (int r = 0; r < ITEMS; ++r) val[r] = (vals_in + base)[(uint32_t)min(at0 + r * 64, max(left - 1, 0))];
         } else {
 #pragma unroll
             for (int r = 0; r < ITEMS; ++r) val[r] = (uint32_t)(base + at0 + r * 64);
         }
     };
-    if constexpr (SELF) {
+    // small sorts load at once, by the launch's bounds; large ones know their block first
+    constexpr bool kEarly = SELF && !SEG;
+    if constexpr (kEarly) {
         const int64_t base = (int64_t)blockIdx.x * TILE;
         if (base >= n_max) return;
         load(base, (int)min(n_max - base, (int64_t)TILE));
     }
     const int64_t n = clamp_count(n_dev, n_max);
     const Digit D = pass_digit(pass);
-    const int nb = (int)((n + TILE - 1) / TILE), block = SELF ? (int)blockIdx.x : xcd_block(nb);
+    const int nb = SEG ? emit_plan(n_dev, n_max, __builtin_ctz(TILE)).blocks : (int)((n + TILE - 1) / TILE);
+    const int block = SELF ? (int)blockIdx.x : xcd_block(nb);
     if (block >= nb) {  // uniform per block
-        if (drop && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
+        if (kept_out && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
         return;
     }
-    const int64_t base = (int64_t)block * TILE;
-    const int left = (int)min(n - base, (int64_t)TILE);
-    if constexpr (!SELF) load(base, left);
+    int64_t base = (int64_t)block * TILE;
+    int todo = (int)min(n - base, (int64_t)TILE);  // items of the block
+    if constexpr (SEG) {
+        const uint2 part = seg[block];
+        base = part.x;
+        todo = (int)part.y;
+    }
+    if constexpr (!kEarly) load(base, min(todo, TILE));
     const int bins = 1 << D.bits;
 
     // output position of each digit's first item of this block
     if constexpr (SELF) {
-        // each thread sums four neighbouring digits over every groups-th row
-        const int row = hist_row(bins), quads = row >> 2;
-        const int quad = tid & (quads - 1), group = tid / quads, groups = THREADS / quads;
-        uint4 all = make_uint4(0u, 0u, 0u, 0u), pre = all;
-        constexpr int kStep = 16;
-        const uint4 *src = reinterpret_cast<const uint4 *>(hist) + quad;
+        // each thread sums eight neighbouring digits over every groups-th row
+        const int row = hist_row(bins), octs = row >> 3;
+        const int oct = tid & (octs - 1), group = tid / octs, groups = THREADS / octs;
+        uint32_t all[8] = {}, pre[8] = {};
+        constexpr int kStep = 8;
+        const uint4 *src = reinterpret_cast<const uint4 *>(hist) + oct;
         for (int r0 = group; r0 < nb; r0 += groups * kStep) {
             uint4 x[kStep];
 #pragma unroll
-            for (int j = 0; j < kStep; ++j) x[j] = src[(size_t)(min(r0 + j * groups, nb - 1) * quads)];
+            for (int j = 0; j < kStep; ++j) x[j] = src[(size_t)(min(r0 + j * groups, nb - 1) * octs)];
 #pragma unroll
             for (int j = 0; j < kStep; ++j) {
                 const int r = r0 + j * groups;
                 const uint32_t in = r < nb ? ~0u : 0u, before = r < block ? ~0u : 0u;
-                all.x += x[j].x & in; all.y += x[j].y & in; all.z += x[j].z & in; all.w += x[j].w & in;
-                pre.x += x[j].x & before; pre.y += x[j].y & before; pre.z += x[j].z & before; pre.w += x[j].w & before;
+                const uint32_t w[4] = {x[j].x & in, x[j].y & in, x[j].z & in, x[j].w & in};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t lo = w[q] & 0xffffu, hi = w[q] >> 16;
+                    all[2 * q] += lo;
+                    all[2 * q + 1] += hi;
+                    pre[2 * q] += lo & before;
+                    pre[2 * q + 1] += hi & before;
+                }
             }
         }
-        s_mem4[tid] = all;
-        s_mem4[THREADS + tid] = pre;
+        // partial sums [group][digit], all of them and then those before the block
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            s_mem4[2 * tid + q] = make_uint4(all[4 * q], all[4 * q + 1], all[4 * q + 2], all[4 * q + 3]);
+            s_mem4[2 * THREADS + 2 * tid + q] = make_uint4(pre[4 * q], pre[4 * q + 1], pre[4 * q + 2], pre[4 * q + 3]);
+        }
         __syncthreads();
     }
     uint32_t dig_carry = 0;
@@ -316,10 +399,10 @@ __global__ __launch_bounds__(THREADS, SELF ? 4 : 5) void k_radix_scatter(
         uint32_t pre = 0, all = 0;
         if (d < bins) {
             if constexpr (SELF) {
-                const int row = hist_row(bins), groups = 4 * THREADS / row;
+                const int row = hist_row(bins), groups = 8 * THREADS / row;
                 for (int g = 0; g < groups; ++g) {
                     all += s_mem[g * row + d];
-                    pre += s_mem[4 * THREADS + g * row + d];
+                    pre += s_mem[8 * THREADS + g * row + d];
                 }
             } else {
                 all = row_total[d];
@@ -331,84 +414,95 @@ __global__ __launch_bounds__(THREADS, SELF ? 4 : 5) void k_radix_scatter(
         dig_carry += dig_tot;
         if (d < bins) s_base[d] = dig_base + pre;
     }
-    if (drop && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
-    __syncthreads();
-    for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
-    __syncthreads();
-
-    // position of each item among the items of its digit in its wave
-    uint16_t *const cnt = wave_cnt + wave * bins;
-    uint32_t rank[ITEMS];
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const bool valid = at0 + r * 64 < left && !(drop && key[r] == drop_key);
-        const uint32_t d = D.of(key[r]);
-        const uint64_t some = __ballot(valid);
-        uint32_t lo = (uint32_t)some, hi = (uint32_t)(some >> 32);  // lanes of the same digit
-        for (int b = 0; b < D.bits; ++b) {
-            const int32_t bit = (int32_t)(d << (31 - b)) >> 31;  // 0 or all ones
-            const uint64_t m = __ballot(bit != 0);
-            lo &= ~((uint32_t)m ^ (uint32_t)bit);
-            hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
-        }
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-        const uint32_t prior = cnt[d];
-        __builtin_amdgcn_wave_barrier();
-        if (valid && below == 0) cnt[d] = (uint16_t)(prior + (uint32_t)(__popc(lo) + __popc(hi)));
-        __builtin_amdgcn_wave_barrier();
-        rank[r] = valid ? prior + below : 0xffffffffu;
-    }
-    __syncthreads();
-
-    // per digit: prefix over the waves, block-local start
-    uint32_t carry = 0;
-#pragma unroll 1
-    for (int d0 = 0; d0 < bins; d0 += THREADS) {
-        const int d = d0 + tid;
-        uint32_t run = 0;
-        if (d < bins)
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) {
-                const uint32_t c = wave_cnt[w * bins + d];
-                wave_cnt[w * bins + d] = (uint16_t)run;
-                run += c;
-            }
-        uint32_t tot;
-        const uint32_t start = carry + block_inclusive_scan<WAVES>(run, smem, &tot) - run;
-        carry += tot;
-        if (d < bins) {
-            s_start[d] = (uint16_t)start;
-            s_base[d] -= start;
-        }
-    }
-    const int count = (int)carry;  // items of this block that stay in the sort
+    if (kept_out && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
     const uint32_t n32 = (uint32_t)n;
-    __syncthreads();
+    for (;;) {
+        const int left = min(todo, TILE);
+        __syncthreads();
+        for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
+        __syncthreads();
+
+        // position of each item among the items of its digit in its wave
+        uint16_t *const cnt = wave_cnt + wave * bins;
+        uint32_t rank[ITEMS];
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r)
-        if (rank[r] != 0xffffffffu) {
+        for (int r = 0; r < ITEMS; ++r) {
+            const bool valid = at0 + r * 64 < left && !(drop && key[r] == drop_key);
             const uint32_t d = D.of(key[r]);
-            rank[r] += (uint32_t)s_start[d] + cnt[d];
+            const uint64_t some = __ballot(valid);
+            uint32_t lo = (uint32_t)some, hi = (uint32_t)(some >> 32);  // lanes of the same digit
+            for (int b = 0; b < D.bits; ++b) {
+                const int32_t bit = (int32_t)(d << (31 - b)) >> 31;  // 0 or all ones
+                const uint64_t m = __ballot(bit != 0);
+                lo &= ~((uint32_t)m ^ (uint32_t)bit);
+                hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
+            }
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            const uint32_t prior = cnt[d];
+            wave_sync();
+            if (valid && below == 0) cnt[d] = (uint16_t)(prior + (uint32_t)(__popc(lo) + __popc(hi)));
+            wave_sync();
+            rank[r] = valid ? prior + below : 0xffffffffu;
         }
-    __syncthreads();  // the counters give way to the staged items
+        __syncthreads();
+
+        // per digit: prefix over the waves, block-local start
+        uint32_t carry = 0;
+#pragma unroll 1
+        for (int d0 = 0; d0 < bins; d0 += THREADS) {
+            const int d = d0 + tid;
+            uint32_t run = 0;
+            if (d < bins)
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r)
-        if (rank[r] != 0xffffffffu) {
-            s_keys[rank[r]] = key[r];
-            s_vals[rank[r]] = val[r];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const int p = r * THREADS + tid;
-        if (p < count) {
-            const uint32_t k = s_keys[p];
-            const uint32_t dst = s_base[D.of(k)] + (uint32_t)p;
-            if (dst < n32) {
-                keys_out[dst] = k;
-                vals_out[dst] = s_vals[p];
+                for (int w = 0; w < WAVES; ++w) {
+                    const uint32_t c = wave_cnt[w * bins + d];
+                    wave_cnt[w * bins + d] = (uint16_t)run;
+                    run += c;
+                }
+            uint32_t tot;
+            const uint32_t start = carry + block_inclusive_scan<WAVES>(run, smem, &tot) - run;
+            carry += tot;
+            if (d < bins) {
+                s_start[d] = (uint16_t)start;
+                s_base[d] -= start;
             }
         }
+        const int count = (int)carry;  // items of this tile that stay in the sort
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (rank[r] != 0xffffffffu) {
+                const uint32_t d = D.of(key[r]);
+                rank[r] += (uint32_t)s_start[d] + cnt[d];
+            }
+        __syncthreads();  // the counters give way to the staged items
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (rank[r] != 0xffffffffu) {
+                s_keys[rank[r]] = key[r];
+                s_vals[rank[r]] = val[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const int p = r * THREADS + tid;
+            if (p < count) {
+                const uint32_t k = s_keys[p];
+                const uint32_t dst = s_base[D.of(k)] + (uint32_t)p;
+                if (dst < n32) {
+                    keys_out[dst] = k;
+                    vals_out[dst] = s_vals[p];
+                }
+            }
+        }
+        todo -= TILE;
+        if (!SEG || todo <= 0) break;  // uniform per block
+        base += TILE;
+        load(base, min(todo, TILE));
+        // the digits' next positions: past this tile's items
+        __syncthreads();
+        for (int d = tid; d < bins; d += THREADS)
+            s_base[d] += d + 1 < bins ? (uint32_t)s_start[d + 1] : (uint32_t)count;
     }
 }
 
@@ -432,8 +526,8 @@ __device__ __forceinline__ void scan_item(const uint32_t *__restrict__ keys, con
     }
 }
 
-// Gathers each sorted item's two counts once (into `tiles` and `rows`, read
-// back by k_scan_apply, which scans them in place) and reduces them per block.
+// Gathers each sorted item's two counts once (the tiles into `tiles`, read back
+// by k_scan_apply, which scans them in place) and reduces them per block.
 // The gathered binning box is also stored in depth order (`sorted_boxes`), so
 // the emission kernel reads it coalesced instead of gathering it again.
 template <int ITEMS>
@@ -441,7 +535,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t *__rest
                                                           const uint2 *__restrict__ boxes,
                                                           const uint32_t *__restrict__ order, int64_t n_max,
                                                           const int64_t *__restrict__ n_dev, int TW, int TH,
-                                                          uint32_t *__restrict__ tiles, uint32_t *__restrict__ rows,
+                                                          uint32_t *__restrict__ tiles,
                                                           uint2 *__restrict__ sorted_boxes,
                                                           unsigned long long *__restrict__ block_sums)
 {
@@ -457,7 +551,6 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t *__rest
             uint2 box;
             scan_item(keys, boxes, order, idx, TW, TH, t, r, box);
             tiles[idx] = t;
-            rows[idx] = r;
             sorted_boxes[idx] = box;
             at += t;
             ar += r;
@@ -555,13 +648,9 @@ __device__ void block_prefix_pairs(const unsigned long long *__restrict__ block_
 }
 
 // Offsets of every sorted item, scanned in place over the counts k_scan_reduce
-// left in `offsets` (box tiles) and `row_offsets` (tile rows), plus the owner
-// map of the tile rows (row_owner[r] = sorted position owning row r) when the
-// instances fit.  The map is written per item (each thread the rows of its
-// own items) or, with `rows_in_order`, in row order by consecutive threads,
-// each looking its row's owner up in the block's item table.  Row order
-// coalesces the stores, which pays off at tens of millions of items; with a
-// few hundred blocks the lookups' latency is exposed and per item is faster.
+// left in `offsets` (box tiles), and, when the instances fit, where each
+// step of the emission starts: steps[m] = (item, row of its box) of tile row
+// m plan.step.
 // With `self_prefix` (few blocks), block_sums still holds every block's raw
 // pair: each block sums the pairs before its own and all of them, block 0
 // writes the totals to counters[0] and counters[2], and k_scan_top is not
@@ -569,12 +658,12 @@ __device__ void block_prefix_pairs(const unsigned long long *__restrict__ block_
 // prefixes and written the totals.
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const int64_t *__restrict__ n_dev,
-                                                         int64_t capacity,
+                                                         int64_t capacity, int tile_w, int tile_h,
+                                                         const uint2 *__restrict__ sorted_boxes,
                                                          const unsigned long long *__restrict__ block_sums,
                                                          int64_t *__restrict__ counters, bool self_prefix,
-                                                         bool rows_in_order, uint32_t *__restrict__ offsets,
-                                                         uint32_t *__restrict__ row_offsets,
-                                                         uint32_t *__restrict__ row_owner)
+                                                         int tile_shift, uint32_t *__restrict__ offsets,
+                                                         uint2 *__restrict__ steps)
 {
     static_assert(ITEMS % 4 == 0, "whole 16-byte loads per thread");
     __shared__ uint32_t smem[kWaves];
@@ -582,26 +671,28 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const in
     // blocked arrangement: thread t owns items base + t*ITEMS .. (aligned 16-byte groups)
     const int64_t base = (int64_t)blockIdx.x * scan_tile(ITEMS) + (int64_t)threadIdx.x * ITEMS;
     uint32_t c[ITEMS], r[ITEMS];
+    const int hshift = __builtin_ctz(tile_h);
     if (base + ITEMS <= n) {
         const uint4 *pc = reinterpret_cast<const uint4 *>(offsets + base);
-        const uint4 *pr = reinterpret_cast<const uint4 *>(row_offsets + base);
+        const uint4 *pb = reinterpret_cast<const uint4 *>(sorted_boxes + base);
 #pragma unroll
         for (int v = 0; v < ITEMS / 4; ++v) {
-            const uint4 cv = pc[v], rv = pr[v];
+            const uint4 cv = pc[v], b0 = pb[2 * v], b1 = pb[2 * v + 1];
             c[4 * v] = cv.x; c[4 * v + 1] = cv.y; c[4 * v + 2] = cv.z; c[4 * v + 3] = cv.w;
-            r[4 * v] = rv.x; r[4 * v + 1] = rv.y; r[4 * v + 2] = rv.z; r[4 * v + 3] = rv.w;
+            r[4 * v] = b0.y; r[4 * v + 1] = b0.w; r[4 * v + 2] = b1.y; r[4 * v + 3] = b1.w;
         }
     } else {
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const bool in = base + j < n;
             c[j] = in ? offsets[base + j] : 0u;
-            r[j] = in ? row_offsets[base + j] : 0u;
+            r[j] = in ? sorted_boxes[base + j].y : 0u;
         }
     }
     uint32_t lt = 0, lr = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
+        r[j] = c[j] ? (r[j] >> 16 >> hshift) - ((r[j] & 0xffffu) >> hshift) + 1u : 0u;
         lt += c[j];
         lr += r[j];
     }
@@ -619,105 +710,233 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const in
         pre[0] = block_sums[2 * blockIdx.x];
         pre[1] = block_sums[2 * blockIdx.x + 1];
         all[0] = (unsigned long long)counters[0];
+        all[1] = (unsigned long long)counters[2];
     }
-    const uint32_t block_rows = tot;  // tile rows of the block's items
+    const int64_t totals[3] = {(int64_t)all[0], 0, (int64_t)all[1]};
+    const EmitPlan P = emit_plan(totals, capacity, tile_shift);
+    const int sshift = __builtin_ctz((unsigned)P.step);
     const bool fits = all[0] <= (unsigned long long)capacity;
     unsigned long long rt = pre[0] + bt;
-    unsigned long long rr = pre[1] + br;
-    // first row of each of the block's items, relative to the block's first row
-    __shared__ uint32_t row_start[scan_tile(ITEMS)];
-    uint32_t lr0 = br;
+    uint32_t rr = (uint32_t)(pre[1] + br);  // below the instances, so 32 bits where they fit
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
         const int64_t idx = base + j;
         if (idx < n) {
             offsets[idx] = rt > 0xffffffffull ? 0xffffffffu : (uint32_t)rt;
-            row_offsets[idx] = rr > 0xffffffffull ? 0xffffffffu : (uint32_t)rr;
-            // rows <= instances, so every row index lies below capacity
-            if (fits && !rows_in_order)
-                for (uint32_t q = 0; q < r[j]; ++q) row_owner[rr + q] = (uint32_t)idx;
+            if (fits && c[j])
+                for (uint32_t m = (rr + (uint32_t)P.step - 1u) >> sshift; m << sshift < rr + r[j]; ++m)
+                    steps[m] = make_uint2((uint32_t)idx, (m << sshift) - rr);
         }
-        row_start[threadIdx.x * ITEMS + j] = lr0;
         rt += c[j];
         rr += r[j];
-        lr0 += r[j];
-    }
-    if (!fits || !rows_in_order) return;  // uniform over the grid
-    __syncthreads();
-    // owner map of the block's rows, written in row order by consecutive
-    // threads: the owner of row q is the last item whose first row is <= q
-    // (items without rows share the first row of the next item)
-    const int64_t block_base = (int64_t)blockIdx.x * scan_tile(ITEMS);
-    const int nvalid = (int)min((int64_t)scan_tile(ITEMS), n - block_base);
-    const unsigned long long row0 = pre[1];
-    for (uint32_t q = threadIdx.x; q < block_rows; q += kThreads) {
-        int lo = 0, hi = nvalid;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (row_start[mid] <= q)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        // rows <= instances, so every row index lies below capacity
-        row_owner[row0 + q] = (uint32_t)(block_base + lo);
     }
 }
 
 // ---------------------------------------------------------------- emission
-// One lane per tile row of the sorted Gaussian-views (a grid-stride loop
-// over the row count the scan produced): the lane computes the support's
-// x-extent over the row and over its rows of pixel slots and writes every
-// tile of the box row at its scanned position, as (tile id, id | slot bits)
-// when the tile's pixel-centre rectangle meets the support and as the empty
-// marker `empty_tile` otherwise.  Instances end up
-// grouped by Gaussian-view in depth order, so a stable sort on the tile id
+// The listed tiles of the depth-sorted Gaussian-views' boxes, in three levels,
+// each spread over the lanes of a wave:
+//   Gaussian-view: its rows in the wave's step;
+//   tile row: the conic is gathered (one 64-byte line), the support's x-extent
+//     over the row and over its rows of pixel slots gives the interval of listed
+//     tiles, and of slot columns, in the row;
+//   listed tile: (tile id, id | slot bits), written next to each other.
+// (A lane that wrote every tile of its row took 105 us of a 1280x960 frame close
+// to a wall, whose rows are up to 160 tiles wide, and 0.90 ms of a 5120x3840 frame
+// of needles whose boxes are nine tenths empty, and with the histogram launch 1.05 ms
+// of 8 views; this takes 45 us, 0.25 ms and 0.85 ms.  A wave for every 512 box
+// instances balances the blocks, but leaves most lanes idle in wide rows and
+// computes steps of few rows in narrow ones: 1.7 ms for the 8 views.)
+// Box tiles that are not listed are never written: a block's instances lie from
+// its first row's box offset on, seg[block] = (offset, number).  `hist` counts
+// them by the tile sort's first digit, so that pass needs no histogram launch.
+// Instances stay grouped by Gaussian-view in depth order, so a stable sort on the tile id
 // alone leaves every tile's list in depth order.  The kernel also clears the
 // tile ranges and the compositing scheduling words for the stages after the
-// tile sort (`clear` holds clear_words uint32 at `clear_a`, then `clear_b`).
+// tile sort (clear_a_words uint32 at `clear_a`, then `clear_b`).
 // Instantiated per tile shape, so the slot layout of the culling bits is
 // constant.
-template <int TW, int TH>
-__global__ __launch_bounds__(kThreads) void k_emit(const uint32_t *__restrict__ order,
-                                                   const uint32_t *__restrict__ offsets,
-                                                   const uint32_t *__restrict__ row_offsets,
-                                                   const uint32_t *__restrict__ row_owner,
-                                                   const uint2 *__restrict__ sorted_boxes,
-                                                   const Conic *__restrict__ conics,
-                                                   const DevView *__restrict__ views, int64_t n,
-                                                   const int64_t *__restrict__ counters, int64_t capacity,
-                                                   uint32_t empty_tile, uint32_t *__restrict__ inst_tiles,
-                                                   uint32_t *__restrict__ inst_ids, uint32_t *__restrict__ clear_a,
-                                                   int64_t clear_a_words, uint32_t *__restrict__ clear_b,
-                                                   int64_t clear_b_words)
+
+// Pixels of the box columns [bx0, bx1] whose centres lie in the extent
+// [xl, xr] of offsets from u0, as [pa, pb]; a rectangle of pixel centres
+// [sx0, sx1] inside the box meets the extent iff sx1 >= pa and sx0 <= pb.
+// The estimates are at most one pixel off; the comparisons decide.  pa > pb
+// when either bound is not a number (no comparison holds then).
+__device__ __forceinline__ void pixel_extent(double xl, double xr, double u0, int bx0, int bx1, int &pa, int &pb)
 {
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    const int64_t tid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    for (int64_t i = tid; i < clear_a_words; i += stride) clear_a[i] = 0u;
-    for (int64_t i = tid; i < clear_b_words; i += stride) clear_b[i] = 0u;
-    if (counters[0] > capacity) return;  // overflow: the instance total reports it
-    const int64_t rows = counters[2];
-    for (int64_t r = tid; r < rows; r += stride) {
-        const uint32_t k = row_owner[r];
-        const uint32_t id = order[k];
-        const PixelBox pb = unpack_box(sorted_boxes[k]);
-        const int v = (int)(id / (uint32_t)n);
-        const int row = (int)(r - row_offsets[k]);
-        const int ty = pb.y0 / TH + row;
-        const int tx0 = pb.x0 / TW, tx1 = pb.x1 / TW;
-        int64_t pos = (int64_t)offsets[k] + (int64_t)row * (tx1 - tx0 + 1);
-        const Conic C = conics[id];
-        const ConicFrame F = conic_frame(C);
-        BandRanges B;
-        band_ranges(C, F, pb, ty, TW, TH, B);
-        const uint32_t row_base = (uint32_t)views[v].tile_base + (uint32_t)(ty * views[v].tiles_x);
-        for (int tx = tx0; tx <= tx1; ++tx, ++pos) {
-            uint32_t bands;
-            const bool listed = tile_listed(C, B, pb, tx, TW, TH, bands);
-            inst_tiles[pos] = listed ? row_base + (uint32_t)tx : empty_tile;
-            inst_ids[pos] = pack_instance(id, bands, TW, TH);
+#pragma clang fp contract(off)
+    const double lo = (double)bx0, hi = (double)bx1;
+    double a = ceil(xl + u0 - 0.5), b = floor(xr + u0 - 0.5);
+    if (!(a + 0.5 - u0 >= xl))
+        a += 1.0;
+    else if ((a - 1.0) + 0.5 - u0 >= xl)
+        a -= 1.0;
+    if (!(b + 0.5 - u0 <= xr))
+        b -= 1.0;
+    else if ((b + 1.0) + 0.5 - u0 <= xr)
+        b += 1.0;
+    pa = (int)fmin(fmax(a, lo), hi + 1.0);
+    pb = (int)fmax(fmin(b, hi), lo - 1.0);
+    if (__builtin_isunordered(xl, xr)) pa = bx1 + 1, pb = bx0 - 1;
+}
+
+// Spreads counted work over a wave: lane l owns `count` units from `start` on
+// (the exclusive scan of the counts), and the lane holding unit at0 + lane gets
+// the owner's lane.  `before` is the owner of unit at0 - 1, used where no owner
+// starts in the window up to this lane; slots are 64 LDS words of the wave.
+__device__ __forceinline__ int unit_owner(uint32_t start, uint32_t count, uint32_t at0, int before, uint32_t *slots)
+{
+    const int lane = threadIdx.x & 63;
+    slots[lane] = 64u;
+    wave_sync();
+    if (count != 0u && start - at0 < 64u) slots[start - at0] = (uint32_t)lane;
+    wave_sync();
+    const uint32_t mine = slots[lane];
+    const uint64_t starts = __ballot(mine != 64u) & (~0ull >> (63 - lane));
+    const int from = starts ? 63 - __builtin_clzll(starts) : 0;
+    const int owner = __shfl((int)mine, from, 64);
+    wave_sync();
+    return starts ? owner : before;
+}
+
+template <int TW, int TH, int TILE, bool SELF>
+__global__ __launch_bounds__(kEmitThreads) void k_emit(
+    const uint32_t *__restrict__ order, const uint32_t *__restrict__ offsets, const uint2 *__restrict__ steps,
+    const uint2 *__restrict__ sorted_boxes, const Conic *__restrict__ conics, const DevView *__restrict__ views,
+    int64_t n, const int64_t *__restrict__ counters, int64_t capacity, RadixPass pass,
+    uint32_t *__restrict__ inst_tiles, uint32_t *__restrict__ inst_ids, uint2 *__restrict__ seg,
+    uint32_t *__restrict__ hist, int nblocks, uint32_t *__restrict__ clear_a, int64_t clear_a_words,
+    uint32_t *__restrict__ clear_b, int64_t clear_b_words)
+{
+    constexpr SlotLayout SL = slot_layout(TW, TH);
+    constexpr int NR = SL.bits ? SL.slots / SL.bx : 0;  // slot rows whose columns travel with the instance
+    constexpr int BX = SL.bits ? SL.bx : 1, CW = SL.bits ? SL.cw : TW;
+    constexpr int LW = TW == 8 ? 3 : TW == 16 ? 4 : 5, LH = TH == 8 ? 3 : TH == 16 ? 4 : 5;
+    constexpr int LC = CW == 8 ? 3 : CW == 16 ? 4 : 5;
+    constexpr int WAVES = kEmitThreads / 64;
+    constexpr int kGRow = 4, kRRow = 2 + NR;
+    __shared__ uint32_t cnt[kMaxBins];
+    __shared__ uint32_t s_g[WAVES][kGRow][64], s_r[WAVES][kRRow][64], s_slots[WAVES][64], s_listed[2][WAVES];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    {
+        const int64_t stride = (int64_t)gridDim.x * kEmitThreads, at = (int64_t)blockIdx.x * kEmitThreads + tid;
+        for (int64_t i = at; i < clear_a_words; i += stride) clear_a[i] = 0u;
+        for (int64_t i = at; i < clear_b_words; i += stride) clear_b[i] = 0u;
+    }
+    const EmitPlan P = emit_plan(counters, capacity, __builtin_ctz(TILE));
+    const int block = SELF ? (int)blockIdx.x : xcd_block(P.blocks);
+    if (block >= P.blocks) return;  // uniform per block
+    const Digit D = pass_digit(pass);
+    const int bins = 1 << D.bits;
+    for (int i = tid; i < bins; i += kEmitThreads) cnt[i] = 0u;
+    const uint32_t kept = (uint32_t)counters[4];
+    const uint32_t row_first = (uint32_t)block * (uint32_t)P.rows;
+    const uint32_t row_end = (uint32_t)min((int64_t)row_first + P.rows, P.rows_all);
+    const int sshift = __builtin_ctz((unsigned)P.step);
+    // box offset of the block's first row
+    const uint2 start = steps[row_first >> sshift];
+    const uint2 start_box = sorted_boxes[start.x];
+    const uint32_t base =
+        offsets[start.x] + start.y * ((start_box.x >> 16 >> LW) - ((start_box.x & 0xffffu) >> LW) + 1u);
+    __syncthreads();
+    uint32_t(*const G)[64] = s_g[wave];
+    uint32_t(*const Rw)[64] = s_r[wave];
+    uint32_t *const slots = s_slots[wave];
+    uint32_t out = 0u;
+    int turn = 0;
+    for (uint32_t r0 = row_first; r0 < row_end; r0 += WAVES * P.step, turn ^= 1) {
+        const uint32_t mine = r0 + (uint32_t)(wave * P.step);  // first row of the wave's step
+        const int n_rows = mine < row_end ? min(P.step, (int)(row_end - mine)) : 0;
+        uint32_t listed = 0u;
+        if (n_rows) {
+            // the Gaussian-views of the step's rows, from the one that its first row belongs to
+            const uint2 first = steps[mine >> sshift];
+            const uint32_t k = min(first.x + (uint32_t)lane, kept - 1u);
+            const uint32_t id = order[k];
+            const uint2 box = sorted_boxes[k];
+            const uint32_t skip = lane == 0 ? first.y : 0u;
+            const uint32_t rows = first.x + lane < kept ? (box.y >> 16 >> LH) - ((box.y & 0xffffu) >> LH) + 1u - skip : 0u;
+            const uint32_t g_start = wave_inclusive_scan(rows) - rows;
+            G[0][lane] = id;
+            G[1][lane] = box.x;
+            G[2][lane] = box.y;
+            G[3][lane] = skip - g_start;  // row of the box = row of the step + this
+            const int g = unit_owner(g_start, rows, 0u, 0, slots);
+            if (lane < n_rows) {
+                const uint32_t gid = G[0][g];
+                const Conic C = conics[gid];
+                const PixelBox pb = unpack_box(make_uint2(G[1][g], G[2][g]));
+                const int ty = (pb.y0 >> LH) + (int)(lane + G[3][g]);
+                const DevView &V = views[gid / (uint32_t)n];
+                const uint32_t tile0 = (uint32_t)V.tile_base + (uint32_t)(ty * V.tiles_x);
+                const ConicFrame F = conic_frame(C);
+                BandRanges B;
+                band_ranges(C, F, pb, ty, TW, TH, B);
+                int pa, pe;
+                pixel_extent(B.row_xl, B.row_xr, C.u0, pb.x0, pb.x1, pa, pe);
+                const int ta = max(pb.x0, pa) >> LW, tb = min(pb.x1, pe) >> LW;
+                if (B.row_valid && pa <= pb.x1 && pe >= pb.x0 && ta <= tb) {
+                    listed = (uint32_t)(tb - ta + 1);
+                    Rw[0][lane] = tile0 + (uint32_t)ta;
+                    Rw[1][lane] = gid;
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) {
+                        // slot columns [lo, hi) from tile ta's first on
+                        uint32_t cols = 0u;
+                        if ((B.valid >> q) & 1u) {
+                            int qa = pa, qe = pe;
+                            if (NR > 1) pixel_extent(B.xl[q], B.xr[q], C.u0, pb.x0, pb.x1, qa, qe);
+                            if (qa <= pb.x1 && qe >= pb.x0) {
+                                const int c0 = max(max(pb.x0, qa) >> LC, ta * BX);
+                                const int c1 = min(min(pb.x1, qe) >> LC, tb * BX + BX - 1);
+                                if (c0 <= c1) cols = (uint32_t)(c0 - ta * BX) | (uint32_t)(c1 + 1 - ta * BX) << 16;
+                            }
+                        }
+                        Rw[2 + q][lane] = cols;
+                    }
+                }
+            }
+        }
+        const uint32_t r_end = wave_inclusive_scan(listed), r_start = r_end - listed;
+        const uint32_t n_listed = __builtin_amdgcn_readlane(r_end, 63);
+        if (lane == 0) s_listed[turn][wave] = n_listed;
+        __syncthreads();
+        uint32_t at = base + out;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const uint32_t x = s_listed[turn][w];
+            at += w < wave ? x : 0u;
+            out += x;
+        }
+        int r_before = 0;
+        for (uint32_t ebase = 0; ebase < n_listed; ebase += 64u) {
+            const int r = unit_owner(r_start, listed, ebase, r_before, slots);
+            r_before = __builtin_amdgcn_readlane(r, 63);
+            const uint32_t e = ebase + lane;
+            const uint32_t j = e - (uint32_t)__shfl((int)r_start, r, 64);
+            if (e < n_listed) {
+                const uint32_t tile = Rw[0][r] + j;
+                uint32_t bands = 0u;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    const uint32_t cols = Rw[2 + q][r], lo = cols & 0xffffu, hi = cols >> 16;
+#pragma unroll
+                    for (int c = 0; c < BX; ++c) {
+                        const uint32_t col = j * BX + c;
+                        if (col >= lo && col < hi) bands |= 1u << (q * BX + c);
+                    }
+                }
+                inst_tiles[at + e] = tile;
+                inst_ids[at + e] = Rw[1][r] | (SL.bits ? bands << kIdBits : 0u);
+                atomicAdd(&cnt[D.of(tile)], 1u);
+            }
         }
     }
+    __syncthreads();
+    if (tid == 0) seg[block] = make_uint2(base, out);
+    const int row = SELF ? hist_row(bins) : bins;
+    for (int d = tid; d < row; d += kEmitThreads)
+        put_count<SELF>(hist, bins, nblocks, block, d, d < bins ? cnt[d] : 0u);
 }
 
 // ------------------------------------------------------------ tile ranges
@@ -856,18 +1075,27 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
 int radix_passes(int bits) { return bits <= 0 ? 0 : (bits + kMaxDigitBits - 1) / kMaxDigitBits; }
 
 namespace {
-// Workgroup shapes, from timings of whole sorts (rocprofv3; graph replays).
-// Up to kSelfMax items a pass is two launches, and the shortest chain in a
-// workgroup wins: three passes over 0.5M depth keys took 34 us of scatter at
-// 512 x 4 and 37 at 1024 x 4 or 512 x 8.  Above it a pass has a scan launch of its
-// own and 512 x 8 is best: a sort of 22.5M depth keys and one of 66M tile ids (8 views)
-// took 0.93 ms of scatter and histograms of it, 1.10 ms at 256 x 16, 0.99 ms at 512 x 16.
-constexpr int kSelfThreads = 512, kSelfItems = 4;
-constexpr int kScanThreads = 512, kScanItems = 8;
-constexpr int64_t kSelfMax = int64_t(1) << 20;
+// Workgroup shapes by the sort's size.  Up to kSelfMax items a pass is two
+// launches, the scatter summing the histogram rows itself: at 0.5M keys, a third of
+// them kept, three passes took 44 us and with a scan launch 50 us; at 0.6M
+// kept it is 73 against 58 us, as every block reads the rows of all.  Up to
+// kMidMax blocks stay small, so that there are enough of them (1.5M tile ids: 42
+// us, 49 us at twice the items); above, larger blocks write longer runs (22.5M depth keys
+// and 66M tile ids: 1.44 ms, 1.66 ms at half the items).
+constexpr int kSortThreads = 512, kSmallItems = 4, kLargeItems = 8;
+constexpr int64_t kSelfMax = int64_t(1) << 19, kMidMax = int64_t(1) << 23;
+
+int block_items(int64_t n_max) { return kSortThreads * (n_max <= kMidMax ? kSmallItems : kLargeItems); }
+
+// log2 of the items of a block of a sort of up to n_max items
+int tile_shift(int64_t n_max) { return __builtin_ctz((unsigned)block_items(n_max)); }
 }  // namespace
 
 namespace {
+// Workgroups that reach every block of xcd_block for any nb up to nblocks: its
+// last round of runs may be partly empty (8 runs of at most 64 or nb / 64 blocks).
+int xcd_grid(int nblocks) { return (nblocks + std::min(512, nblocks / 8) + 15) & ~7; }
+
 // The widest digit of any pass of a sort on `bits` bits; with a key range the
 // first pass has kFirstBits bits and the others up to the widest.
 int widest_digit(int bits, bool ranged, int pass)
@@ -883,56 +1111,68 @@ int widest_digit(int bits, bool ranged, int pass)
 size_t radix_scratch_words(int64_t n_max, int bits, bool ranged)
 {
     const bool self = n_max <= kSelfMax;
-    const int64_t tile = self ? kSelfThreads * kSelfItems : kScanThreads * kScanItems;
-    const size_t row = std::max((size_t)1 << widest_digit(bits, ranged, 1), (size_t)4);
-    return row * (size_t)((n_max + tile - 1) / tile) + (self ? 0 : row);
+    const int64_t tile = block_items(n_max);
+    const size_t bins = (size_t)1 << widest_digit(bits, ranged, 1);
+    const size_t blocks = (size_t)((n_max + tile - 1) / tile);
+    return self ? std::max(bins, (size_t)8) / 2 * blocks : bins * blocks + bins;
 }
+
+namespace {
+template <int TH, int IT, bool SELF>
+void radix_pass(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *vo, int64_t n_max, const int64_t *pn,
+                const RadixPass &pass, int wide, bool drop, uint32_t drop_key, int64_t *kept_out,
+                const RadixRange *top, const uint2 *seg, uint32_t *scratch, hipStream_t stream)
+{
+    constexpr int tile = TH * IT;
+    const int nblocks = (int)((n_max + tile - 1) / tile), grid = xcd_grid(nblocks);
+    uint32_t *const hist = scratch, *const row_total = scratch + (size_t)wide * nblocks;
+    // the first histogram launch also finds the largest key, in one more
+    // workgroup; the emission has made the histogram of its segments
+    if (!seg)
+        k_radix_hist<TH, IT, SELF><<<grid + (top ? 1 : 0), TH, 0, stream>>>(
+            ki, n_max, pn, pass, drop, drop_key, hist, nblocks, top ? top->part_max : nullptr, top ? top->n_parts : 0,
+            top ? top->kmax : nullptr);
+    if (!SELF) k_radix_scan_rows<<<wide, kThreads, 0, stream>>>(hist, nblocks, n_max, pn, pass, tile, seg != nullptr,
+                                                               row_total);
+    const auto scatter = seg ? &k_radix_scatter<TH, IT, SELF, true> : &k_radix_scatter<TH, IT, SELF, false>;
+    scatter<<<grid, TH, 0, stream>>>(ki, vi, ko, vo, n_max, pn, pass, drop, drop_key, kept_out, hist, row_total, nblocks,
+                                     seg);
+}
+
+hipError_t sort_passes(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, int64_t n_max,
+                       const int64_t *n_dev, int bits, const RadixRange *range, bool drop, uint32_t drop_key,
+                       int64_t *kept_out, bool iota, const uint2 *seg, uint32_t *scratch, hipStream_t stream)
+{
+    const int passes = radix_passes(bits);
+    const bool fewer = drop || seg;  // items leave the sort in the first pass
+    uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
+    for (int p = 0; p < passes; ++p) {
+        const bool first = p == 0;
+        const RadixPass pass{range ? range->kmax : nullptr, range ? range->base : 0u, bits, p, passes};
+        const int wide = 1 << widest_digit(bits, range != nullptr, p);
+        const auto run = n_max <= kSelfMax  ? &radix_pass<kSortThreads, kSmallItems, true>
+                         : n_max <= kMidMax ? &radix_pass<kSortThreads, kSmallItems, false>
+                                            : &radix_pass<kSortThreads, kLargeItems, false>;
+        run(ki, iota && first ? nullptr : vi, ko, vo, n_max, fewer && !first ? kept_out : n_dev, pass, wide,
+            drop && first, drop_key, fewer && first ? kept_out : nullptr, first ? range : nullptr,
+            first ? seg : nullptr, scratch, stream);
+        std::swap(ki, ko);
+        std::swap(vi, vo);
+    }
+    return hipGetLastError();
+}
+}  // namespace
 
 hipError_t radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, int64_t n_max,
                       const int64_t *n_dev, int bits, const RadixRange *range, bool drop, uint32_t drop_key,
                       int64_t *kept_out, uint32_t *scratch, hipStream_t stream, bool iota)
 {
-    const int passes = radix_passes(bits);
-    if (n_max <= 0 || passes == 0) {
+    if (n_max <= 0 || radix_passes(bits) == 0) {
         if (drop) k_fill_u32<<<1, kThreads, 0, stream>>>(reinterpret_cast<uint32_t *>(kept_out), 0u, 2);
         return hipGetLastError();
     }
-    uint32_t *ki = keys, *vi = vals, *ko = keys_alt, *vo = vals_alt;
-    for (int p = 0; p < passes; ++p) {
-        const int wide = 1 << widest_digit(bits, range != nullptr, p);
-        uint32_t *const hist = scratch;
-        // the first pass drops, the later ones sort the kept items
-        const bool pdrop = drop && p == 0;
-        const int64_t *pn = drop && p > 0 ? kept_out : n_dev;
-        const uint32_t *pvi = iota && p == 0 ? nullptr : vi;
-        const RadixPass pass{range ? range->kmax : nullptr, range ? range->base : 0u, bits, p, passes};
-        // the first histogram launch also finds the largest key, in one more workgroup
-        const bool top = range && p == 0;
-        const uint32_t *parts = top ? range->part_max : nullptr;
-        const int n_parts = top ? range->n_parts : 0;
-        uint32_t *kmax_out = top ? range->kmax : nullptr;
-        if (n_max <= kSelfMax) {
-            constexpr int TH = kSelfThreads, IT = kSelfItems, tile = TH * IT;
-            const int nblocks = (int)((n_max + tile - 1) / tile), grid = (nblocks + 7) & ~7;
-            k_radix_hist<TH, IT, true><<<grid + top, TH, 0, stream>>>(ki, n_max, pn, pass, pdrop, drop_key, hist,
-                                                                      nblocks, parts, n_parts, kmax_out);
-            k_radix_scatter<TH, IT, true><<<grid, TH, 0, stream>>>(ki, pvi, ko, vo, n_max, pn, pass, pdrop, drop_key,
-                                                                   kept_out, hist, nullptr, nblocks);
-        } else {
-            constexpr int TH = kScanThreads, IT = kScanItems, tile = TH * IT;
-            const int nblocks = (int)((n_max + tile - 1) / tile), grid = (nblocks + 7) & ~7;
-            uint32_t *const row_total = scratch + (size_t)wide * nblocks;
-            k_radix_hist<TH, IT, false><<<grid + top, TH, 0, stream>>>(ki, n_max, pn, pass, pdrop, drop_key, hist,
-                                                                       nblocks, parts, n_parts, kmax_out);
-            k_radix_scan_rows<<<wide, kThreads, 0, stream>>>(hist, nblocks, n_max, pn, pass, tile, row_total);
-            k_radix_scatter<TH, IT, false><<<grid, TH, 0, stream>>>(ki, pvi, ko, vo, n_max, pn, pass, pdrop, drop_key,
-                                                                    kept_out, hist, row_total, nblocks);
-        }
-        uint32_t *t;
-        t = ki; ki = ko; ko = t;
-        t = vi; vi = vo; vo = t;
-    }
-    return hipGetLastError();
+    return sort_passes(keys, vals, keys_alt, vals_alt, n_max, n_dev, bits, range, drop, drop_key, kept_out, iota,
+                       nullptr, scratch, stream);
 }
 
 // sized for the smallest tile, so either choice of items per thread fits
@@ -945,26 +1185,34 @@ size_t scan_block_entries(int64_t n)
 namespace {
 template <int ITEMS>
 void scan_launch(const uint32_t *keys, const uint2 *boxes, const uint32_t *order, int64_t n, const int64_t *n_dev,
-                 int tile_w, int tile_h, int64_t capacity, uint32_t *offsets, uint32_t *row_offsets,
-                 uint32_t *row_owner, uint2 *sorted_boxes, unsigned long long *block_sums, int64_t *counters,
-                 hipStream_t stream)
+                 int tile_w, int tile_h, int64_t capacity, uint32_t *offsets, uint2 *steps, uint2 *sorted_boxes,
+                 unsigned long long *block_sums, int64_t *counters, hipStream_t stream)
 {
     const int nb = (int)((n + scan_tile(ITEMS) - 1) / scan_tile(ITEMS));
     k_scan_reduce<ITEMS><<<nb, kThreads, 0, stream>>>(keys, boxes, order, n, n_dev, tile_w, tile_h, offsets,
-                                                      row_offsets, sorted_boxes, block_sums);
+                                                      sorted_boxes, block_sums);
     // up to kScanSelfPrefixBlocks blocks, each apply block sums the block
     // pairs before it (at most that many loads) instead of a separate scan
     const bool self_prefix = nb <= kScanSelfPrefixBlocks;
     if (!self_prefix) k_scan_top<<<1, 1024, 0, stream>>>(block_sums, nb, counters);
-    k_scan_apply<ITEMS><<<nb, kThreads, 0, stream>>>(n, n_dev, capacity, block_sums, counters, self_prefix,
-                                                     nb >= kScanRowOrderBlocks, offsets, row_offsets, row_owner);
+    k_scan_apply<ITEMS><<<nb, kThreads, 0, stream>>>(n, n_dev, capacity, tile_w, tile_h, sorted_boxes, block_sums,
+                                                     counters, self_prefix, tile_shift(capacity), offsets, steps);
 }
+
+// The binning's scratch: the emission's steps (at least 64 rows each, or 8 of
+// a block), its blocks' segments (no more than the tile sort has blocks) and the tile sort's histograms.
+int64_t emit_blocks(int64_t capacity) { return ((capacity - 1) >> tile_shift(capacity)) + 1; }
+size_t step_words(int64_t capacity)
+{
+    return 4 * (size_t)(std::max(capacity / 64 + 1, 8 * emit_blocks(capacity)) / 2 + 1);
+}
+size_t seg_words(int64_t capacity) { return 4 * (size_t)(emit_blocks(capacity) / 2 + 1); }
 }  // namespace
 
 hipError_t binning_scan(const uint32_t *keys, const uint2 *boxes, const uint32_t *order, int64_t n,
                         const int64_t *n_dev, int tile_w, int tile_h, int64_t capacity, uint32_t *offsets,
-                        uint32_t *row_offsets, uint32_t *row_owner, uint2 *sorted_boxes,
-                        unsigned long long *block_sums, int64_t *counters, hipStream_t stream)
+                        uint32_t *bin_scratch, uint2 *sorted_boxes, unsigned long long *block_sums,
+                        int64_t *counters, hipStream_t stream)
 {
     if (n <= 0) {
         // counters[0] and counters[2] (int64) = 0, counters[1] (capacity) kept
@@ -973,30 +1221,49 @@ hipError_t binning_scan(const uint32_t *keys, const uint2 *boxes, const uint32_t
         return hipGetLastError();
     }
     if (n <= (int64_t(1) << 20))
-        scan_launch<4>(keys, boxes, order, n, n_dev, tile_w, tile_h, capacity, offsets, row_offsets, row_owner,
-                       sorted_boxes, block_sums, counters, stream);
+        scan_launch<4>(keys, boxes, order, n, n_dev, tile_w, tile_h, capacity, offsets,
+                       reinterpret_cast<uint2 *>(bin_scratch), sorted_boxes, block_sums, counters, stream);
     else
-        scan_launch<8>(keys, boxes, order, n, n_dev, tile_w, tile_h, capacity, offsets, row_offsets, row_owner,
-                       sorted_boxes, block_sums, counters, stream);
+        scan_launch<8>(keys, boxes, order, n, n_dev, tile_w, tile_h, capacity, offsets,
+                       reinterpret_cast<uint2 *>(bin_scratch), sorted_boxes, block_sums, counters, stream);
     return hipGetLastError();
 }
 
-int emit_grid(int num_cus) { return 8 * num_cus; }
-
-hipError_t launch_emit(const uint32_t *order, const uint32_t *offsets, const uint32_t *row_offsets,
-                       const uint32_t *row_owner, const uint2 *sorted_boxes, const Conic *conics, const DevView *views,
-                       int64_t n, int n_views, const int64_t *counters, int64_t capacity, int tile_w, int tile_h,
-                       uint32_t empty_tile, uint32_t *inst_tiles, uint32_t *inst_ids, uint2 *ranges,
-                       int64_t total_tiles, uint32_t *sched, int grid, hipStream_t stream)
+size_t bin_scratch_words(int64_t capacity, int tile_bits)
 {
+    return step_words(capacity) + seg_words(capacity) + radix_scratch_words(capacity, tile_bits, false);
+}
+
+hipError_t emit_and_sort(const uint32_t *order, const uint32_t *offsets, uint32_t *bin_scratch,
+                         const uint2 *sorted_boxes, const Conic *conics, const DevView *views, int64_t n,
+                         const int64_t *counters, int64_t capacity, int tile_w, int tile_h, int tile_bits,
+                         uint32_t *tiles, uint32_t *ids, uint32_t *tiles_alt, uint32_t *ids_alt, int64_t *listed,
+                         uint2 *ranges, int64_t total_tiles, uint32_t *sched, hipStream_t stream, bool emit)
+{
+    const uint2 *const steps = reinterpret_cast<const uint2 *>(bin_scratch);
+    uint2 *const seg = reinterpret_cast<uint2 *>(bin_scratch + step_words(capacity));
+    uint32_t *const hist = bin_scratch + step_words(capacity) + seg_words(capacity);
+    if (!emit)
+        return sort_passes(tiles, ids, tiles_alt, ids_alt, capacity, counters, tile_bits, nullptr, false, 0u, listed,
+                           false, seg, hist, stream);
+    const int nblocks = (int)emit_blocks(capacity), grid = xcd_grid(nblocks);
+    const RadixPass pass{nullptr, 0u, tile_bits, 0, radix_passes(tile_bits)};
     // runs even with no Gaussian: it clears the ranges and scheduling words
-#define RGS_EMIT(W, H)                                                                                               \
-    if (tile_w == W && tile_h == H) {                                                                                \
-        k_emit<W, H><<<grid, kThreads, 0, stream>>>(order, offsets, row_offsets, row_owner, sorted_boxes, conics,     \
-                                                    views, n > 0 ? n : 1, counters, capacity, empty_tile, inst_tiles, \
-                                                    inst_ids, reinterpret_cast<uint32_t *>(ranges), 2 * total_tiles,  \
-                                                    sched, (int64_t)sched_words());                                   \
-        return hipGetLastError();                                                                                    \
+#define RGS_EMIT_SEG(W, H, SEG, SELF)                                                                                 \
+    k_emit<W, H, SEG, SELF><<<grid, kEmitThreads, 0, stream>>>(order, offsets, steps, sorted_boxes, conics, views,     \
+                                                           n > 0 ? n : 1, counters, capacity, pass, tiles, ids, seg, \
+                                                           hist, nblocks,                                             \
+                                                           reinterpret_cast<uint32_t *>(ranges), 2 * total_tiles,     \
+                                                           sched, (int64_t)sched_words())
+#define RGS_EMIT(W, H)                                                                 \
+    if (tile_w == W && tile_h == H) {                                                  \
+        if (capacity <= kSelfMax)                                                      \
+            RGS_EMIT_SEG(W, H, kSortThreads * kSmallItems, true);                      \
+        else if (capacity <= kMidMax)                                                  \
+            RGS_EMIT_SEG(W, H, kSortThreads * kSmallItems, false);                     \
+        else                                                                           \
+            RGS_EMIT_SEG(W, H, kSortThreads * kLargeItems, false);                     \
+        return hipGetLastError();                                                      \
     }
     RGS_EMIT(8, 8)
     RGS_EMIT(8, 16)
@@ -1008,7 +1275,7 @@ hipError_t launch_emit(const uint32_t *order, const uint32_t *offsets, const uin
     RGS_EMIT(32, 16)
     RGS_EMIT(32, 32)
 #undef RGS_EMIT
-    (void)n_views;
+#undef RGS_EMIT_SEG
     return hipErrorInvalidValue;
 }
 

@@ -73,3 +73,41 @@ def test_sorted_order_and_lists(r, n, depths, w, h, views):
     assert np.all(np.diff(both) > 0)
     rng = read(buf, lay.tile_ranges, 2 * lay.total_tiles, np.uint32).reshape(-1, 2).astype(np.int64)
     assert np.array_equal(rng[:, 1] - rng[:, 0], np.bincount(tiles, minlength=lay.total_tiles))
+
+
+@pytest.mark.parametrize("tile", [(8, 8), (8, 16), (16, 16), (32, 8), (32, 32)])
+@pytest.mark.parametrize("kind", ["tiny", "wide", "mixed"])
+def test_emission_lists(r, kind, tile):
+    """Rows of one tile, rows across the whole view and both in one frame, at
+    capacities just above the need (the fewest blocks) and far above it: the
+    same lists, and those of the oracle."""
+    import oracle
+    import scenegen
+
+    say(f"case emission {kind} {tile}")
+    n = {"tiny": 3000, "wide": 150, "mixed": 1200}[kind]
+    sc = scenegen.tiny_scene(23, n, half_extent=1.0, log_scale_mean={"tiny": -6.0, "wide": -0.7, "mixed": -4.0}[kind],
+                             log_scale_std={"tiny": 0.2, "wide": 0.4, "mixed": 1.6}[kind])
+    cam = scenegen.pinhole(scenegen.look_at((0.2, 0.1, -3.0)), 611, 389, 60.0)
+    opts = scenegen.default_options(tile_w=tile[0], tile_h=tile[1])
+    g = {k: torch.from_numpy(np.ascontiguousarray(sc[k])).cuda() for k in
+         ("means", "log_scales", "quats", "opacity_logits", "sh")}
+    g["sh_degree"] = sc["sh_degree"]
+    _, (buf, ws) = r.render(g, [cam], opts, keep_workspace=True)
+    need = r.status(ws)[1]
+    got = []
+    for cap in (need, need + 1, 2 * need + 77, (1 << 20) + need):
+        buf, ws = r.new_workspace(n, [cam], cap, 0, opts)
+        outs = r.allocate_outputs([cam])
+        r.render_into(g, [cam], outs, ws, opts)
+        assert r.status(ws) == (True, need)
+        lay = r.layout(n, [cam], cap, 0, opts)
+        got.append(instance_lists(buf, lay, with_bands=True))
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.array_equal(a, b)
+    sp = oracle.preprocess(sc, cam, opts)
+    tiles, _, ids = oracle.tile_lists(sp, cam, opts, 0)
+    bad = np.nonzero(sp["hazard"] != 0)[0]
+    ok, keep = ~np.isin(got[0][1], bad), ~np.isin(ids, bad)
+    assert np.array_equal(got[0][0][ok], tiles[keep]) and np.array_equal(got[0][1][ok], ids[keep])
