@@ -113,7 +113,7 @@ struct rgs_context {
     std::vector<FrameEvents> pool;
     double stage_ms[kNumStages] = {0};
     int64_t frames = 0;
-    int grid_fwd[64] = {0}, grid_fwd_exact[64] = {0}, grid_bwd[64] = {0}, grid_bwd_exact[64] = {0};
+    int grid_fwd[kBlendKernels][64] = {{0}}, grid_bwd[64] = {0}, grid_bwd_exact[64] = {0};
     unsigned long long *view_stamps = nullptr;  // rgs_set_view_clocks (caller-owned device memory)
     int view_stamps_views = 0;
     std::map<std::string, TileShape> tune_cache;  // autotuned tile shapes by configuration class
@@ -479,8 +479,8 @@ struct Timer {
 void ensure_grids(rgs_context *ctx, TileShape s)
 {
     const int k = shape_index(s);
-    if (!ctx->grid_fwd[k]) ctx->grid_fwd[k] = blend_grid(s, false, ctx->num_cus);
-    if (!ctx->grid_fwd_exact[k]) ctx->grid_fwd_exact[k] = blend_grid(s, true, ctx->num_cus);
+    for (int kernel = 0; kernel < kBlendKernels; ++kernel)
+        if (!ctx->grid_fwd[kernel][k]) ctx->grid_fwd[kernel][k] = blend_grid(s, kernel, ctx->num_cus);
     if (!ctx->grid_bwd[k]) ctx->grid_bwd[k] = blend_backward_grid(s, false, ctx->num_cus);
     if (!ctx->grid_bwd_exact[k]) ctx->grid_bwd_exact[k] = blend_backward_grid(s, true, ctx->num_cus);
 }
@@ -554,14 +554,16 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     tm.mark(ST_TSORT);
     const uint32_t *inst_tiles = at<uint32_t>(ws, L.inst_tiles_a);
     const uint32_t *inst_ids = at<uint32_t>(ws, L.inst_ids_a);
-    const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? (uint32_t)RGS_SPLIT_LEN : 0u;
-    const int blend_blocks = opts.mip == 2 ? ctx->grid_fwd_exact[shape_index(s)] : ctx->grid_fwd[shape_index(s)];
-    const uint32_t waves = (uint32_t)(4 * blend_blocks);
+    const BlendMode mode = blend_mode(s, opts.mip == 2, L.total_tiles);
+    const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? kSplitLen : 0u;
+    const int blend_blocks = ctx->grid_fwd[mode.kernel()][shape_index(s)];
+    const uint32_t waves = (uint32_t)(mode.waves() * blend_blocks);
     RGS_HIP(ctx, launch_tile_ranges(inst_tiles, listed, L.capacity, L.total_tiles, split_min, waves, ranges, sched,
                                     at<uint32_t>(ws, L.tile_order), stream));
     tm.mark(ST_RANGES);
-    RGS_HIP(ctx, launch_blend(s, ranges, tile_order, sched + sched_item_count(), inst_ids, records, views, n_views,
-                              L.total_tiles, NV, dopt, sched, blend_blocks, item_clock, stream));
+    RGS_HIP(ctx, launch_blend(s, mode, ranges, tile_order, sched + sched_item_count(), inst_ids, records, views,
+                              n_views, L.total_tiles, NV, dopt, sched,
+                              (int)std::min<int64_t>(blend_blocks, L.total_tiles), item_clock, stream));
     tm.mark(ST_BLEND);
     if (view_stamps)
         RGS_HIP(ctx, launch_view_clock_max(item_clock, tile_order, sched + sched_item_count(), 2 * L.total_tiles,

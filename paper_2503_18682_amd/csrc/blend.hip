@@ -11,7 +11,8 @@
 // address from serialising every take), stages 64 raster records at a
 // time in its own LDS slice and reads them back as broadcasts, and leaves the
 // tile as soon as a ballot shows that no lane has a live pixel (early ray
-// termination).  No workgroup barrier is ever taken.
+// termination).  Small frames and exact MIP give the longest lists, or
+// all, to whole workgroups instead (k_blend_team).
 //
 // Per fragment (Sec. 4.2, eq. 16): with delta the pixel-centre offset from the
 // projected centre, n = G delta is the quad-plane offset times den and
@@ -208,6 +209,11 @@ struct PlainModel {
         put_test_form(dst, r, x0, y0, log2_pmin);
     }
     __device__ static Rec load(const float4 *p) { return load_trec(p); }
+    __device__ static float3 colour(const float4 *p)
+    {
+        const float4 d = p[3];
+        return make_float3(d.y, d.z, d.w);
+    }
     __device__ static bool test(const Rec &R, float pxr, float pyr, float, float, F &f)
     {
         return frag_test(R, pxr, pyr, f);
@@ -328,6 +334,7 @@ struct ExactMipModel {
                     e.x, e.y, e.z, e.w, f.x, f.y, f.z, f.w, g.x, g.y, g.z, g.w, h.x, h.y, h.z, h.w,
                     __float_as_uint(a.w)};
     }
+    __device__ static float3 colour(const float4 *p) { return make_float3(p[5].w, p[6].w, p[7].w); }
     __device__ static bool test(const Rec &R, float pxr, float pyr, float inv_norm, float log2_pmin, F &f)
     {
         const float dx = pxr - R.cx, dy = pyr - R.cy;
@@ -404,24 +411,22 @@ __device__ __forceinline__ int slot_y(int lane, int k)
     return SL.rh * (k / SL.bx) + lane / SL.cw;
 }
 
+constexpr uint32_t kPrioLen = 100u;
+
+// The items of a queue from `first` on, one at a time, by one wave.
 template <int TW, int TH, class M>
-__global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
-                                               const uint32_t *__restrict__ work_order,
-                                               const uint32_t *__restrict__ n_items_p,
-                                               const uint32_t *__restrict__ inst_ids,
-                                               const float4 *__restrict__ records, const DevView *__restrict__ views,
-                                               BlendParams P, unsigned int *__restrict__ queue)
+__device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, const uint32_t *__restrict__ work_order,
+                                            int64_t first, int64_t n_items, const uint32_t *__restrict__ inst_ids,
+                                            const float4 *__restrict__ records, const DevView *__restrict__ views,
+                                            const BlendParams &P, unsigned int *head, int q, int nq,
+                                            float4 (*__restrict__ s_rec)[M::kStaged])
 {
     constexpr int PPL = slot_layout(TW, TH).slots;
     static_assert(64 % TW == 0 && PPL * 64 == TW * TH, "tile shape");
-    __shared__ float4 s_rec[4][64][M::kStaged];
     const uint32_t amax_bits = __float_as_uint(P.alpha_max);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
-    unsigned int *const head = queue + q * kQueueStride;
-    const int64_t n_items = *n_items_p;
+    const int lane = threadIdx.x & 63;
     for (;;) {
-        const int64_t slot = q + (int64_t)nq * wave_fetch_add(head, 1u);
+        const int64_t slot = first + q + (int64_t)nq * wave_fetch_add(head, 1u);
         if (slot >= n_items) break;
         const uint32_t item = work_order[slot];
         const int tile = (int)(item >> 2);
@@ -436,6 +441,17 @@ __global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
         // pixel centres relative to the block corner; NaN marks a pixel that
         // is outside the image, outside the work item, or done
         const uint2 rg = ranges[tile];
+        // the longest lists end last: their waves issue first (3720 -> 3460 us for 16 views of 1M
+        // Gaussians; steps of 64 to 200 entries measured alike)
+        const uint32_t len = rg.y - rg.x;
+        if (len > 4u * kPrioLen)
+            __builtin_amdgcn_s_setprio(3);
+        else if (len > 2u * kPrioLen)
+            __builtin_amdgcn_s_setprio(2);
+        else if (len > kPrioLen)
+            __builtin_amdgcn_s_setprio(1);
+        else
+            __builtin_amdgcn_s_setprio(0);
         float T[PPL], C0[PPL], C1[PPL], C2[PPL], pxr[PPL], pyr[PPL], aux[PPL];
         int last[PPL];
         // pixel slots (64 pixels each) that hold a live pixel: a slot
@@ -465,7 +481,7 @@ __global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
             const uint32_t inst = inst_ids[rg.x + lane];
             float4 r[M::kRaw];
             M::fetch(r, records, inst, P.n_records, PPL <= 4);
-            M::stage(s_rec[wave][lane], r, x0, y0, P.log2_pmin);
+            M::stage(s_rec[lane], r, x0, y0, P.log2_pmin);
         }
         uint32_t nid = inst_ids[min(rg.x + 64 + lane, rg.y - 1u)];
         for (uint32_t base = rg.x; base < rg.y && wave_live; base += 64) {
@@ -477,7 +493,7 @@ __global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
             nid = inst_ids[min(base + 128 + lane, rg.y - 1u)];
             lds_wave_sync();
             for (uint32_t j = 0; j < nb; ++j) {
-                const typename M::Rec R = M::load(s_rec[wave][j]);
+                const typename M::Rec R = M::load(s_rec[j]);
                 const RowSpan span = row_span(R.rows, ty * TH);
                 const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
 #pragma unroll
@@ -521,7 +537,7 @@ __global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
             lds_wave_sync();
             if (have_next) {
                 M::settle(raw, cid, P.n_records, PPL <= 4);
-                M::stage(s_rec[wave][lane], raw, x0, y0, P.log2_pmin);
+                M::stage(s_rec[lane], raw, x0, y0, P.log2_pmin);
             }
         }
         }
@@ -542,6 +558,240 @@ __global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
         if (P.item_clock != nullptr) P.item_clock[slot] = wall_clock64();
     }
 }
+
+// Compositing of a tile by the eight waves of a workgroup: the split tiles,
+// two items in a row each, or all tiles of a small frame.  A frame ends no sooner
+// than its longest list, and a wave alone takes 400 to 1000 cycles for a list entry,
+// nearly all of it latency (a frame of 108 tiles kept 4 % of the VALU issue slots busy).
+// Here the list is taken in batches of 64 / slots records.  Waves 0 .. slots - 1 composite
+// one slot each: the chain T -> T (1 - alpha) is all that is left of a record, its alphas and
+// colours read from LDS four records ahead.  The other waves meanwhile compute the next batch's alphas,
+// which depend on no other record, and the last of them also stages the batch after that.
+// The values and their order are those of the single wave, bit for bit.
+// Measured, k_blend -> k_blend_team: 51 -> 25 us at 128x96, 78 -> 43 us at 317x211, 75 -> 52 us at
+// 1280x720; exact MIP 122 -> 72 us for two views of 801x533, 535 -> 330 us for two of 1032x1104.
+// Four waves that took turns (alphas, barrier, compositing) came to 39 us at 128x96.
+constexpr int kTeamThreads = 512, kTeamWaves = kTeamThreads / 64;
+
+// Two workgroups on a CU, or three where at most six registers spill for it (plain model, two slots: 88 -> 80).
+template <int TW, int TH, class M>
+constexpr int team_waves_per_simd()
+{
+    return M::kStaged == 4 && TW * TH <= 128 ? 6 : 4;
+}
+
+template <int TW, int TH, class M>
+__global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) void k_blend_team(
+    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ work_order, const uint32_t *__restrict__ n_items_p,
+    const uint32_t *__restrict__ inst_ids, const float4 *__restrict__ records, const DevView *__restrict__ views,
+    BlendParams P, int all_tiles, unsigned int *__restrict__ queue)
+{
+    constexpr int PPL = slot_layout(TW, TH).slots, B = 64 / PPL, NP = kTeamWaves - PPL;
+    static_assert(PPL <= 4, "a compositing wave per slot, and as many others");
+    // LDS: the alphas of two batches and the records of three; later a batch of records for each wave
+    constexpr int kAlpha4 = 2 * PPL * B * 16, kRec4 = 3 * B * M::kStaged, kWave4 = kTeamWaves * 64 * M::kStaged;
+    __shared__ float4 s_mem[kAlpha4 + kRec4 > kWave4 ? kAlpha4 + kRec4 : kWave4];
+    float(*const s_alpha)[PPL][B][64] = reinterpret_cast<float(*)[PPL][B][64]>(s_mem);
+    float4(*const s_rec)[B][M::kStaged] = reinterpret_cast<float4(*)[B][M::kStaged]>(s_mem + kAlpha4);
+    __shared__ unsigned long long s_hit[2][NP][PPL];  // records that reach a pixel of the slot, by producer
+    __shared__ uint32_t s_live[PPL];                  // the slot holds a pixel that has not stopped
+    __shared__ uint32_t s_ticket[2];
+    const uint32_t amax_bits = __float_as_uint(P.alpha_max);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
+    unsigned int *const head = queue + q * kQueueStride;  // the teams' is half a stride on
+    // units of work: the split tiles, and all the others after them if asked for
+    const int64_t n_split = n_items_p[1] >> 1, n_units = all_tiles ? (int64_t)n_items_p[0] - n_split : n_split;
+    const bool composer = wave < PPL, stager = wave == kTeamWaves - 1 && lane < B;
+    const int prod = wave - PPL;  // producer
+    // the next tile's ticket is taken while this one is composited
+    if (wave == 0) s_ticket[0] = wave_fetch_add(head + kQueueStride / 2, 1u);
+    for (int turn = 0;; turn ^= 1) {
+        __syncthreads();
+        const int64_t unit = q + (int64_t)nq * (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket[turn]);
+        if (unit >= n_units) break;  // uniform over the workgroup
+        const int64_t slot = unit < n_split ? 2 * unit : unit + n_split;
+        uint32_t ticket = 0u;
+        if (wave == kTeamWaves - 2) ticket = wave_fetch_add(head + kQueueStride / 2, 1u);
+        const int tile = (int)(work_order[slot] >> 2);
+        const uint2 rg = ranges[tile];
+        const DevView &V = views[find_view(views, P.n_views, tile)];
+        const int local = tile - V.tile_base;
+        const int tx = local % V.tiles_x, ty = local / V.tiles_x;
+        const int ox = (tx * TW) & ~31, oy = (ty * TH) & ~31;
+        const float x0 = (float)ox, y0 = (float)oy;
+        float pxr[PPL], pyr[PPL], aux[PPL];
+        bool done = true;  // (composers) the lane's pixel is outside the image or has stopped
+#pragma unroll
+        for (int k = 0; k < PPL; ++k) {
+            const int px = tx * TW + slot_x<TW, TH>(lane, k), py = ty * TH + slot_y<TW, TH>(lane, k);
+            const bool on = px < V.width && py < V.height;
+            pxr[k] = (float)(px - ox) + 0.5f;
+            pyr[k] = on ? (float)(py - oy) + 0.5f : __builtin_nanf("");
+            aux[k] = M::pixel_aux(V, px, py);
+            if (k == wave) done = !on;
+        }
+        float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
+        int last = (int)(rg.y - rg.x);
+        const int n_batches = (last + B - 1) / B;
+        uint32_t nid = 0u;
+        if (stager && last > 0) {
+            const uint32_t inst = inst_ids[min(rg.x + lane, rg.y - 1u)];
+            nid = inst_ids[min(rg.x + B + lane, rg.y - 1u)];
+            if (rg.x + lane < rg.y) {
+                float4 r[M::kRaw];
+                M::fetch(r, records, inst, P.n_records, PPL <= 4);
+                M::stage(s_rec[0][lane], r, x0, y0, P.log2_pmin);
+            }
+        }
+        if (composer) {
+            const bool any = __ballot(!done) != 0;
+            if (lane == 0) s_live[wave] = any ? 1u : 0u;
+        }
+        // step b: producers take batch b, composers batch b - 1
+        int rb = 0;  // record buffer of batch b
+        for (int b = 0; b <= n_batches; ++b) {
+            __syncthreads();
+            uint32_t live = 0u;
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) live |= s_live[k] << k;
+            live = __builtin_amdgcn_readfirstlane(live);
+            if (live == 0u) break;  // uniform: flags change between the barriers of two steps only
+            __syncthreads();
+            const int rprev = rb == 0 ? 2 : rb - 1, rnext = rb == 2 ? 0 : rb + 1;
+            if (composer) {
+                if (b > 0 && ((live >> wave) & 1u)) {
+                    float(*const A)[64] = s_alpha[(b - 1) & 1][wave];
+                    float4(*const Rc)[M::kStaged] = s_rec[rprev];
+                    unsigned long long m = 0ull;
+#pragma unroll
+                    for (int w = 0; w < NP; ++w) m |= s_hit[(b - 1) & 1][w][wave];
+                    // (the builtin returns a signed int)
+                    m = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)m) |
+                        (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(m >> 32)) << 32;
+                    const int first = (b - 1) * B;
+                    // groups of four records, the next group's values in flight
+                    constexpr int G = 4;
+                    int j[G], jn[G];
+                    float a[G], an[G];
+                    float3 c[G], cn[G];
+                    auto fetch = [&](int(&jj)[G], float(&aa)[G], float3(&cc)[G]) {
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            jj[i] = m ? __builtin_ctzll(m) : 64;
+                            m &= m - 1ull;
+                            const int at = jj[i] & (B - 1);
+                            aa[i] = A[at][lane];
+                            cc[i] = M::colour(Rc[at]);
+                        }
+                    };
+                    fetch(j, a, c);
+                    while (j[0] < 64) {
+                        fetch(jn, an, cn);
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            if (j[i] == 64) break;  // uniform
+                            const float ai = done ? 0.0f : a[i];
+                            if (__ballot(ai > 0.0f) == 0) continue;
+                            const float ta = T * ai;
+                            const float Tn = T - ta;
+                            const bool stop = Tn < P.t_eps;
+                            const float wt = stop ? 0.0f : ta;
+                            C0 = __builtin_fmaf(wt, c[i].x, C0);
+                            C1 = __builtin_fmaf(wt, c[i].y, C1);
+                            C2 = __builtin_fmaf(wt, c[i].z, C2);
+                            T = stop ? T : Tn;
+                            last = stop ? first + j[i] : last;
+                            done = done | stop;
+                        }
+                        if (__ballot(!done) == 0) break;
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            j[i] = jn[i];
+                            a[i] = an[i];
+                            c[i] = cn[i];
+                        }
+                    }
+                    const bool any = __ballot(!done) != 0;
+                    if (lane == 0) s_live[wave] = any ? 1u : 0u;
+                }
+            } else if (b < n_batches) {
+                const uint32_t base = rg.x + (uint32_t)(b * B);
+                const int nb = min(B, (int)(rg.y - base));
+                const uint32_t cid = nid;
+                float4 raw[M::kRaw];
+                if (stager) {
+                    M::load_raw(raw, records, cid, P.n_records);
+                    nid = inst_ids[min(base + 2 * B + lane, rg.y - 1u)];
+                }
+                unsigned long long hits[PPL];
+#pragma unroll
+                for (int k = 0; k < PPL; ++k) hits[k] = 0ull;
+                for (int j = prod; j < nb; j += NP) {
+                    const typename M::Rec R = M::load(s_rec[rb][j]);
+                    const RowSpan span = row_span(R.rows, ty * TH);
+                    const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
+#pragma unroll
+                    for (int k = 0; k < PPL; ++k) {
+                        if (!((live >> k) & 1u) || !band_open<TW, TH>(bands, span, k)) continue;
+                        typename M::F f;
+                        const bool hit = M::test(R, pxr[k], pyr[k], aux[k], P.log2_pmin, f);
+                        if (__ballot(hit) == 0) continue;
+                        const float w = M::omega(R, f);
+                        s_alpha[b & 1][k][j][lane] = hit ? __uint_as_float(min(__float_as_uint(w), amax_bits)) : 0.0f;
+                        hits[k] |= 1ull << j;
+                    }
+                }
+                if (lane == 0)
+#pragma unroll
+                    for (int k = 0; k < PPL; ++k) s_hit[b & 1][prod][k] = hits[k];
+                if (stager && base + B + lane < rg.y) {
+                    M::settle(raw, cid, P.n_records, PPL <= 4);
+                    M::stage(s_rec[rnext][lane], raw, x0, y0, P.log2_pmin);
+                }
+            }
+            rb = rnext;
+        }
+        if (composer) {
+            const size_t plane = (size_t)V.width * V.height;
+            const int px = tx * TW + slot_x<TW, TH>(lane, wave), py = ty * TH + slot_y<TW, TH>(lane, wave);
+            if (px < V.width && py < V.height) {
+                const size_t p = (size_t)py * V.width + px;
+                V.rgb[p] = C0 + T * P.bg0;
+                V.rgb[plane + p] = C1 + T * P.bg1;
+                V.rgb[2 * plane + p] = C2 + T * P.bg2;
+                V.final_T[p] = T;
+                V.n_contrib[p] = last;
+            }
+        }
+        // completion clock of the tile (every lane stores the same value)
+        if (P.item_clock != nullptr) {
+            const unsigned long long now = wall_clock64();
+            P.item_clock[slot] = now;
+            if (unit < n_split) P.item_clock[slot + 1] = now;
+        }
+        if (wave == kTeamWaves - 2) s_ticket[turn ^ 1] = ticket;
+    }
+    if (all_tiles) return;
+    // (all waves are past the barrier of the last ticket: the batches' memory is free)
+    blend_items<TW, TH, M>(ranges, work_order, 2 * n_split, n_items_p[0], inst_ids, records, views, P, head, q, nq,
+                           reinterpret_cast<float4(*)[M::kStaged]>(s_mem) + wave * 64);
+}
+
+template <int TW, int TH, class M>
+__global__ __launch_bounds__(256) void k_blend(const uint2 *__restrict__ ranges,
+                                               const uint32_t *__restrict__ work_order,
+                                               const uint32_t *__restrict__ n_items_p,
+                                               const uint32_t *__restrict__ inst_ids,
+                                               const float4 *__restrict__ records, const DevView *__restrict__ views,
+                                               BlendParams P, int, unsigned int *__restrict__ queue)
+{
+    __shared__ float4 s_rec[4][64][M::kStaged];
+    const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
+    blend_items<TW, TH, M>(ranges, work_order, 0, *n_items_p, inst_ids, records, views, P, queue + q * kQueueStride, q,
+                           nq, s_rec[threadIdx.x >> 6]);
+}
+
 
 // Sums of 16 per-lane values over the wave by transposing while reducing:
 // at each step a lane keeps one half of its values and takes its partner's
@@ -972,11 +1222,10 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
     }
 }
 
-template <int TW, int TH>
-int occupancy_grid(const void *kernel, int num_cus)
+int occupancy_grid(const void *kernel, int threads, int num_cus)
 {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     return per_cu * num_cus;
 }
 
@@ -1024,47 +1273,73 @@ bool tile_shape_supported(int w, int h)
 
 #define RGS_SHAPES(X) X(8, 8) X(8, 16) X(8, 32) X(16, 8) X(16, 16) X(16, 32) X(32, 8) X(32, 16) X(32, 32)
 
-int blend_grid(TileShape s, bool exact_mip, int num_cus)
+// Where teams are taken.  Exact MIP always gains, as the team kernel costs it no
+// occupancy (4 waves per SIMD either way): 122 -> 72 us at 6868 tiles, 535 -> 330 us at 17802.
+// The plain kernel goes from 7 to 6 waves per SIMD, and gains only where the longest
+// lists bound the frame: 75 -> 52 us at 7200 tiles, 105 -> 108 us at 9600 with long lists
+// everywhere, 123 -> 152 us at 16200.  A team for every tile spends twice the instructions:
+// 78 -> 43 us at 560 tiles, but 75 -> 141 us at 7200.
+constexpr int64_t kTeamTiles = 10000, kTeamAllTiles = 1024;
+constexpr int kTeamSlots = 4;
+
+BlendMode blend_mode(TileShape s, bool exact_mip, int64_t total_tiles)
 {
-#define X(W, H)                                                                                                  \
-    if (s.w == W && s.h == H)                                                                                    \
-        return exact_mip ? occupancy_grid<W, H>(reinterpret_cast<const void *>(&k_blend<W, H, ExactMipModel>), num_cus) \
-                         : occupancy_grid<W, H>(reinterpret_cast<const void *>(&k_blend<W, H, PlainModel>), num_cus);
+    const bool team = slot_layout(s.w, s.h).slots <= kTeamSlots && (exact_mip || total_tiles <= kTeamTiles);
+    return BlendMode{exact_mip, team, team && total_tiles <= kTeamAllTiles};
+}
+
+// The kernel of a shape and mode; null where blend_mode never asks for it.
+using BlendKernel = void (*)(const uint2 *, const uint32_t *, const uint32_t *, const uint32_t *, const float4 *,
+                             const DevView *, BlendParams, int, unsigned int *);
+template <int TW, int TH>
+BlendKernel blend_kernel(int kernel)
+{
+    if constexpr (slot_layout(TW, TH).slots <= kTeamSlots)
+        return kernel == 0   ? &k_blend<TW, TH, PlainModel>
+               : kernel == 2 ? &k_blend_team<TW, TH, PlainModel>
+               : kernel == 3 ? &k_blend_team<TW, TH, ExactMipModel>
+                             : nullptr;
+    else
+        return kernel == 0 ? &k_blend<TW, TH, PlainModel> : kernel == 1 ? &k_blend<TW, TH, ExactMipModel> : nullptr;
+}
+
+BlendKernel blend_kernel(TileShape s, int kernel)
+{
+#define X(W, H) \
+    if (s.w == W && s.h == H) return blend_kernel<W, H>(kernel);
     RGS_SHAPES(X)
 #undef X
-    return num_cus;
+    return nullptr;
+}
+
+int blend_grid(TileShape s, int kernel, int num_cus)
+{
+    const BlendKernel k = blend_kernel(s, kernel);
+    return k ? occupancy_grid(reinterpret_cast<const void *>(k), kernel & 2 ? kTeamThreads : 256, num_cus) : num_cus;
 }
 
 int blend_backward_grid(TileShape s, bool exact_mip, int num_cus)
 {
 #define X(W, H)                                                                                                  \
     if (s.w == W && s.h == H)                                                                                    \
-        return exact_mip ? occupancy_grid<W, H>(reinterpret_cast<const void *>(&k_blend_bwd_exact<W, H>), num_cus) \
-                         : occupancy_grid<W, H>(reinterpret_cast<const void *>(&k_blend_bwd<W, H>), num_cus);
+        return exact_mip ? occupancy_grid(reinterpret_cast<const void *>(&k_blend_bwd_exact<W, H>), 256, num_cus) \
+                         : occupancy_grid(reinterpret_cast<const void *>(&k_blend_bwd<W, H>), 256, num_cus);
     RGS_SHAPES(X)
 #undef X
     return num_cus;
 }
 
-hipError_t launch_blend(TileShape s, const uint2 *ranges, const uint32_t *work_order, const uint32_t *n_items,
-                        const uint32_t *inst_ids, const float4 *records, const DevView *views, int n_views,
-                        int64_t total_tiles, int64_t n_records, const DevOptions &opt, unsigned int *queue, int grid,
-                        unsigned long long *item_clock, hipStream_t stream)
+hipError_t launch_blend(TileShape s, BlendMode mode, const uint2 *ranges, const uint32_t *work_order,
+                        const uint32_t *n_items, const uint32_t *inst_ids, const float4 *records, const DevView *views,
+                        int n_views, int64_t total_tiles, int64_t n_records, const DevOptions &opt, unsigned int *queue,
+                        int grid, unsigned long long *item_clock, hipStream_t stream)
 {
     const BlendParams P = make_params(opt, n_views, total_tiles, n_records, item_clock);
-#define X(W, H)                                                                                                  \
-    if (s.w == W && s.h == H) {                                                                                  \
-        if (opt.mip == 2)                                                                                        \
-            k_blend<W, H, ExactMipModel><<<grid, 256, 0, stream>>>(ranges, work_order, n_items, inst_ids, records, \
-                                                                   views, P, queue);                             \
-        else                                                                                                     \
-            k_blend<W, H, PlainModel><<<grid, 256, 0, stream>>>(ranges, work_order, n_items, inst_ids, records,   \
-                                                                views, P, queue);                                \
-        return hipGetLastError();                                                                                \
-    }
-    RGS_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
+    const BlendKernel k = blend_kernel(s, mode.kernel());
+    if (!k) return hipErrorInvalidValue;
+    k<<<grid, mode.team ? kTeamThreads : 256, 0, stream>>>(ranges, work_order, n_items, inst_ids, records, views, P,
+                                                           mode.all ? 1 : 0, queue);
+    return hipGetLastError();
 }
 
 hipError_t launch_blend_backward(TileShape s, const uint2 *ranges, const uint32_t *work_order,

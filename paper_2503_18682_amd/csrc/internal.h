@@ -169,11 +169,12 @@ constexpr int kQueueStride = 1024;
 // order: work items tile << 2 | part (0 whole tile; 1, 2 the first and
 // second half of its pixel rows, for tiles whose list is longer than
 // max(split_min, *counters / waves), split_min 0 = never split) by
-// decreasing list length, at most 2 * total_tiles of them.
+// decreasing list length, the split tiles before all others, at most
+// 2 * total_tiles of them.
 // `ranges` and `sched` must be zero (emit_and_sort clears them).  `sched` holds
 // sched_words() uint32: the forward queue heads from word 0, the backward
-// heads from sched_backward_heads(), bucket histograms, and the number of
-// work items at sched_item_count().
+// heads from sched_backward_heads(), bucket histograms, and at
+// sched_item_count() the number of work items and, next, of those of split tiles.
 size_t sched_words();
 size_t sched_backward_heads();
 size_t sched_item_count();
@@ -181,20 +182,37 @@ hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counter
                               int64_t total_tiles, uint32_t split_min, uint32_t waves, uint2 *ranges,
                               uint32_t *sched, uint32_t *work_order, hipStream_t stream);
 
-// Shortest list composited as two half-tile work items (for tile shapes with
-// at least two pixel slots per lane).
-#ifndef RGS_SPLIT_LEN
-#define RGS_SPLIT_LEN 256
-#endif
+// Shortest list composited as two half-tile work items, or by a team (for tile
+// shapes with at least two pixel slots per lane).  Teams: a 1280x720 frame took 75 us
+// with 256, 55 us with 128 and 63 us with 64; two exact MIP views of 801x533 108, 72 and 86 us.
+// Large frames do not mind (1920x1080 and 4 views of a megapixel: the same with 128 and 256).
+constexpr uint32_t kSplitLen = 128;
 
-// Compositing of the work items work_order[0, *n_items) (see
-// launch_tile_ranges); `queue` holds the kQueues heads (zero).
+// How the tiles of a frame are composited.
+//   per wave   a wave takes whole tiles and halves (k_blend)
+//   teams      the workgroups first take the split tiles, all waves of a
+//              workgroup on one tile, then go on as above (k_blend_team)
+//   all teams  every tile by a workgroup
+// A team needs about twice the instructions of a wave, but a third of
+// its time per list entry.
+struct BlendMode {
+    bool exact_mip, team, all;
+    int kernel() const { return (exact_mip ? 1 : 0) + (team ? 2 : 0); }
+    int waves() const { return team ? 8 : 4; }  // of a workgroup
+};
+constexpr int kBlendKernels = 4;
+// The rule, by shape, model and number of tiles of the frame.
+BlendMode blend_mode(TileShape shape, bool exact_mip, int64_t total_tiles);
+
+// Compositing of the work items work_order[0, n_items[0]), of which the first
+// n_items[1] are those of split tiles (see launch_tile_ranges); `queue` holds the
+// kQueues heads (zero; the teams' heads are half a stride behind them).
 // item_clock (may be null): per work-order slot, the device wall clock when
 // the item finished.
-hipError_t launch_blend(TileShape shape, const uint2 *ranges, const uint32_t *work_order, const uint32_t *n_items,
-                        const uint32_t *inst_ids, const float4 *records, const DevView *views, int n_views,
-                        int64_t total_tiles, int64_t n_records, const DevOptions &opt, unsigned int *queue, int grid,
-                        unsigned long long *item_clock, hipStream_t stream);
+hipError_t launch_blend(TileShape shape, BlendMode mode, const uint2 *ranges, const uint32_t *work_order,
+                        const uint32_t *n_items, const uint32_t *inst_ids, const float4 *records, const DevView *views,
+                        int n_views, int64_t total_tiles, int64_t n_records, const DevOptions &opt, unsigned int *queue,
+                        int grid, unsigned long long *item_clock, hipStream_t stream);
 
 // Per-view completion clocks: stamps[0] = frame start (written by
 // launch_view_clock_start, which also clears stamps[1..n_views]), stamps[1 + v]
@@ -204,7 +222,7 @@ hipError_t launch_view_clock_start(unsigned long long *stamps, int n_views, hipS
 hipError_t launch_view_clock_max(const unsigned long long *item_clock, const uint32_t *work_order,
                                  const uint32_t *n_items, int64_t max_items, const DevView *views, int n_views,
                                  unsigned long long *stamps, hipStream_t stream);
-int blend_grid(TileShape shape, bool exact_mip, int num_cus);
+int blend_grid(TileShape shape, int kernel, int num_cus);  // resident workgroups of BlendMode::kernel()
 
 // Backward compositing over the same work items (whole tiles and halves).
 hipError_t launch_blend_backward(TileShape shape, const uint2 *ranges, const uint32_t *work_order,

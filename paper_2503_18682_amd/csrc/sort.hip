@@ -989,19 +989,22 @@ __global__ __launch_bounds__(kThreads) void k_tile_ranges(const uint32_t *__rest
 
 // -------------------------------------------------------- tile scheduling
 // Work order of the compositing kernels: work items sorted by decreasing list
-// length (coarse buckets of 4 entries, order inside a bucket arbitrary), so
+// length (coarse buckets, order inside a bucket arbitrary), so
 // the longest lists start first and the persistent grid drains evenly.  A
 // tile whose list is longer than the average work of a compositing wave
 // (listed instances / waves, at least split_min; split_min 0: never split)
 // becomes two items, each compositing half of the tile's pixel rows against
-// the whole list, which halves the longest chains of dependent work.  Item
+// the whole list, which halves the longest chains of dependent work; split tiles
+// come before all others, so that k_blend_team finds them by their number.  Item
 // value = tile << 2 | part (0 whole tile, 1 first half, 2 second half).
 constexpr int kSchedBuckets = 256;
+constexpr int kSplitBuckets = 64;  // the buckets of split tiles, above those of all others
 constexpr int64_t kRangeBlocks = 4096;
 
-__device__ __forceinline__ uint32_t work_bucket(uint32_t len)
+__device__ __forceinline__ uint32_t work_bucket(uint32_t len, uint32_t parts)
 {
-    return min(len >> 2, (uint32_t)(kSchedBuckets - 1));
+    return parts == 2u ? (uint32_t)(kSchedBuckets - kSplitBuckets) + min(len >> 5, (uint32_t)(kSplitBuckets - 1))
+                       : min(len >> 2, (uint32_t)(kSchedBuckets - kSplitBuckets - 1));
 }
 
 __device__ __forceinline__ uint32_t split_length(const int64_t *listed, uint32_t split_min, uint32_t waves)
@@ -1027,7 +1030,8 @@ __global__ __launch_bounds__(kThreads) void k_sched_hist(const uint2 *__restrict
     const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (t < total_tiles) {
         const uint2 r = ranges[t];
-        atomicAdd(&cnt[work_bucket(r.y - r.x)], work_parts(r.y - r.x, split_len));
+        const uint32_t parts = work_parts(r.y - r.x, split_len);
+        atomicAdd(&cnt[work_bucket(r.y - r.x, parts)], parts);
     }
     __syncthreads();
     if (cnt[threadIdx.x]) atomicAdd(&hist[threadIdx.x], cnt[threadIdx.x]);
@@ -1050,14 +1054,17 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     const uint32_t before = block_inclusive_scan<kWaves>(hb, smem, &tot) - hb;
     base[kSchedBuckets - 1 - threadIdx.x] = before;
     cnt[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *n_items = tot;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) n_items[0] = tot;
+        if (threadIdx.x == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
+    }
     __syncthreads();
     const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     uint32_t b = 0, rank = 0, parts = 0;
     if (t < total_tiles) {
         const uint2 r = ranges[t];
-        b = work_bucket(r.y - r.x);
         parts = work_parts(r.y - r.x, split_len);
+        b = work_bucket(r.y - r.x, parts);
         rank = atomicAdd(&cnt[b], parts);
     }
     __syncthreads();
