@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
 // is culled.  A clipped vertex at z <= 0 (only the camera centre can be one),
 // or a polygon beyond kClipMaxVerts vertices (rounding only), keeps the
 // whole view.  One wave per block; each lane keeps its two polygons in LDS.
-constexpr int kClipBlock = 64, kClipMaxVerts = 16, kClipGrid = 32;
+constexpr int kClipBlock = 64, kClipMaxVerts = 16, kClipGrid = 256;
 
 __global__ __launch_bounds__(kClipBlock) void k_clip_crossing(const double *__restrict__ crossing,
                                                               const unsigned long long *__restrict__ crossing_count,
