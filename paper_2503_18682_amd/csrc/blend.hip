@@ -411,7 +411,20 @@ __device__ __forceinline__ int slot_y(int lane, int k)
     return SL.rh * (k / SL.bx) + lane / SL.cw;
 }
 
+// The longest lists end last: their waves issue first (k_blend 3720 -> 3460 us for 8 views of 3M
+// Gaussians, k_blend_bwd 10.6 -> 9.65 ms for 16 views of 6M; steps of 64 to 200 entries measured alike).
 constexpr uint32_t kPrioLen = 100u;
+__device__ __forceinline__ void prioritise(uint32_t len)
+{
+    if (len > 4u * kPrioLen)
+        __builtin_amdgcn_s_setprio(3);
+    else if (len > 2u * kPrioLen)
+        __builtin_amdgcn_s_setprio(2);
+    else if (len > kPrioLen)
+        __builtin_amdgcn_s_setprio(1);
+    else
+        __builtin_amdgcn_s_setprio(0);
+}
 
 // The items of a queue from `first` on, one at a time, by one wave.
 template <int TW, int TH, class M>
@@ -441,17 +454,7 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
         // pixel centres relative to the block corner; NaN marks a pixel that
         // is outside the image, outside the work item, or done
         const uint2 rg = ranges[tile];
-        // the longest lists end last: their waves issue first (3720 -> 3460 us for 16 views of 1M
-        // Gaussians; steps of 64 to 200 entries measured alike)
-        const uint32_t len = rg.y - rg.x;
-        if (len > 4u * kPrioLen)
-            __builtin_amdgcn_s_setprio(3);
-        else if (len > 2u * kPrioLen)
-            __builtin_amdgcn_s_setprio(2);
-        else if (len > kPrioLen)
-            __builtin_amdgcn_s_setprio(1);
-        else
-            __builtin_amdgcn_s_setprio(0);
+        prioritise(rg.y - rg.x);
         float T[PPL], C0[PPL], C1[PPL], C2[PPL], pxr[PPL], pyr[PPL], aux[PPL];
         int last[PPL];
         // pixel slots (64 pixels each) that hold a live pixel: a slot
@@ -847,6 +850,7 @@ __device__ __forceinline__ float wave_sum16(const float (&v)[16], int lane)
     float x = (up ? c[1] : c[0]) + dpp<kDppRowHalfMirror>(up ? c[0] : c[1]);
     x += dpp<kDppQuadXor2>(x);
     x += dpp<kDppQuadXor1>(x);
+    asm("" : "+v"(x));  // here, not under the caller's lane mask, where the sum could not take its DPP operand
     return x;
 }
 
@@ -854,6 +858,13 @@ __device__ __forceinline__ int wave_sum16_index(int lane)
 {
     return ((lane >> 5) & 1) * 8 + ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
 }
+
+// Backward compositing: the list is walked back from each pixel's last entry.
+// Bound by VALU issue (about 110 instructions for a record that reaches one slot, 45 of them the
+// sums over the wave), so the record's address and id cost as little as they can: one LDS
+// address for all of its reads, the id beside the record and taken as a scalar, a scalar walk.
+// Together 11.45 -> 10.6 ms for 16 views of 6M Gaussians, 1464 -> 1410 us for 4 views of 1M.
+__device__ __forceinline__ void put_id(float4 *rec, uint32_t id) { rec[4].x = __uint_as_float(id); }
 
 template <int TW, int TH>
 __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ranges,
@@ -865,8 +876,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
                                                    float *__restrict__ record_grads, unsigned int *__restrict__ queue)
 {
     constexpr int PPL = slot_layout(TW, TH).slots;
-    __shared__ float4 s_rec[4][64][4];
-    __shared__ uint32_t s_id[4][64];
+    __shared__ float4 s_rec[4][64][5];  // the test form and, in the fifth, the record's id
     const uint32_t amax_bits = __float_as_uint(P.alpha_max);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
@@ -912,7 +922,8 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, d, 64));
         const uint2 rg = ranges[tile];
-        maxlast = min(maxlast, (int)(rg.y - rg.x));
+        maxlast = __builtin_amdgcn_readfirstlane(min(maxlast, (int)(rg.y - rg.x)));  // the walk is uniform
+        prioritise((uint32_t)maxlast);
         // The last batch of the walked part of the list goes straight to LDS.
         // While a batch is walked back, the raw records of the batch before
         // it and the ids of the one before that are in flight, with no branch
@@ -924,7 +935,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
             if (lane < maxlast - lo) {
                 const uint32_t v = inst_ids[rg.x + lo + lane];
                 const uint32_t id = v & kIdMask;
-                s_id[wave][lane] = id < P.n_records ? id : 0xffffffffu;
+                put_id(s_rec[wave][lane], id < P.n_records ? id : 0xffffffffu);
                 float4 r[4];
                 fetch_record(r, records, v, P.n_records, PPL <= 4);
                 put_test_form(s_rec[wave][lane], r, x0, y0, P.log2_pmin);
@@ -933,7 +944,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
             nid = inst_ids[rg.x + min(nlo + lane, maxlast - 1)];
         }
         for (int hi = maxlast; hi > 0; hi -= 64) {
-            const int lo = hi > 64 ? hi - 64 : 0;
+            const int lo = __builtin_amdgcn_readfirstlane(hi > 64 ? hi - 64 : 0);
             const int nb = hi - lo;
             const int nlo = lo > 64 ? lo - 64 : 0;
             const bool have_next = lane < lo - nlo;
@@ -943,9 +954,15 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
             const int nnlo = nlo > 64 ? nlo - 64 : 0;
             nid = inst_ids[rg.x + min(nnlo + lane, maxlast - 1)];
             lds_wave_sync();
-            for (int jj = nb - 1; jj >= 0; --jj) {
-                const int j = lo + jj;
-                const TRec R = load_trec(s_rec[wave][jj]);
+            // the record's LDS address, kept in one register (left to itself the
+            // compiler recomputes it for each of the reads)
+            uint32_t at = (uint32_t)((wave * 64 + nb) * sizeof(s_rec[0][0]));
+            for (int j = hi - 1; j >= lo; --j) {
+                at -= (uint32_t)sizeof(s_rec[0][0]);
+                asm("" : "+v"(at));
+                const float4 *const rp = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_rec) + at);
+                const TRec R = load_trec(rp);
+                const uint32_t rid = __builtin_amdgcn_readfirstlane(__float_as_uint(rp[4].x));
                 const RowSpan span = row_span(R.rows, ty * TH);
                 const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
                 // the slots of a lane share its pixel column when they are row
@@ -1029,9 +1046,8 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
                                         dg, db, 0.f, 0.f, 0.f};
                 const float sum = wave_sum16(vals, lane);
                 const int c = wave_sum16_index(lane);
-                const uint32_t rid = s_id[wave][jj];
                 // one lane per component adds it to the record's accumulators
-                if ((lane & 3) == 0 && c < 13 && rid != 0xffffffffu)
+                if (rid != 0xffffffffu && (lane & 3) == 0 && c < 13)
                     atomicAdd(record_grads + (size_t)rid * kGradFloats + c, sum);
             }
             lds_wave_sync();
@@ -1039,7 +1055,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
                 PlainModel::settle(raw, cid, P.n_records, PPL <= 4);
                 put_test_form(s_rec[wave][lane], raw, x0, y0, P.log2_pmin);
                 const uint32_t id = cid & kIdMask;
-                s_id[wave][lane] = id < P.n_records ? id : 0xffffffffu;
+                put_id(s_rec[wave][lane], id < P.n_records ? id : 0xffffffffu);
             }
         }
     }
@@ -1058,6 +1074,9 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 //   [0, 1] the projected centre, [2..4] P0, [5..7] P1, [8..10] Q0,
 //   [11..13] Q1, [14..16] rho, [17..19] s'^2, [20] e, [21] log2o,
 //   [22..24] colour.
+// Most of its 200 instructions per slot are the chain above, where products and sums
+// fuse: 337 -> 302 us for two views of 801x533 (half of the VALU issue slots; the lists are
+// short and end one by one).
 template <int TW, int TH>
 __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict__ ranges,
                                                          const uint32_t *__restrict__ work_order,
@@ -1068,11 +1087,12 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
                                                          float *__restrict__ record_grads,
                                                          unsigned int *__restrict__ queue)
 {
+    // (no decision below but M::test's, which is written out)
+#pragma clang fp contract(fast)
     using M = ExactMipModel;
     constexpr int PPL = slot_layout(TW, TH).slots;
     constexpr float kLn2 = 0.69314718055994531f;
-    __shared__ float4 s_rec[4][64][M::kStaged];
-    __shared__ uint32_t s_id[4][64];
+    __shared__ float4 s_rec[4][64][M::kStaged + 1];  // the staged record and, after it, its id
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
     unsigned int *const head = queue + q * kQueueStride;
@@ -1117,22 +1137,27 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, d, 64));
         const uint2 rg = ranges[tile];
-        maxlast = min(maxlast, (int)(rg.y - rg.x));
+        maxlast = __builtin_amdgcn_readfirstlane(min(maxlast, (int)(rg.y - rg.x)));  // the walk is uniform
+        prioritise((uint32_t)maxlast);
         for (int hi = maxlast; hi > 0; hi -= 64) {
-            const int lo = hi > 64 ? hi - 64 : 0;
+            const int lo = __builtin_amdgcn_readfirstlane(hi > 64 ? hi - 64 : 0);
             const int nb = hi - lo;
             if (lane < nb) {
                 const uint32_t v = inst_ids[rg.x + lo + lane];
                 const uint32_t id = v & kIdMask;
-                s_id[wave][lane] = id < P.n_records ? id : 0xffffffffu;
+                s_rec[wave][lane][M::kStaged].x = __uint_as_float(id < P.n_records ? id : 0xffffffffu);
                 float4 r[M::kRaw];
                 M::fetch(r, records, v, P.n_records, PPL <= 4);
                 M::stage(s_rec[wave][lane], r, x0, y0, P.log2_pmin);
             }
             lds_wave_sync();
-            for (int jj = nb - 1; jj >= 0; --jj) {
-                const int j = lo + jj;
-                const XRec R = M::load(s_rec[wave][jj]);
+            uint32_t at = (uint32_t)((wave * 64 + nb) * sizeof(s_rec[0][0]));  // (see k_blend_bwd)
+            for (int j = hi - 1; j >= lo; --j) {
+                at -= (uint32_t)sizeof(s_rec[0][0]);
+                asm("" : "+v"(at));
+                const float4 *const rp = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_rec) + at);
+                const XRec R = M::load(rp);
+                const uint32_t rid = __builtin_amdgcn_readfirstlane(__float_as_uint(rp[M::kStaged].x));
                 const RowSpan span = row_span(R.rows, ty * TH);
                 const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
                 float acc[25];
@@ -1203,7 +1228,6 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
                     acc[21] += g * kLn2;
                 }
                 if (!wave_hit) continue;
-                const uint32_t rid = s_id[wave][jj];
                 const int c = wave_sum16_index(lane);
                 const float lo16[16] = {acc[0], acc[1], acc[2], acc[3], acc[4], acc[5], acc[6], acc[7],
                                         acc[8], acc[9], acc[10], acc[11], acc[12], acc[13], acc[14], acc[15]};
@@ -1211,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
                 const float hi16[16] = {acc[16], acc[17], acc[18], acc[19], acc[20], acc[21], acc[22], acc[23],
                                         acc[24], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 const float s_hi = wave_sum16(hi16, lane);
-                if ((lane & 3) == 0 && rid != 0xffffffffu) {
+                if (rid != 0xffffffffu && (lane & 3) == 0) {
                     float *dst = record_grads + (size_t)rid * kGradFloatsExactMip;
                     atomicAdd(dst + c, s_lo);
                     if (c < 9) atomicAdd(dst + 16 + c, s_hi);
