@@ -379,6 +379,7 @@ DevOptions dev_options(const rgs_options &o)
 {
     DevOptions d{};
     d.p_min = o.p_min;
+    d.log2_pmin = std::log2(o.p_min);
     d.alpha_max = o.alpha_max;
     d.t_eps = o.t_eps;
     d.near_z = o.near_z;

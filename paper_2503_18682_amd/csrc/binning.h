@@ -64,6 +64,15 @@ __device__ inline double fast_rsqrt(double x)
     return y;
 }
 
+// 1 / x for x well inside the double range, to the same accuracy
+__device__ inline double fast_rcp(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return y;
+}
+
 __device__ inline ConicFrame conic_frame(const Conic &C)
 {
 #pragma clang fp contract(off)

@@ -28,7 +28,7 @@ struct DevView {
 };
 
 struct DevOptions {
-    double p_min, alpha_max, t_eps, near_z, mip_sigma2_px;
+    double p_min, log2_pmin, alpha_max, t_eps, near_z, mip_sigma2_px;
     int32_t mip;
     int32_t tile_w, tile_h;
     int32_t tile_wshift, tile_hshift;  // log2 of the tile shape (powers of two)

@@ -6,8 +6,14 @@
 // parameters (236 B per Gaussian at SH degree 3) are read from HBM once per
 // batch with coalesced structure-of-arrays loads.  Everything up to the tile
 // rectangle and the depth key is evaluated in double precision (full rate on
-// CDNA) with FMA contraction disabled, so the integer decisions (culls, tile
-// rectangles, keys) are those of an exact evaluation up to double rounding.
+// CDNA), so the integer decisions (culls, tile rectangles, keys) are those of
+// an exact evaluation up to double rounding.  The camera-frame centre, and with it the
+// near cull and the depth key, is taken without contraction; the geometry after it fuses
+// products and sums, and takes reciprocals and inverse roots as the hardware
+// estimate with two Newton steps.  16 views of 6M Gaussians 3.05 -> 2.83 ms, 8 views of 3M with
+// MIP 1280 -> 1224 us, one of 500k 39.6 -> 36.8 us; what is left is the writes
+// (24 B per Gaussian-view, 128 B more per kept one) and, with many
+// views, waves in which only some lanes are kept.
 #include <hip/hip_fp16.h>
 
 #include "binning.h"
@@ -66,7 +72,7 @@ struct Centre {
 __device__ inline Centre projected_centre(const double mu[3], const DevView &V)
 {
     Centre c;
-    const double k0 = 1.0 / mu[2];
+    const double k0 = fast_rcp(mu[2]);
     c.u = V.fx * mu[0] * k0 + V.cx;
     c.v = V.fy * mu[1] * k0 + V.cy;
     c.u_hi = (float)c.u;
@@ -80,6 +86,12 @@ __device__ inline Centre projected_centre(const double mu[3], const DevView &V)
 // Kernel variants by divergence and MIP mode, so that each carries only its
 // own code (fewer registers and instructions in the common ray-based one).
 enum PrepMode { kPrepRay = 0, kPrepMipApprox = 1, kPrepMipExact = 2, kPrepGS = 3 };
+
+// log2 of the opacity whose support cut-off is kappa = 2 ln(o / p_min)
+__device__ __forceinline__ float log2_opacity(double kappa, const DevOptions &opt)
+{
+    return (float)(opt.log2_pmin + kappa * 0.72134752044448170368);  // 1 / (2 ln 2)
+}
 
 // View-dependent colour, max(0, SH(direction camera centre -> mean) + 1/2),
 // in two steps.  sh_load keeps Gaussian i's coefficients in the block's LDS
@@ -182,7 +194,9 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
     // support cut-off (eq. 3) and the record's log2 opacity; the MIP transform
     // changes the opacity per view and recomputes them
     const double kappa_o = -2.0 * log(opt.p_min / o);
-    const float log2o_o = (float)log2(o);
+    const float log2o_o = log2_opacity(kappa_o, opt);
+
+    const double root_kappa_o = sqrt(kappa_o);
 
     uint32_t top_key = 0u;  // largest depth key of this thread's kept views
     for (int v = 0; v < n_views; ++v) {
@@ -208,6 +222,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
             }
         }
         do {
+#pragma clang fp contract(fast)
             if (!ok || !(mu[2] > opt.near_z)) break;
             double Rp[9];  // R_p = W_rot R
             for (int r = 0; r < 3; ++r)
@@ -319,26 +334,22 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
                 // Approximate MIP (Sec. 5, eq. 17): add sigma^2 |mu|^2 to every
                 // variance (pixel-invariant tau = |mu|) and scale the opacity by
                 // sqrt(|Sigma| c^2 / (|Sigma^| c^^2)).
-                const double tb = sqrt(mu[0] * mu[0] + mu[1] * mu[1] + mu[2] * mu[2]);
+                const double tb2 = mu[0] * mu[0] + mu[1] * mu[1] + mu[2] * mu[2];
                 const double sig2 = opt.mip_sigma2_px / (V.fx * V.fy);
-                double det = 1.0, deth = 1.0, c2p = 0.0, c2h = 0.0, sh2[3], ish2[3];
+                double det = 1.0, deth = 1.0, c2p = 0.0, c2h = 0.0;
                 for (int k = 0; k < 3; ++k) {
-                    const double s2 = sv[k] * sv[k];
-                    sh2[k] = s2 + sig2 * tb * tb;
-                    ish2[k] = 1.0 / sh2[k];
+                    const double s2 = sv[k] * sv[k], sh2 = s2 + sig2 * tb2;
                     det *= s2;
-                    deth *= sh2[k];
+                    deth *= sh2;
                     c2p += ml[k] * ml[k] * (isv[k] * isv[k]);
-                    c2h += ml[k] * ml[k] * ish2[k];
+                    isv[k] = fast_rsqrt(sh2);
+                    sv[k] = sh2 * isv[k];
+                    c2h += ml[k] * ml[k] * (isv[k] * isv[k]);
                 }
                 // mip = 3: the widening without the modulation (dilation only)
                 const double ov = opt.mip == 3 ? o : o * sqrt(det * c2p / (deth * c2h));
-                for (int k = 0; k < 3; ++k) {
-                    sv[k] = sqrt(sh2[k]);
-                    isv[k] = sv[k] * ish2[k];
-                }
                 kappa = -2.0 * log(opt.p_min / ov);
-                log2o = (float)log2(ov);
+                log2o = log2_opacity(kappa, opt);
             }
             // support cut-off (eq. 3) and the camera-inside skip (eq. 6)
             if (!(kappa > 0.0)) break;
@@ -347,16 +358,15 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
             if (!(c2 > kappa)) break;
 
             // Sec. 4.1: whitened unit centre, b, R_{mu^ <- v} (App. A.1)
-            const double c = sqrt(c2);
-            const double ic = 1.0 / c, ic2 = 1.0 / c2;
+            const double ic = c2 < 1e300 ? fast_rsqrt(c2) : 0.0, ic2 = ic * ic;
             const double muh[3] = {mw[0] * ic, mw[1] * ic, mw[2] * ic};
-            const double b = sqrt(1.0 - kappa * ic2);
+            const double b2 = 1.0 - kappa * ic2;
             double Rv[9];
             {
                 const double sgn = muh[2] >= 0.0 ? 1.0 : -1.0;  // align to v or to -v
                 const double a3[3] = {muh[0], muh[1], muh[2] + sgn};
                 const double a2 = a3[0] * a3[0] + a3[1] * a3[1] + a3[2] * a3[2];
-                const double t2 = 2.0 / a2;
+                const double t2 = 2.0 * fast_rcp(a2);
                 for (int r = 0; r < 3; ++r)
                     for (int cc = 0; cc < 3; ++cc) Rv[3 * r + cc] = t2 * a3[r] * a3[cc] - (r == cc ? 1.0 : 0.0);
                 if (sgn < 0.0)  // right-multiply by P = diag(-1, 1, -1)
@@ -379,20 +389,21 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
             }
             // closed-form top eigenvector u1 of the 2x2 B; u0 = u1 turned by +90 degrees
             const double mean = 0.5 * (Ba + Bd);
-            const double rad = sqrt(0.25 * (Ba - Bd) * (Ba - Bd) + Bh * Bh);
+            const double rad2 = 0.25 * (Ba - Bd) * (Ba - Bd) + Bh * Bh;
+            const double rad = rad2 > 1e-290 ? rad2 * fast_rsqrt(rad2) : 0.0;
             const double lmax = mean + rad;
             double u1x = 1.0, u1y = 0.0;
             if (!(2.0 * rad <= 1e-6 * lmax)) {
                 const double v1x = Bh, v1y = lmax - Ba, v2x = lmax - Bd, v2y = Bh;
-                const double n1 = sqrt(v1x * v1x + v1y * v1y), n2 = sqrt(v2x * v2x + v2y * v2y);
+                const double n1 = v1x * v1x + v1y * v1y, n2 = v2x * v2x + v2y * v2y;
                 const bool first = n1 >= n2;
-                const double inv = 1.0 / (first ? n1 : n2);
+                const double inv = fast_rsqrt(first ? n1 : n2);
                 u1x = (first ? v1x : v2x) * inv;
                 u1y = (first ? v1y : v2y) * inv;
             }
             const double u0x = -u1y, u0y = u1x;
             // quad vertices V_k = mu + Q_{0:2} U (sqrt(kappa)/b) O_k (eq. 15)
-            const double hs = sqrt(kappa) / b;
+            const double hs = (MODE == kPrepRay ? root_kappa_o : sqrt(kappa)) * (b2 > 1e-300 ? fast_rsqrt(b2) : INFINITY);
             double QU[6];
             for (int r = 0; r < 3; ++r) {
                 QU[2 * r] = Q[3 * r] * u0x + Q[3 * r + 1] * u0y;
@@ -424,7 +435,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
                 const double Vx = QU[0] * z0 + QU[1] * z1 + mu[0];
                 const double Vy = QU[2] * z0 + QU[3] * z1 + mu[1];
                 const double Vz = QU[4] * z0 + QU[5] * z1 + mu[2];
-                const double iz = 1.0 / Vz;
+                const double iz = fast_rcp(Vz);
                 const double u = V.fx * Vx * iz + V.cx;
                 const double vv = V.fy * Vy * iz + V.cy;
                 umin = fmin(umin, u);
@@ -449,7 +460,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
 
             // ---- raster record (float32) ----
             const Centre pc = projected_centre(mu, V);
-            const double k0 = 1.0 / mu[2];
+            const double k0 = fast_rcp(mu[2]);
             const double u_c = pc.u, v_c = pc.v;
             // A2 = (S^-1 R_p^T)[:, 0:2] diag(1/fx, 1/fy): a pixel offset delta moves
             // the whitened ray direction by A2 delta.
@@ -472,9 +483,9 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
                 const double M00 = G[0][0] * G[0][0] + G[1][0] * G[1][0];
                 const double M01 = G[0][0] * G[0][1] + G[1][0] * G[1][1];
                 const double M11 = G[0][1] * G[0][1] + G[1][1] * G[1][1];
-                C.P00 = b * b * M00 - kappa * gx * gx;
-                C.P01 = b * b * M01 - kappa * gx * gy;
-                C.P11 = b * b * M11 - kappa * gy * gy;
+                C.P00 = b2 * M00 - kappa * gx * gx;
+                C.P01 = b2 * M01 - kappa * gx * gy;
+                C.P11 = b2 * M11 - kappa * gy * gy;
                 C.h0 = kappa * k0 * gx;
                 C.h1 = kappa * k0 * gy;
                 C.f0 = kappa * k0 * k0;
