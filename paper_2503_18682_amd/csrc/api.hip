@@ -533,18 +533,27 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     const float near_f = (float)opts.near_z;
     uint32_t near_key;
     std::memcpy(&near_key, &near_f, 4);
-    const RadixRange range{near_key, part_max, (int)((g.n + 63) / 64), reinterpret_cast<uint32_t *>(counters + 6)};
-    // its scratch is what the emission clears or the binning scan fills later
-    uint32_t *const dscratch = radix_scratch_words(NV, 32, true) <= sched_words() ? sched : at<uint32_t>(ws, L.sorted_boxes);
-    RGS_HIP(ctx, radix_sort(keys_in, ord_in, keys_alt, ord_alt, NV, nullptr, 32, &range, true, 0xffffffffu, kept,
-                            dscratch, stream, true));
-    tm.mark(ST_DSORT);
     const uint32_t *order = at<uint32_t>(ws, L.order_a);
     uint32_t *offsets = at<uint32_t>(ws, L.offsets);
     uint32_t *bin_scratch = at<uint32_t>(ws, L.bin_scratch);
     uint2 *sorted_boxes = at<uint2>(ws, L.sorted_boxes);
-    RGS_HIP(ctx, binning_scan(at<uint32_t>(ws, L.keys_a), bin_boxes, order, NV, kept, s.w, s.h, L.capacity, offsets,
-                              bin_scratch, sorted_boxes, at<unsigned long long>(ws, L.block_sums), counters, stream));
+    if (order_small(NV)) {
+        RGS_HIP(ctx, launch_order_small(keys_in, bin_boxes, NV, near_key, s.w, s.h, L.capacity,
+                                        at<uint32_t>(ws, L.keys_a), at<uint32_t>(ws, L.order_a), offsets, bin_scratch,
+                                        sorted_boxes, counters, stream));
+        tm.mark(ST_DSORT);
+    } else {
+        const RadixRange range{near_key, part_max, (int)((g.n + 63) / 64), reinterpret_cast<uint32_t *>(counters + 6)};
+        // its scratch is what the emission clears or the binning scan fills later
+        uint32_t *const dscratch =
+            radix_scratch_words(NV, 32, true) <= sched_words() ? sched : at<uint32_t>(ws, L.sorted_boxes);
+        RGS_HIP(ctx, radix_sort(keys_in, ord_in, keys_alt, ord_alt, NV, nullptr, 32, &range, true, 0xffffffffu, kept,
+                                dscratch, stream, true));
+        tm.mark(ST_DSORT);
+        RGS_HIP(ctx, binning_scan(at<uint32_t>(ws, L.keys_a), bin_boxes, order, NV, kept, s.w, s.h, L.capacity, offsets,
+                                  bin_scratch, sorted_boxes, at<unsigned long long>(ws, L.block_sums), counters,
+                                  stream));
+    }
     tm.mark(ST_SCAN);
     for (const bool emit : {true, false}) {
         RGS_HIP(ctx, emit_and_sort(order, offsets, bin_scratch, sorted_boxes, conics, views, g.n, counters, L.capacity,

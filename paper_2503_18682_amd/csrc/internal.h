@@ -144,6 +144,14 @@ hipError_t binning_scan(const uint32_t *keys, const uint2 *boxes, const uint32_t
                         uint32_t *bin_scratch, uint2 *sorted_boxes, unsigned long long *block_sums,
                         int64_t *counters, hipStream_t stream);
 size_t scan_block_entries(int64_t n);
+
+// Depth order and binning scan of few Gaussian-views (order_small(n)) in one
+// launch: radix_sort's kept keys and ids in keys_out and order, binning_scan's outputs,
+// counters[4] (kept) and counters[6] (largest key).
+bool order_small(int64_t n);
+hipError_t launch_order_small(const uint32_t *keys, const uint2 *boxes, int64_t n, uint32_t near_key, int tile_w,
+                              int tile_h, int64_t capacity, uint32_t *keys_out, uint32_t *order, uint32_t *offsets,
+                              uint32_t *bin_scratch, uint2 *sorted_boxes, int64_t *counters, hipStream_t stream);
 size_t bin_scratch_words(int64_t capacity, int tile_bits);
 
 // With `emit`: the listed instances (tile id, id | slot bits) of the box

@@ -732,6 +732,181 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const in
     }
 }
 
+// Depth order and binning scan of at most kSmallViews Gaussian-views by one
+// workgroup, in place of six sort and two scan launches of 4 to 8 us each.  A least
+// significant digit sort in LDS: each wave ranks its ROUNDS * 64 items in order
+// by the lanes of equal digit, and the digits are the bits between the
+// near plane's key and the largest one, spread over as few passes as 8 bits a pass allow.
+// Then the boxes are gathered and both counts scanned, as k_scan_reduce and k_scan_apply do.
+// Whole frames at 128x96 by the number of Gaussians, general path -> this: 64 73 -> 48
+// us, 1000 95 -> 73 us, 2000 119 -> 104 us, 4000 148 -> 136 us; 8000 155 -> 165 us, so the line is at 4096.
+// Bound by the latency of a pass (about 2.5 us).
+constexpr int kSmallDigitBits = 8;
+constexpr int64_t kSmallViews = 4096;
+
+template <int THREADS, int ROUNDS>
+__global__ __launch_bounds__(THREADS) void k_order_small(
+    const uint32_t *__restrict__ keys, const uint2 *__restrict__ boxes, int n, uint32_t near_key, int wshift,
+    int hshift, int64_t capacity, int tile_shift, uint32_t *__restrict__ keys_out, uint32_t *__restrict__ order,
+    uint32_t *__restrict__ offsets, uint2 *__restrict__ steps, uint2 *__restrict__ sorted_boxes,
+    int64_t *__restrict__ counters)
+{
+    constexpr int kBins = 1 << kSmallDigitBits, WAVES = THREADS / 64;
+    static_assert(THREADS >= kBins, "a thread per digit");
+    __shared__ uint32_t s_key[ROUNDS * THREADS];
+    __shared__ uint16_t s_id[ROUNDS * THREADS];
+    __shared__ uint16_t s_cnt[WAVES][kBins];
+    __shared__ uint32_t s_wave[WAVES];
+    __shared__ unsigned long long s_sum[2][WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int at0 = wave * ROUNDS * 64 + lane;  // item r of the thread is at0 + 64 r
+    uint32_t key[ROUNDS], id[ROUNDS];
+    uint32_t top = 0u;  // largest kept key
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        id[r] = (uint32_t)(at0 + 64 * r);
+        key[r] = keys[min(at0 + 64 * r, n - 1)];
+        if (at0 + 64 * r >= n) key[r] = 0xffffffffu;
+        if (key[r] != 0xffffffffu) top = max(top, key[r]);
+    }
+    if (tid == 0) s_wave[0] = 0u;
+    __syncthreads();
+    if (top) atomicMax(&s_wave[0], top);
+    __syncthreads();
+    top = s_wave[0];
+    const int bits = top > near_key ? 32 - __clz((int)(top - near_key)) : 1;
+    const int passes = (bits + kSmallDigitBits - 1) / kSmallDigitBits, width = (bits + passes - 1) / passes;
+    const uint32_t mask = (1u << width) - 1u;
+    int count = n;  // items, after the first pass the kept ones
+    for (int p = 0; p < passes; ++p) {
+        __syncthreads();
+        for (int i = tid; i < WAVES * kBins / 2; i += THREADS)
+            reinterpret_cast<uint32_t *>(s_cnt)[i] = 0u;
+        __syncthreads();
+        const int shift = p * width;
+        uint32_t digit[ROUNDS], rank[ROUNDS];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const bool valid = p == 0 ? key[r] != 0xffffffffu : at0 + 64 * r < count;
+            const uint32_t d = ((key[r] - near_key) >> shift) & mask;
+            uint64_t same = __ballot(valid);  // lanes of the same digit
+            for (int b = 0; b < width; ++b) {
+                const bool one = (d >> b) & 1u;
+                const uint64_t m = __ballot(one);
+                same &= one ? m : ~m;
+            }
+            const uint32_t below =
+                __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+            const uint32_t prior = s_cnt[wave][d];
+            wave_sync();
+            if (valid && below == 0) s_cnt[wave][d] = (uint16_t)(prior + (uint32_t)__popcll(same));
+            wave_sync();
+            digit[r] = d;
+            rank[r] = valid ? prior + below : 0xffffffffu;
+        }
+        __syncthreads();
+        uint32_t before[WAVES] = {}, run = 0;
+        if (tid <= (int)mask)
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                before[w] = run;
+                run += s_cnt[w][tid];
+            }
+        uint32_t tot;
+        const uint32_t start = block_inclusive_scan<WAVES>(run, s_wave, &tot) - run;
+        if (tid <= (int)mask)
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) s_cnt[w][tid] = (uint16_t)(start + before[w]);
+        count = (int)tot;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if (rank[r] != 0xffffffffu) {
+                const uint32_t to = s_cnt[wave][digit[r]] + rank[r];
+                s_key[to] = key[r];
+                s_id[to] = (uint16_t)id[r];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+            if (at0 + 64 * r < count) {
+                key[r] = s_key[at0 + 64 * r];
+                id[r] = s_id[at0 + 64 * r];
+            }
+    }
+    // thread t scans positions t ROUNDS .. t ROUNDS + ROUNDS - 1
+    uint32_t c[ROUNDS], rows[ROUNDS];
+    uint2 box[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int at = tid * ROUNDS + r;
+        box[r] = make_uint2(0u, 0u);
+        if (at < count) {
+            id[r] = s_id[at];
+            box[r] = boxes[id[r]];
+            keys_out[at] = s_key[at];
+            order[at] = id[r];
+        }
+    }
+    unsigned long long lt = 0, lr = 0;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int at = tid * ROUNDS + r;
+        const PixelBox pb = unpack_box(box[r]);
+        rows[r] = at < count ? (uint32_t)((pb.y1 >> hshift) - (pb.y0 >> hshift) + 1) : 0u;
+        c[r] = rows[r] * (uint32_t)((pb.x1 >> wshift) - (pb.x0 >> wshift) + 1);
+        if (at < count) sorted_boxes[at] = box[r];
+        lt += c[r];
+        lr += rows[r];
+    }
+    unsigned long long it = lt, ir = lr;  // inclusive over the wave
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long a = __shfl_up(it, d, 64), b = __shfl_up(ir, d, 64);
+        if (lane >= d) {
+            it += a;
+            ir += b;
+        }
+    }
+    if (lane == 63) {
+        s_sum[0][wave] = it;
+        s_sum[1][wave] = ir;
+    }
+    __syncthreads();
+    unsigned long long pre[2] = {0, 0}, all[2] = {0, 0};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (w < wave) pre[q] += s_sum[q][w];
+            all[q] += s_sum[q][w];
+        }
+    if (tid == 0) {
+        counters[0] = (int64_t)all[0];
+        counters[2] = (int64_t)all[1];
+        counters[4] = count;
+        *reinterpret_cast<uint32_t *>(counters + 6) = top;
+    }
+    const int64_t totals[3] = {(int64_t)all[0], 0, (int64_t)all[1]};
+    const EmitPlan P = emit_plan(totals, capacity, tile_shift);
+    const int sshift = __builtin_ctz((unsigned)P.step);
+    const bool fits = all[0] <= (unsigned long long)capacity;
+    unsigned long long rt = pre[0] + it - lt;
+    uint32_t rr = (uint32_t)(pre[1] + ir - lr);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int at = tid * ROUNDS + r;
+        if (at < count) {
+            offsets[at] = rt > 0xffffffffull ? 0xffffffffu : (uint32_t)rt;
+            if (fits && c[r])
+                for (uint32_t m = (rr + (uint32_t)P.step - 1u) >> sshift; m << sshift < rr + rows[r]; ++m)
+                    steps[m] = make_uint2((uint32_t)at, (m << sshift) - rr);
+        }
+        rt += c[r];
+        rr += rows[r];
+    }
+}
+
 // ---------------------------------------------------------------- emission
 // The listed tiles of the depth-sorted Gaussian-views' boxes, in three levels,
 // each spread over the lanes of a wave:
@@ -1077,6 +1252,64 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     }
 }
 
+// The same for at most kSmallTiles tiles, in one launch of one workgroup, with
+// the ranges too (`find_ranges`) where the capacity is small: 128 tiles of a frame of 1000 Gaussians
+// 4 us instead of 8, 560 tiles with a launch for the ranges 6.5 instead of 9.
+constexpr int kSmallTiles = 1024;
+constexpr int64_t kSmallInstances = int64_t(1) << 15;
+
+__global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint32_t *__restrict__ inst_tiles,
+                                                             const int64_t *__restrict__ listed, int64_t capacity,
+                                                             int total_tiles, uint32_t split_min, uint32_t waves,
+                                                             bool find_ranges, uint2 *__restrict__ ranges,
+                                                             uint32_t *__restrict__ n_items,
+                                                             uint32_t *__restrict__ work_order)
+{
+    __shared__ uint2 s_range[kSmallTiles];
+    __shared__ uint32_t base[kSchedBuckets];
+    __shared__ uint32_t smem[kSmallTiles / 64];
+    const int t = threadIdx.x;
+    if (t < kSchedBuckets) base[t] = 0u;
+    uint2 r = make_uint2(0u, 0u);
+    if (find_ranges) {
+        const int n = (int)clamp_count(listed, capacity);
+        s_range[t] = r;
+        __syncthreads();
+        for (int i = t; i < n; i += kSmallTiles) {
+            const uint32_t tile = inst_tiles[i];
+            const uint32_t before = i > 0 ? inst_tiles[i - 1] : 0xffffffffu;
+            const uint32_t after = i + 1 < n ? inst_tiles[i + 1] : 0xffffffffu;
+            if (tile >= (uint32_t)total_tiles) continue;
+            if (before != tile) s_range[tile].x = (uint32_t)i;
+            if (after != tile) s_range[tile].y = (uint32_t)i + 1u;
+        }
+        __syncthreads();
+        r = s_range[t];
+        if (t < total_tiles) ranges[t] = r;
+    } else {
+        if (t < total_tiles) r = ranges[t];
+        __syncthreads();
+    }
+    const uint32_t split_len = split_length(listed, split_min, waves);
+    const uint32_t len = r.y - r.x, parts = t < total_tiles ? work_parts(len, split_len) : 0u;
+    const uint32_t b = work_bucket(len, parts);
+    const uint32_t rank = parts ? atomicAdd(&base[b], parts) : 0u;
+    __syncthreads();
+    // buckets in decreasing order, as in k_sched_scatter
+    const uint32_t hb = t < kSchedBuckets ? base[kSchedBuckets - 1 - t] : 0u;
+    uint32_t tot;
+    const uint32_t before = block_inclusive_scan<kSmallTiles / 64>(hb, smem, &tot) - hb;
+    if (t < kSchedBuckets) base[kSchedBuckets - 1 - t] = before;
+    if (t == 0) n_items[0] = tot;
+    if (t == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
+    __syncthreads();
+    if (parts == 1u) work_order[base[b] + rank] = (uint32_t)t << 2;
+    if (parts == 2u) {
+        work_order[base[b] + rank] = (uint32_t)t << 2 | 1u;
+        work_order[base[b] + rank + 1] = (uint32_t)t << 2 | 2u;
+    }
+}
+
 }  // namespace
 
 int radix_passes(int bits) { return bits <= 0 ? 0 : (bits + kMaxDigitBits - 1) / kMaxDigitBits; }
@@ -1236,6 +1469,28 @@ hipError_t binning_scan(const uint32_t *keys, const uint2 *boxes, const uint32_t
     return hipGetLastError();
 }
 
+bool order_small(int64_t n) { return n > 0 && n <= kSmallViews; }
+
+hipError_t launch_order_small(const uint32_t *keys, const uint2 *boxes, int64_t n, uint32_t near_key, int tile_w,
+                              int tile_h, int64_t capacity, uint32_t *keys_out, uint32_t *order, uint32_t *offsets,
+                              uint32_t *bin_scratch, uint2 *sorted_boxes, int64_t *counters, hipStream_t stream)
+{
+#define RGS_SMALL(THREADS, ROUNDS)                                                                                   \
+    k_order_small<THREADS, ROUNDS><<<1, THREADS, 0, stream>>>(                                                       \
+        keys, boxes, (int)n, near_key, __builtin_ctz((unsigned)tile_w), __builtin_ctz((unsigned)tile_h), capacity,   \
+        tile_shift(capacity), keys_out, order, offsets, reinterpret_cast<uint2 *>(bin_scratch), sorted_boxes, counters)
+    if (n <= 256)
+        RGS_SMALL(256, 1);
+    else if (n <= 1024)
+        RGS_SMALL(512, 2);
+    else if (n <= 2048)
+        RGS_SMALL(1024, 2);
+    else
+        RGS_SMALL(1024, 4);
+#undef RGS_SMALL
+    return hipGetLastError();
+}
+
 size_t bin_scratch_words(int64_t capacity, int tile_bits)
 {
     return step_words(capacity) + seg_words(capacity) + radix_scratch_words(capacity, tile_bits, false);
@@ -1310,9 +1565,15 @@ hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counter
     // the ranges, queue heads and scheduling histograms were cleared by k_emit
     // a grid-stride loop over the listed instances (a grid sized for the whole
     // capacity would mostly launch idle workgroups)
-    if (capacity > 0) {
+    const bool small = total_tiles <= kSmallTiles, find = small && capacity <= kSmallInstances;
+    if (capacity > 0 && !find) {
         const unsigned grid = (unsigned)std::min<int64_t>((capacity + 4 * kThreads - 1) / (4 * kThreads), kRangeBlocks);
         k_tile_ranges<<<grid, kThreads, 0, stream>>>(inst_tiles, counters, capacity, total_tiles, ranges);
+    }
+    if (small) {
+        k_sched_small<<<1, kSmallTiles, 0, stream>>>(inst_tiles, counters, capacity, (int)total_tiles, split_min, waves,
+                                                     find, ranges, sched + sched_item_count(), work_order);
+        return hipGetLastError();
     }
     const unsigned nb = (unsigned)((total_tiles + kThreads - 1) / kThreads);
     uint32_t *hist = sched + 2 * sched_backward_heads(), *cursor = hist + kSchedBuckets;

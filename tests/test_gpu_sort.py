@@ -43,7 +43,10 @@ def _scene(n, depths, seed):
 
 CASES = [(1, "linear", 64, 48, 1), (2047, "same", 320, 240, 1), (2048, "wide", 8, 8, 1), (2049, "linear", 640, 480, 1),
          (4097, "wide", 1000, 900, 2), (40000, "linear", 5000, 4300, 1), ((1 << 20) - 1, "linear", 640, 480, 1),
-         ((1 << 20) + 1, "wide", 640, 480, 1), (700_000, "wide", 1024, 1024, 3)]
+         ((1 << 20) + 1, "wide", 640, 480, 1), (700_000, "wide", 1024, 1024, 3),
+         # one workgroup for the depth order (up to 4096 Gaussian-views), and for the tile order (up to 1024 tiles)
+         (1024, "linear", 256, 256, 1), (1025, "wide", 264, 256, 1), (4096, "same", 256, 256, 1),
+         (2048, "wide", 128, 128, 2), (4097, "linear", 100, 75, 1), (256, "wide", 100, 75, 1), (257, "wide", 64, 48, 2)]
 
 
 @pytest.mark.parametrize("n,depths,w,h,views", CASES)
