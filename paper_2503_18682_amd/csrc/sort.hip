@@ -297,7 +297,11 @@ __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restri
 // scanned, with row_total.
 // SEG: the items are the emission's: those of block b are the
 // seg[b].y from seg[b].x on, any number of them, taken a tile at a time; the
-// number of items sorted goes to *kept_out.
+// number of items sorted goes to *kept_out.  Where a window of 16 blocks is less than half
+// full, neighbouring blocks whose items fit one tile are taken by one workgroup: a 5120x3840
+// frame of needles lists a tenth of its box instances, and its pass took 286 us
+// with a workgroup for each block and takes 210 us; a frame that lists three quarters
+// would lose (59 -> 63 us).
 template <int THREADS, int ITEMS, bool SELF, bool SEG>
 __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
@@ -342,19 +346,71 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     const int64_t n = clamp_count(n_dev, n_max);
     const Digit D = pass_digit(pass);
     const int nb = SEG ? emit_plan(n_dev, n_max, __builtin_ctz(TILE)).blocks : (int)((n + TILE - 1) / TILE);
-    const int block = SELF ? (int)blockIdx.x : xcd_block(nb);
+    int block = SELF ? (int)blockIdx.x : xcd_block(nb);
     if (block >= nb) {  // uniform per block
         if (kept_out && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
         return;
     }
     int64_t base = (int64_t)block * TILE;
     int todo = (int)min(n - base, (int64_t)TILE);  // items of the block
+    // (SEG) the workgroup's segments, from `block` on, `segs` of them: lane s
+    // holds segment s of the window of kWindow that `block` lies in
+    constexpr int kWindow = 16;
+    uint2 part = make_uint2(0u, 0u);
+    int seg0 = 0, segs = 1;
     if constexpr (SEG) {
-        const uint2 part = seg[block];
-        base = part.x;
-        todo = (int)part.y;
+        const int first = block & ~(kWindow - 1), here = min(nb - first, kWindow);
+        if (lane < here) part = seg[first + lane];
+        seg0 = block - first;
+        todo = (int)__builtin_amdgcn_readlane(part.y, seg0);
+        const int all = (int)__builtin_amdgcn_readlane(wave_inclusive_scan(part.y), kWindow - 1);
+        if (2 * (int64_t)all <= (int64_t)here * TILE) {
+            int group = -1, held = 0;
+            const int want = seg0;
+            segs = todo = 0;
+            for (int s = 0; s < here; ++s) {
+                const int c = (int)__builtin_amdgcn_readlane(part.y, s);
+                if (s == 0 || held + c > TILE) {
+                    ++group;
+                    held = 0;
+                }
+                held += c;
+                if (group == want) {
+                    if (segs == 0) seg0 = s;
+                    ++segs;
+                    todo = held;
+                }
+            }
+            if (segs == 0) return;  // uniform per block
+            block = first + seg0;
+        }
+        base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(part.x, seg0);
     }
-    if constexpr (!kEarly) load(base, min(todo, TILE));
+    // items [from, from + TILE) of the workgroup's
+    auto load_items = [&](int from) {
+        const int left = min(todo - from, TILE);
+        if (!SEG || segs == 1) {
+            load(base + from, left);
+            return;
+        }
+        uint32_t src[ITEMS];
+        uint32_t start = 0;  // items before the segment
+        for (int s = seg0; s < seg0 + segs; ++s) {
+            const uint32_t delta = (uint32_t)__builtin_amdgcn_readlane(part.x, s) - start;
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) {
+                const uint32_t i = (uint32_t)(from + min(at0 + r * 64, max(left - 1, 0)));
+                if (s == seg0 || i >= start) src[r] = i + delta;
+            }
+            start += (uint32_t)__builtin_amdgcn_readlane(part.y, s);
+        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) key[r] = keys_in[src[r]];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) val[r] = vals_in[src[r]];
+    };
+    int from = 0;
+    if constexpr (!kEarly) load_items(0);
     const int bins = 1 << D.bits;
 
     // output position of each digit's first item of this block
@@ -417,7 +473,7 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     if (kept_out && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
     const uint32_t n32 = (uint32_t)n;
     for (;;) {
-        const int left = min(todo, TILE);
+        const int left = min(todo - from, TILE);
         __syncthreads();
         for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
         __syncthreads();
@@ -495,10 +551,9 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
                 }
             }
         }
-        todo -= TILE;
-        if (!SEG || todo <= 0) break;  // uniform per block
-        base += TILE;
-        load(base, min(todo, TILE));
+        from += TILE;
+        if (!SEG || from >= todo) break;  // uniform per block
+        load_items(from);
         // the digits' next positions: past this tile's items
         __syncthreads();
         for (int d = tid; d < bins; d += THREADS)

@@ -114,3 +114,36 @@ def test_emission_lists(r, kind, tile):
     bad = np.nonzero(sp["hazard"] != 0)[0]
     ok, keep = ~np.isin(got[0][1], bad), ~np.isin(ids, bad)
     assert np.array_equal(got[0][0][ok], tiles[keep]) and np.array_equal(got[0][1][ok], ids[keep])
+
+
+@pytest.mark.parametrize("tile", [(8, 16), (16, 8)])
+@pytest.mark.parametrize("n,size", [(40, 900), (600, 900), (2500, 1500)])
+def test_sparse_segments(r, n, size, tile):
+    """Thin diagonal needles: most box tiles are not listed, so the tile sort takes
+    many emission blocks (from one window's few to hundreds of windows) together."""
+    import oracle
+    import scenegen
+
+    say(f"case sparse n {n} size {size} {tile}")
+    sc = scenegen.tiny_scene(31, n, half_extent=0.8, log_scale_mean=-7.0, log_scale_std=0.2)
+    sc["log_scales"] = np.ascontiguousarray(sc["log_scales"])
+    sc["log_scales"][0] = -0.9  # one long axis
+    cam = scenegen.pinhole(scenegen.look_at((0.2, 0.1, -3.0)), size, size - 37, 60.0)
+    opts = scenegen.default_options(tile_w=tile[0], tile_h=tile[1])
+    g = {k: torch.from_numpy(np.ascontiguousarray(sc[k])).cuda() for k in
+         ("means", "log_scales", "quats", "opacity_logits", "sh")}
+    g["sh_degree"] = sc["sh_degree"]
+    _, (buf, ws) = r.render(g, [cam], opts, keep_workspace=True)
+    need = r.status(ws)[1]
+    for cap in (need, 2 * need + 77, (1 << 20) + need):
+        buf, ws = r.new_workspace(n, [cam], cap, 0, opts)
+        r.render_into(g, [cam], r.allocate_outputs([cam]), ws, opts)
+        assert r.status(ws) == (True, need)
+        lay = r.layout(n, [cam], cap, 0, opts)
+        got = instance_lists(buf, lay, with_bands=True)
+        assert len(got[0]) < 0.5 * need
+        sp = oracle.preprocess(sc, cam, opts)
+        tiles, _, ids = oracle.tile_lists(sp, cam, opts, 0)
+        bad = np.nonzero(sp["hazard"] != 0)[0]
+        ok, keep = ~np.isin(got[1], bad), ~np.isin(ids, bad)
+        assert np.array_equal(got[0][ok], tiles[keep]) and np.array_equal(got[1][ok], ids[keep])
