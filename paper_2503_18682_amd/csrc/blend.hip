@@ -517,19 +517,23 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
                     const float ta = T[k] * a;
                     const float Tn = T[k] - ta;
                     const bool stop = Tn < P.t_eps;
-                    const float wt = stop ? 0.0f : ta;
-                    C0[k] = __builtin_fmaf(wt, R.r, C0[k]);
-                    C1[k] = __builtin_fmaf(wt, R.g, C1[k]);
-                    C2[k] = __builtin_fmaf(wt, R.b, C2[k]);
-                    T[k] = stop ? T[k] : Tn;
+                    // (the weight's selection is left to the rare case: 2 to 5 %
+                    // of a kernel bound by VALU issue.  Branches for the other two, by lane
+                    // or by wave, cost a quarter more: copies where the paths join)
+                    float wt = ta;
                     if (__ballot(stop) != 0) {
                         // some pixel of the slot stops before this entry: it has
                         // consumed the entries before it, and it is done (a NaN
                         // row offset fails every later test)
+                        wt = stop ? 0.0f : ta;
                         last[k] = stop ? (int)(base - rg.x + j) : last[k];
                         pyr[k] = stop ? __builtin_nanf("") : pyr[k];
                         if (__ballot(pyr[k] == pyr[k]) == 0) live &= ~(1u << k);
                     }
+                    C0[k] = __builtin_fmaf(wt, R.r, C0[k]);
+                    C1[k] = __builtin_fmaf(wt, R.g, C1[k]);
+                    C2[k] = __builtin_fmaf(wt, R.b, C2[k]);
+                    T[k] = stop ? T[k] : Tn;
                 }
                 // leave the tile once no pixel is live
                 if (live == 0u) {
