@@ -176,6 +176,7 @@ __device__ __forceinline__ void put_test_form(float4 *dst, const float4 (&r)[4],
 // record above (with or without the approximate MIP of eq. 17, which only
 // changes the record's values); ExactMipModel evaluates the exact MIP weight.
 struct PlainModel {
+    static constexpr bool kPriority = true;
     static constexpr int kRaw = 4, kStaged = 4;
     using Rec = TRec;
     using F = Frag;
@@ -261,6 +262,7 @@ struct XFrag {
 };
 
 struct ExactMipModel {
+    static constexpr bool kPriority = false;  // 329 us with, 313 us without, for two views of 1032x1104
     static constexpr int kRaw = 7, kStaged = 8;
     using Rec = XRec;
     using F = XFrag;
@@ -454,7 +456,7 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
         // pixel centres relative to the block corner; NaN marks a pixel that
         // is outside the image, outside the work item, or done
         const uint2 rg = ranges[tile];
-        prioritise(rg.y - rg.x);
+        if (M::kPriority) prioritise(rg.y - rg.x);
         float T[PPL], C0[PPL], C1[PPL], C2[PPL], pxr[PPL], pyr[PPL], aux[PPL];
         int last[PPL];
         // pixel slots (64 pixels each) that hold a live pixel: a slot
@@ -1079,8 +1081,15 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 //   [11..13] Q1, [14..16] rho, [17..19] s'^2, [20] e, [21] log2o,
 //   [22..24] colour.
 // Most of its 200 instructions per slot are the chain above, where products and sums
-// fuse: 337 -> 302 us for two views of 801x533 (half of the VALU issue slots; the lists are
-// short and end one by one).
+// fuse: 337 -> 302 us for two views of 801x533.  Then the longest lists
+// bound it (1.7 waves per SIMD on average), so as long as the lists, which come in
+// decreasing length, are no shorter than kTeamBackwardLen and the average work of a wave, the four waves
+// of a workgroup share a list: each takes a quarter, first only for the product of
+// 1 / (1 - alpha) and the sum of the colour term over it, from which follows the
+// state that the others leave it.  The second test costs a fifth more: 302 -> 197 us;
+// with lists from 24 entries on 218 us, from 72 on 195 us, from 128 on 230 us.
+constexpr uint32_t kTeamBackwardLen = 64;
+
 template <int TW, int TH>
 __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict__ ranges,
                                                          const uint32_t *__restrict__ work_order,
@@ -1100,9 +1109,22 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
     unsigned int *const head = queue + q * kQueueStride;
+    // products of 1 / (1 - alpha) and sums of the colour term over a wave's share of a list
+    __shared__ float2 s_share[4][PPL][64];
+    __shared__ uint32_t s_ticket;
     const int64_t n_items = *n_items_p;
+    const uint32_t team_len = max(kTeamBackwardLen, n_items_p[2]);
+    bool team = true;  // the whole workgroup is on one item, as long as the lists are long
     for (;;) {
-        const int64_t slot = q + (int64_t)nq * wave_fetch_add(head, 1u);
+        int64_t slot;
+        if (team) {
+            __syncthreads();
+            if (wave == 0) s_ticket = wave_fetch_add(head, 1u);
+            __syncthreads();
+            slot = q + (int64_t)nq * (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket);
+        } else {
+            slot = q + (int64_t)nq * wave_fetch_add(head, 1u);
+        }
         if (slot >= n_items) break;
         const uint32_t item = work_order[slot];
         const int tile = (int)(item >> 2);
@@ -1142,10 +1164,7 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
         for (int d = 32; d >= 1; d >>= 1) maxlast = max(maxlast, __shfl_xor(maxlast, d, 64));
         const uint2 rg = ranges[tile];
         maxlast = __builtin_amdgcn_readfirstlane(min(maxlast, (int)(rg.y - rg.x)));  // the walk is uniform
-        prioritise((uint32_t)maxlast);
-        for (int hi = maxlast; hi > 0; hi -= 64) {
-            const int lo = __builtin_amdgcn_readfirstlane(hi > 64 ? hi - 64 : 0);
-            const int nb = hi - lo;
+        const auto stage = [&](int lo, int nb) {
             if (lane < nb) {
                 const uint32_t v = inst_ids[rg.x + lo + lane];
                 const uint32_t id = v & kIdMask;
@@ -1155,6 +1174,59 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
                 M::stage(s_rec[wave][lane], r, x0, y0, P.log2_pmin);
             }
             lds_wave_sync();
+        };
+        int from = 0, to = maxlast;  // the wave's share of the list
+        if (team) {
+            const int share = (maxlast + 3) >> 2;
+            from = __builtin_amdgcn_readfirstlane(min(wave * share, maxlast));
+            to = min(from + share, maxlast);
+            float Tr[PPL], Sr[PPL];
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) {
+                Tr[k] = 1.0f;
+                Sr[k] = 0.0f;
+            }
+            for (int hi = to; hi > from; hi -= 64) {
+                const int lo = max(hi - 64, from), nb = hi - lo;
+                stage(lo, nb);
+                uint32_t at = (uint32_t)((wave * 64 + nb) * sizeof(s_rec[0][0]));
+                for (int j = hi - 1; j >= lo; --j) {
+                    at -= (uint32_t)sizeof(s_rec[0][0]);
+                    asm("" : "+v"(at));
+                    const XRec R = M::load(reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(s_rec) + at));
+                    const RowSpan span = row_span(R.rows, ty * TH);
+                    const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
+#pragma unroll
+                    for (int k = 0; k < PPL; ++k) {
+                        if (k < k_lo || k >= k_hi || !band_open<TW, TH>(bands, span, k)) continue;
+                        XFrag f;
+                        const bool hit = (j < last[k]) & M::test(R, pxr[k], pyr[k], aux[k], P.log2_pmin, f);
+                        if (__ballot(hit) == 0) continue;
+                        const float a = fminf(hit ? M::omega(R, f) : 0.0f, P.alpha_max);
+                        Tr[k] *= __builtin_amdgcn_rcpf(1.0f - a);
+                        Sr[k] += Tr[k] * a * (R.r * g0[k] + R.g * g1[k] + R.b * g2[k]);
+                    }
+                }
+                lds_wave_sync();
+            }
+#pragma unroll
+            for (int k = 0; k < PPL; ++k) s_share[wave][k][lane] = make_float2(Tr[k], Sr[k]);
+            __syncthreads();
+            // state at the end of the wave's share: past the shares behind it
+            for (int w = 3; w > wave; --w)
+#pragma unroll
+                for (int k = 0; k < PPL; ++k) {
+                    const float2 b = s_share[w][k][lane];
+                    S[k] += T[k] * b.y;
+                    T[k] *= b.x;
+                }
+        }
+        const bool staged = team && to - from <= 64;
+        team = team && rg.y - rg.x >= team_len;  // the items behind are no longer
+        for (int hi = to; hi > from; hi -= 64) {
+            const int lo = __builtin_amdgcn_readfirstlane(max(hi - 64, from));
+            const int nb = hi - lo;
+            if (!staged) stage(lo, nb);
             uint32_t at = (uint32_t)((wave * 64 + nb) * sizeof(s_rec[0][0]));  // (see k_blend_bwd)
             for (int j = hi - 1; j >= lo; --j) {
                 at -= (uint32_t)sizeof(s_rec[0][0]);

@@ -182,7 +182,8 @@ constexpr int kQueueStride = 1024;
 // `ranges` and `sched` must be zero (emit_and_sort clears them).  `sched` holds
 // sched_words() uint32: the forward queue heads from word 0, the backward
 // heads from sched_backward_heads(), bucket histograms, and at
-// sched_item_count() the number of work items and, next, of those of split tiles.
+// sched_item_count() the number of work items, of those of split tiles, and the
+// listed instances by wave.
 size_t sched_words();
 size_t sched_backward_heads();
 size_t sched_item_count();

@@ -1237,11 +1237,15 @@ __device__ __forceinline__ uint32_t work_bucket(uint32_t len, uint32_t parts)
                        : min(len >> 2, (uint32_t)(kSchedBuckets - kSplitBuckets - 1));
 }
 
+// average work of a wave
+__device__ __forceinline__ uint32_t wave_share(const int64_t *listed, uint32_t waves)
+{
+    return (uint32_t)((*listed + waves - 1) / waves);
+}
+
 __device__ __forceinline__ uint32_t split_length(const int64_t *listed, uint32_t split_min, uint32_t waves)
 {
-    if (split_min == 0u) return 0u;
-    const int64_t share = (*listed + waves - 1) / waves;
-    return (uint32_t)max((int64_t)split_min, share);
+    return split_min == 0u ? 0u : max(split_min, wave_share(listed, waves));
 }
 
 __device__ __forceinline__ uint32_t work_parts(uint32_t len, uint32_t split_len)
@@ -1285,7 +1289,10 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     base[kSchedBuckets - 1 - threadIdx.x] = before;
     cnt[threadIdx.x] = 0;
     if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) n_items[0] = tot;
+        if (threadIdx.x == 0) {
+            n_items[0] = tot;
+            n_items[2] = wave_share(listed, waves);
+        }
         if (threadIdx.x == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
     }
     __syncthreads();
@@ -1355,7 +1362,10 @@ __global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint32_t *__r
     uint32_t tot;
     const uint32_t before = block_inclusive_scan<kSmallTiles / 64>(hb, smem, &tot) - hb;
     if (t < kSchedBuckets) base[kSchedBuckets - 1 - t] = before;
-    if (t == 0) n_items[0] = tot;
+    if (t == 0) {
+        n_items[0] = tot;
+        n_items[2] = wave_share(listed, waves);
+    }
     if (t == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
     __syncthreads();
     if (parts == 1u) work_order[base[b] + rank] = (uint32_t)t << 2;

@@ -61,3 +61,38 @@ def test_teams_equal_waves(r, n, logit, w, h, mip, tile):
             assert torch.equal(a, b)
     if n >= 6000:
         assert int(alone[2].max()) > 128
+
+
+# Lists below a team's shortest, of one and of several batches to a wave; the last shape has 16 slots.
+@pytest.mark.parametrize("tile", [(8, 8), (8, 16), (16, 16), (32, 32)])
+@pytest.mark.parametrize("n,logit", [(40, 0.0), (300, -2.0), (2500, -4.0)])
+def test_team_gradients(r, n, logit, tile):
+    """Exact MIP gradients of a view alone (long lists by four waves together) and
+    beside a view without upstream gradient whose instances raise the average
+    work of a wave above every list (waves alone)."""
+    say(f"case team gradients n {n} logit {logit} tile {tile}")
+    from paper_2503_18682_amd import _lib as L
+
+    g = _scene(n, logit, n)
+    cam = _cam(101, 77, 90.0)
+    opts = dict(tile_w=tile[0], tile_h=tile[1], mip=2)
+    # the same Gaussians seen large, until the instances suffice
+    reps = max(1, 3000 // n)
+    wide = [dict(_cam(2000, 2000, 1800.0)) for _ in range(reps)]
+
+    def grads(cams):
+        dl = [torch.zeros(3, c["height"], c["width"], device="cuda") for c in cams]
+        dl[0] = torch.rand(3, cam["height"], cam["width"], generator=torch.Generator().manual_seed(3)).cuda() - 0.4
+        outs, (buf, ws) = r.render(g, cams, opts, flags=L.RGS_WS_BACKWARD, keep_workspace=True)
+        return r.backward(g, cams, outs, dl, ws, opts), outs[0]
+
+    a, out = grads([cam])
+    b, _ = grads([cam] + wide)
+    if n == 2500:
+        assert int(out["n_contrib"].max()) > 256
+    # T and the colour term pass up to 2500 roundings of 2^-24 in either order, and the terms of a
+    # gradient may cancel to a tenth
+    tol = 2 * 2500 * 2.0 ** -24 * 10
+    for k in ("means", "log_scales", "quats", "opacity_logits", "sh"):
+        top = float(a[k].abs().max())
+        assert top > 0 and float((a[k] - b[k]).abs().max()) <= tol * top, k
