@@ -188,11 +188,14 @@ __global__ __launch_bounds__(256) void k_zero_kept_grads(const uint32_t *__restr
 
 // Geometry and opacity (the colour part is k_colour_bwd).
 // One instantiation per divergence and MIP mode (as the forward preprocess),
-// so that each carries only its own chain.
+// so that each carries only its own chain.  With few waves on a SIMD (3, by the
+// registers of the double precision chain) the wait for a view's gradient line would stay
+// exposed, so the next view's is fetched ahead: 16 views of 6M Gaussians 1360 -> 1175 us,
+// of 39M kept lines.
 enum BwdMode { kBwdRay = 0, kBwdMip = 1, kBwdMipExact = 2, kBwdGS = 3 };
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_preprocess_bwd(
+__global__ __launch_bounds__(256, MODE == 0 ? 3 : 1) void k_preprocess_bwd(
     const float *__restrict__ means, const float *__restrict__ log_scales, const float *__restrict__ quats,
     const float *__restrict__ opacity_logits, int n, const DevView *__restrict__ views, int n_views,
     const uint32_t *__restrict__ tile_counts, const float *__restrict__ record_grads, DevOptions opt,
@@ -222,11 +225,32 @@ __global__ __launch_bounds__(256) void k_preprocess_bwd(
 
     double dm[3] = {0, 0, 0}, dl[3] = {0, 0, 0}, dR[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, da = 0.0;
 
-    for (int v = 0; v < n_views; ++v) {
-        const size_t idx = (size_t)v * n + i;
-        if (tile_counts[idx] == 0) continue;
+    constexpr int kStride = MODE == kBwdMipExact ? kGradFloatsExactMip : kGradFloats, kUsed = MODE == kBwdMipExact ? 0 : 10;
+    // the next view's gradient and the count of the one after it are in flight
+    const auto count = [&](int v) { return v < n_views ? tile_counts[(size_t)v * n + i] : 0u; };
+    float gr_next[12];
+    const auto fetch = [&](int v) {
+        const float4 *src = reinterpret_cast<const float4 *>(record_grads + ((size_t)v * n + i) * kStride);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float4 x = src[c];
+            gr_next[4 * c] = x.x;
+            gr_next[4 * c + 1] = x.y;
+            gr_next[4 * c + 2] = x.z;
+            gr_next[4 * c + 3] = x.w;
+        }
+    };
+    uint32_t here = count(0), next = count(1), after;
+    if (kUsed && here) fetch(0);
+    for (int v = 0; v < n_views; ++v, here = next, next = after) {
+        after = count(v + 2);
+        float own[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) own[c] = gr_next[c];
+        if (kUsed && next) fetch(v + 1);
+        if (here == 0) continue;
         const DevView &V = views[v];
-        const float *gr = record_grads + idx * (MODE == kBwdMipExact ? kGradFloatsExactMip : kGradFloats);
+        const float *gr = kUsed ? own : record_grads + ((size_t)v * n + i) * kStride;
         if constexpr (MODE == kBwdMipExact) {
             const double mu[3] = {V.w2c[0] * m[0] + V.w2c[1] * m[1] + V.w2c[2] * m[2] + V.w2c[3],
                                   V.w2c[4] * m[0] + V.w2c[5] * m[1] + V.w2c[6] * m[2] + V.w2c[7],
@@ -423,11 +447,17 @@ __global__ __launch_bounds__(256) void k_colour_bwd(const float *__restrict__ me
     }
     const double m[3] = {means[i], means[n + i], means[2 * n + i]};
     double dm[3] = {0, 0, 0};
+    // the next view's count and the view's gradient are loaded ahead of their use (1770 -> 1645 us
+    // for 16 views of 6M Gaussians; with the next view's gradient ahead too 255 registers and 1700 us)
+    uint32_t next = tile_counts[i];
     for (int v = 0; v < n_views; ++v) {
         const size_t idx = (size_t)v * n + i;
-        if (tile_counts[idx] == 0) continue;
-        const DevView &V = views[v];
+        const uint32_t here = next;
+        if (v + 1 < n_views) next = tile_counts[idx + n];
+        if (here == 0) continue;
         const float *gr = record_grads + idx * grad_stride;
+        const float g3[3] = {gr[rgb_offset], gr[rgb_offset + 1], gr[rgb_offset + 2]};
+        const DevView &V = views[v];
         float dir[3];
         double dist;
         view_dir(m, V.centre, dir, &dist);
@@ -437,7 +467,7 @@ __global__ __launch_bounds__(256) void k_colour_bwd(const float *__restrict__ me
         // channels clamped at zero in the forward pass no gradient
         float gcol[3];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) gcol[ch] = col[ch] > 0.0f ? gr[rgb_offset + ch] : 0.0f;
+        for (int ch = 0; ch < 3; ++ch) gcol[ch] = col[ch] > 0.0f ? g3[ch] : 0.0f;
         float wk[NK];
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
