@@ -361,7 +361,10 @@ class RenderFunction(torch.autograd.Function):
         # the backward must see the forward's tile shape
         options = renderer.resolve_options(int(means.shape[1]), cams, options)
         outs, (buf, ws) = renderer.render(g, cams, options, flags=L.RGS_WS_BACKWARD, check=True, keep_workspace=True)
-        ctx.renderer, ctx.cams, ctx.options, ctx.g, ctx.outs, ctx.ws_buf, ctx.ws = renderer, cams, options, g, outs, buf, ws
+        ctx.renderer, ctx.cams, ctx.options, ctx.g, ctx.ws_buf, ctx.ws = renderer, cams, options, g, buf, ws
+        # not the returned tensors themselves: they hold this node, which would hold them and the
+        # workspace in a cycle until a garbage collection
+        ctx.outs = [{k: t.detach() for k, t in o.items()} for o in outs]
         return tuple(o["rgb"] for o in outs)
 
     @staticmethod
