@@ -309,7 +309,7 @@ rgs_status compute_layout(rgs_context *ctx, int64_t n, const rgs_camera *cams, i
         tiles += (int64_t)((cams[v].width + s.w - 1) / s.w) * ((cams[v].height + s.h - 1) / s.h);
     if (tiles >= (int64_t(1) << 29)) return fail(ctx, RGS_EINVAL, "too many tiles (at most 2^29 - 1)");
     L.total_tiles = tiles;
-    L.tile_bits = bits_for(tiles + 1);  // 2^tile_bits - 1 (the empty-instance tile) >= tiles
+    L.tile_bits = bits_for(tiles + 1);  // 2^tile_bits > tiles
     L.nv_records = n * n_views;
     L.capacity = capacity;
     const size_t NV = (size_t)L.nv_records;
@@ -568,8 +568,8 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? kSplitLen : 0u;
     const int blend_blocks = ctx->grid_fwd[mode.kernel()][shape_index(s)];
     const uint32_t waves = (uint32_t)(mode.waves() * blend_blocks);
-    RGS_HIP(ctx, launch_tile_ranges(inst_tiles, listed, L.capacity, L.total_tiles, split_min, waves, ranges, sched,
-                                    at<uint32_t>(ws, L.tile_order), stream));
+    RGS_HIP(ctx, launch_tile_ranges(inst_tiles, listed, L.capacity, L.total_tiles, L.tile_bits, split_min, waves, ranges,
+                                    sched, at<uint32_t>(ws, L.tile_order), stream));
     tm.mark(ST_RANGES);
     RGS_HIP(ctx, launch_blend(s, mode, ranges, tile_order, sched + sched_item_count(), inst_ids, records, views,
                               n_views, L.total_tiles, NV, dopt, sched,

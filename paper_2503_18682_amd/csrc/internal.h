@@ -188,7 +188,7 @@ size_t sched_words();
 size_t sched_backward_heads();
 size_t sched_item_count();
 hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counters, int64_t capacity,
-                              int64_t total_tiles, uint32_t split_min, uint32_t waves, uint2 *ranges,
+                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, uint2 *ranges,
                               uint32_t *sched, uint32_t *work_order, hipStream_t stream);
 
 // Shortest list composited as two half-tile work items, or by a team (for tile

@@ -295,6 +295,8 @@ __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restri
 // block sums the rows before its own (and all of them for the digit bases)
 // itself, so the pass needs no scan launch.  Otherwise hist is digit-major and
 // scanned, with row_total.
+// With `ranges` (SEG, a sort of one pass) the digits are the tiles, and the first block
+// writes the range of each one that has items: no k_tile_ranges launch (4 us).
 // SEG: the items are the emission's: those of block b are the
 // seg[b].y from seg[b].x on, any number of them, taken a tile at a time; the
 // number of items sorted goes to *kept_out.  Where a window of 16 blocks is less than half
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
     uint32_t *__restrict__ vals_out, int64_t n_max, const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
     uint32_t drop_key, int64_t *__restrict__ kept_out, const uint32_t *__restrict__ hist,
-    const uint32_t *__restrict__ row_total, int nblocks, const uint2 *__restrict__ seg)
+    const uint32_t *__restrict__ row_total, int nblocks, const uint2 *__restrict__ seg, uint2 *__restrict__ ranges)
 {
     constexpr int TILE = THREADS * ITEMS, WAVES = THREADS / 64;
     constexpr int kCntWords = WAVES * kMaxBins / 2, kSumWords = SELF ? 16 * THREADS : 0;
@@ -469,6 +471,7 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
         const uint32_t dig_base = dig_carry + block_inclusive_scan<WAVES>(all, smem, &dig_tot) - all;
         dig_carry += dig_tot;
         if (d < bins) s_base[d] = dig_base + pre;
+        if (SEG && ranges && block == 0 && d < bins && all != 0u) ranges[d] = make_uint2(dig_base, dig_base + all);
     }
     if (kept_out && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
     const uint32_t n32 = (uint32_t)n;
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(int64_t n_max, const in
 // by the lanes of equal digit, and the digits are the bits between the
 // near plane's key and the largest one, spread over as few passes as 8 bits a pass allow.
 // Then the boxes are gathered and both counts scanned, as k_scan_reduce and k_scan_apply do.
-// Whole frames at 128x96 by the number of Gaussians, general path -> this: 64 73 -> 48
+// Whole frames at 128x128 by the number of Gaussians, general path -> this: 64 73 -> 48
 // us, 1000 95 -> 73 us, 2000 119 -> 104 us, 4000 148 -> 136 us; 8000 155 -> 165 us, so the line is at 4096.
 // Bound by the latency of a pass (about 2.5 us).
 constexpr int kSmallDigitBits = 8;
@@ -1314,44 +1317,22 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     }
 }
 
-// The same for at most kSmallTiles tiles, in one launch of one workgroup, with
-// the ranges too (`find_ranges`) where the capacity is small: 128 tiles of a frame of 1000 Gaussians
-// 4 us instead of 8, 560 tiles with a launch for the ranges 6.5 instead of 9.
+// The same for at most kSmallTiles tiles in one launch of one workgroup: 2.7 us
+// instead of 5.5 for 560 tiles.
 constexpr int kSmallTiles = 1024;
-constexpr int64_t kSmallInstances = int64_t(1) << 15;
 
-__global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint32_t *__restrict__ inst_tiles,
-                                                             const int64_t *__restrict__ listed, int64_t capacity,
-                                                             int total_tiles, uint32_t split_min, uint32_t waves,
-                                                             bool find_ranges, uint2 *__restrict__ ranges,
-                                                             uint32_t *__restrict__ n_items,
+__global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint2 *__restrict__ ranges, int total_tiles,
+                                                             const int64_t *__restrict__ listed, uint32_t split_min,
+                                                             uint32_t waves, uint32_t *__restrict__ n_items,
                                                              uint32_t *__restrict__ work_order)
 {
-    __shared__ uint2 s_range[kSmallTiles];
     __shared__ uint32_t base[kSchedBuckets];
     __shared__ uint32_t smem[kSmallTiles / 64];
     const int t = threadIdx.x;
     if (t < kSchedBuckets) base[t] = 0u;
     uint2 r = make_uint2(0u, 0u);
-    if (find_ranges) {
-        const int n = (int)clamp_count(listed, capacity);
-        s_range[t] = r;
-        __syncthreads();
-        for (int i = t; i < n; i += kSmallTiles) {
-            const uint32_t tile = inst_tiles[i];
-            const uint32_t before = i > 0 ? inst_tiles[i - 1] : 0xffffffffu;
-            const uint32_t after = i + 1 < n ? inst_tiles[i + 1] : 0xffffffffu;
-            if (tile >= (uint32_t)total_tiles) continue;
-            if (before != tile) s_range[tile].x = (uint32_t)i;
-            if (after != tile) s_range[tile].y = (uint32_t)i + 1u;
-        }
-        __syncthreads();
-        r = s_range[t];
-        if (t < total_tiles) ranges[t] = r;
-    } else {
-        if (t < total_tiles) r = ranges[t];
-        __syncthreads();
-    }
+    if (t < total_tiles) r = ranges[t];
+    __syncthreads();
     const uint32_t split_len = split_length(listed, split_min, waves);
     const uint32_t len = r.y - r.x, parts = t < total_tiles ? work_parts(len, split_len) : 0u;
     const uint32_t b = work_bucket(len, parts);
@@ -1426,7 +1407,7 @@ namespace {
 template <int TH, int IT, bool SELF>
 void radix_pass(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *vo, int64_t n_max, const int64_t *pn,
                 const RadixPass &pass, int wide, bool drop, uint32_t drop_key, int64_t *kept_out,
-                const RadixRange *top, const uint2 *seg, uint32_t *scratch, hipStream_t stream)
+                const RadixRange *top, const uint2 *seg, uint2 *ranges, uint32_t *scratch, hipStream_t stream)
 {
     constexpr int tile = TH * IT;
     const int nblocks = (int)((n_max + tile - 1) / tile), grid = xcd_grid(nblocks);
@@ -1441,12 +1422,13 @@ void radix_pass(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *
                                                                row_total);
     const auto scatter = seg ? &k_radix_scatter<TH, IT, SELF, true> : &k_radix_scatter<TH, IT, SELF, false>;
     scatter<<<grid, TH, 0, stream>>>(ki, vi, ko, vo, n_max, pn, pass, drop, drop_key, kept_out, hist, row_total, nblocks,
-                                     seg);
+                                     seg, ranges);
 }
 
 hipError_t sort_passes(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32_t *vals_alt, int64_t n_max,
                        const int64_t *n_dev, int bits, const RadixRange *range, bool drop, uint32_t drop_key,
-                       int64_t *kept_out, bool iota, const uint2 *seg, uint32_t *scratch, hipStream_t stream)
+                       int64_t *kept_out, bool iota, const uint2 *seg, uint2 *ranges, uint32_t *scratch,
+                       hipStream_t stream)
 {
     const int passes = radix_passes(bits);
     const bool fewer = drop || seg;  // items leave the sort in the first pass
@@ -1460,7 +1442,7 @@ hipError_t sort_passes(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint3
                                             : &radix_pass<kSortThreads, kLargeItems, false>;
         run(ki, iota && first ? nullptr : vi, ko, vo, n_max, fewer && !first ? kept_out : n_dev, pass, wide,
             drop && first, drop_key, fewer && first ? kept_out : nullptr, first ? range : nullptr,
-            first ? seg : nullptr, scratch, stream);
+            first ? seg : nullptr, passes == 1 ? ranges : nullptr, scratch, stream);
         std::swap(ki, ko);
         std::swap(vi, vo);
     }
@@ -1477,7 +1459,7 @@ hipError_t radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys_alt, uint32
         return hipGetLastError();
     }
     return sort_passes(keys, vals, keys_alt, vals_alt, n_max, n_dev, bits, range, drop, drop_key, kept_out, iota,
-                       nullptr, scratch, stream);
+                       nullptr, nullptr, scratch, stream);
 }
 
 // sized for the smallest tile, so either choice of items per thread fits
@@ -1572,7 +1554,7 @@ hipError_t emit_and_sort(const uint32_t *order, const uint32_t *offsets, uint32_
     uint32_t *const hist = bin_scratch + step_words(capacity) + seg_words(capacity);
     if (!emit)
         return sort_passes(tiles, ids, tiles_alt, ids_alt, capacity, counters, tile_bits, nullptr, false, 0u, listed,
-                           false, seg, hist, stream);
+                           false, seg, ranges, hist, stream);
     const int nblocks = (int)emit_blocks(capacity), grid = xcd_grid(nblocks);
     const RadixPass pass{nullptr, 0u, tile_bits, 0, radix_passes(tile_bits)};
     // runs even with no Gaussian: it clears the ranges and scheduling words
@@ -1624,20 +1606,20 @@ size_t sched_item_count() { return 2 * sched_backward_heads() + 2 * kSchedBucket
 size_t sched_words() { return sched_item_count() + 4; }
 
 hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counters, int64_t capacity,
-                              int64_t total_tiles, uint32_t split_min, uint32_t waves, uint2 *ranges,
+                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, uint2 *ranges,
                               uint32_t *sched, uint32_t *work_order, hipStream_t stream)
 {
-    // the ranges, queue heads and scheduling histograms were cleared by k_emit
+    // the ranges, queue heads and scheduling histograms were cleared by k_emit; a tile sort
+    // of one pass has written the ranges
     // a grid-stride loop over the listed instances (a grid sized for the whole
     // capacity would mostly launch idle workgroups)
-    const bool small = total_tiles <= kSmallTiles, find = small && capacity <= kSmallInstances;
-    if (capacity > 0 && !find) {
+    if (capacity > 0 && radix_passes(tile_bits) > 1) {
         const unsigned grid = (unsigned)std::min<int64_t>((capacity + 4 * kThreads - 1) / (4 * kThreads), kRangeBlocks);
         k_tile_ranges<<<grid, kThreads, 0, stream>>>(inst_tiles, counters, capacity, total_tiles, ranges);
     }
-    if (small) {
-        k_sched_small<<<1, kSmallTiles, 0, stream>>>(inst_tiles, counters, capacity, (int)total_tiles, split_min, waves,
-                                                     find, ranges, sched + sched_item_count(), work_order);
+    if (total_tiles <= kSmallTiles) {
+        k_sched_small<<<1, kSmallTiles, 0, stream>>>(ranges, (int)total_tiles, counters, split_min, waves,
+                                                     sched + sched_item_count(), work_order);
         return hipGetLastError();
     }
     const unsigned nb = (unsigned)((total_tiles + kThreads - 1) / kThreads);
