@@ -571,15 +571,15 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
 // Compositing of a tile by the eight waves of a workgroup: the split tiles,
 // two items in a row each, or all tiles of a small frame.  A frame ends no sooner
 // than its longest list, and a wave alone takes 400 to 1000 cycles for a list entry,
-// nearly all of it latency (a frame of 108 tiles kept 4 % of the VALU issue slots busy).
+// nearly all of it latency (a frame of 128 tiles kept 4 % of the VALU issue slots busy).
 // Here the list is taken in batches of 64 / slots records.  Waves 0 .. slots - 1 composite
 // one slot each: the chain T -> T (1 - alpha) is all that is left of a record, its alphas and
 // colours read from LDS four records ahead.  The other waves meanwhile compute the next batch's alphas,
 // which depend on no other record, and the last of them also stages the batch after that.
 // The values and their order are those of the single wave, bit for bit.
-// Measured, k_blend -> k_blend_team: 51 -> 25 us at 128x96, 78 -> 43 us at 317x211, 75 -> 52 us at
-// 1280x720; exact MIP 122 -> 72 us for two views of 801x533, 535 -> 330 us for two of 1032x1104.
-// Four waves that took turns (alphas, barrier, compositing) came to 39 us at 128x96.
+// Measured, k_blend -> k_blend_team: 51 -> 25 us at 128x128, 78 -> 43 us at 317x211, 75 -> 52 us at
+// 1280x720; exact MIP 122 -> 72 us for two views of 801x533, 535 -> 272 us for two of 1032x1104.
+// Four waves that took turns (alphas, barrier, compositing) came to 39 us at 128x128.
 constexpr int kTeamThreads = 512, kTeamWaves = kTeamThreads / 64;
 
 // Two workgroups on a CU, or three where at most six registers spill for it (plain model, two slots: 88 -> 80).
@@ -603,14 +603,20 @@ __global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) v
     float(*const s_alpha)[PPL][B][64] = reinterpret_cast<float(*)[PPL][B][64]>(s_mem);
     float4(*const s_rec)[B][M::kStaged] = reinterpret_cast<float4(*)[B][M::kStaged]>(s_mem + kAlpha4);
     __shared__ unsigned long long s_hit[2][NP][PPL];  // records that reach a pixel of the slot, by producer
-    __shared__ uint32_t s_live[PPL];                  // the slot holds a pixel that has not stopped
+    __shared__ uint32_t s_live[2][PPL];  // the slot holds a pixel that has not stopped, by step
     __shared__ uint32_t s_ticket[2];
     const uint32_t amax_bits = __float_as_uint(P.alpha_max);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = min((int)gridDim.x, kQueues), q = (int)blockIdx.x % nq;
     unsigned int *const head = queue + q * kQueueStride;  // the teams' is half a stride on
-    // units of work: the split tiles, and all the others after them if asked for
-    const int64_t n_split = n_items_p[1] >> 1, n_units = all_tiles ? (int64_t)n_items_p[0] - n_split : n_split;
+    // Units of work: the split tiles, and all the others after them if asked for.  Teams shorten
+    // the few longest lists, so no more of them than half the workgroups (two views of 1032x1104
+    // with exact MIP, 1217 split tiles of 17802: 272 us; 289 with as many as workgroups, 319 with all), and
+    // none where most lists are long alike (a wall close by, 1770 tiles: 52 us, with teams 72).
+    int64_t n_split = n_items_p[1] >> 1;
+    const int64_t most = (gridDim.x + 1) / 2;
+    if (!all_tiles && n_split > most) n_split = 2 * n_split > P.total_tiles ? 0 : most;
+    const int64_t n_units = all_tiles ? (int64_t)n_items_p[0] - n_split : n_split;
     const bool composer = wave < PPL, stager = wave == kTeamWaves - 1 && lane < B;
     const int prod = wave - PPL;  // producer
     // the next tile's ticket is taken while this one is composited
@@ -655,18 +661,19 @@ __global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) v
         }
         if (composer) {
             const bool any = __ballot(!done) != 0;
-            if (lane == 0) s_live[wave] = any ? 1u : 0u;
+            if (lane == 0) s_live[0][wave] = any ? 1u : 0u;
         }
-        // step b: producers take batch b, composers batch b - 1
+        // Step b: producers take batch b, composers batch b - 1.  One barrier a
+        // step: all that a step writes is read in the next one, and written again
+        // in the one after that.
         int rb = 0;  // record buffer of batch b
         for (int b = 0; b <= n_batches; ++b) {
             __syncthreads();
             uint32_t live = 0u;
 #pragma unroll
-            for (int k = 0; k < PPL; ++k) live |= s_live[k] << k;
+            for (int k = 0; k < PPL; ++k) live |= s_live[b & 1][k] << k;
             live = __builtin_amdgcn_readfirstlane(live);
-            if (live == 0u) break;  // uniform: flags change between the barriers of two steps only
-            __syncthreads();
+            if (live == 0u) break;  // uniform
             const int rprev = rb == 0 ? 2 : rb - 1, rnext = rb == 2 ? 0 : rb + 1;
             if (composer) {
                 if (b > 0 && ((live >> wave) & 1u)) {
@@ -721,9 +728,9 @@ __global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) v
                             c[i] = cn[i];
                         }
                     }
-                    const bool any = __ballot(!done) != 0;
-                    if (lane == 0) s_live[wave] = any ? 1u : 0u;
                 }
+                const bool any = __ballot(!done) != 0;
+                if (lane == 0) s_live[(b + 1) & 1][wave] = any ? 1u : 0u;
             } else if (b < n_batches) {
                 const uint32_t base = rg.x + (uint32_t)(b * B);
                 const int nb = min(B, (int)(rg.y - base));
@@ -1374,7 +1381,7 @@ bool tile_shape_supported(int w, int h)
 #define RGS_SHAPES(X) X(8, 8) X(8, 16) X(8, 32) X(16, 8) X(16, 16) X(16, 32) X(32, 8) X(32, 16) X(32, 32)
 
 // Where teams are taken.  Exact MIP always gains, as the team kernel costs it no
-// occupancy (4 waves per SIMD either way): 122 -> 72 us at 6868 tiles, 535 -> 330 us at 17802.
+// occupancy (4 waves per SIMD either way): 122 -> 72 us at 6868 tiles, 535 -> 272 us at 17802.
 // The plain kernel goes from 7 to 6 waves per SIMD, and gains only where the longest
 // lists bound the frame: 75 -> 52 us at 7200 tiles, 105 -> 108 us at 9600 with long lists
 // everywhere, 123 -> 152 us at 16200.  A team for every tile spends twice the instructions:
