@@ -565,7 +565,7 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     const uint32_t *inst_tiles = at<uint32_t>(ws, L.inst_tiles_a);
     const uint32_t *inst_ids = at<uint32_t>(ws, L.inst_ids_a);
     const BlendMode mode = blend_mode(s, opts.mip == 2, L.total_tiles);
-    const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? kSplitLen : 0u;
+    const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? (mode.team ? kTeamSplitLen : kSplitLen) : 0u;
     const int blend_blocks = ctx->grid_fwd[mode.kernel()][shape_index(s)];
     const uint32_t waves = (uint32_t)(mode.waves() * blend_blocks);
     RGS_HIP(ctx, launch_tile_ranges(inst_tiles, listed, L.capacity, L.total_tiles, L.tile_bits, split_min, waves, ranges,

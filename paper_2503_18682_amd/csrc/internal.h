@@ -194,8 +194,9 @@ hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counter
 // Shortest list composited as two half-tile work items, or by a team (for tile
 // shapes with at least two pixel slots per lane).  Teams: a 1280x720 frame took 75 us
 // with 256, 55 us with 128 and 63 us with 64; two exact MIP views of 801x533 108, 72 and 86 us.
-// Large frames do not mind (1920x1080 and 4 views of a megapixel: the same with 128 and 256).
-constexpr uint32_t kSplitLen = 128;
+// Halves read and stage every record twice: a 1920x1080 frame of 500k Gaussians took 113.6
+// us with 128 and 110.6 us with 256.
+constexpr uint32_t kSplitLen = 256, kTeamSplitLen = 128;
 
 // How the tiles of a frame are composited.
 //   per wave   a wave takes whole tiles and halves (k_blend)
