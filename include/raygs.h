@@ -271,10 +271,11 @@ rgs_status rgs_autotune_training(rgs_context *ctx, const rgs_gaussians *g, const
  * may be NULL. */
 typedef struct {
     size_t counters;       /* int64[8]: [0] instances needed (tiles of all binning boxes), [1] capacity,
-                              [2] tile rows of all binning boxes, [3] listed instances (sorted; the rest are
-                              empty), [4] kept (not culled) Gaussian-views, [5] quads with a vertex at
+                              [2] tile rows of all binning boxes, [3] listed instances (sorted; no others
+                              are written), [4] kept (not culled) Gaussian-views, [5] quads with a vertex at
                               z <= 0 (65536 of them, in no fixed order, have their box clipped to the
-                              view frustum; any others keep the whole view) */
+                              view frustum; any others keep the whole view), [6] (low 32 bits) the largest
+                              depth key that the sort's digits have to cover */
     size_t views;          /* per-view device table */
     size_t records;        /* float[16] per Gaussian-view (float[28] with mip = 2), index v * n + i */
     size_t depth_keys;     /* uint32 per Gaussian-view: the kept views' keys, sorted, in [0, counters[4]) */
@@ -288,7 +289,7 @@ typedef struct {
                               [0, counters[4]) */
     size_t offsets;        /* uint32 per Gaussian-view: first instance of each sorted entry */
     size_t inst_tiles;     /* uint32 per instance: global tile id, sorted, [0, counters[3]) (binning box tiles
-                              whose pixel-centre rectangle misses the support are dropped by the sort) */
+                              whose pixel-centre rectangle misses the support are never written) */
     size_t inst_ids;       /* uint32 per instance: Gaussian-view id (low 28 bits) sorted by (tile, depth, id);
                               with tile shapes of at most 4 pixel slots of 64 pixels, the top 4 bits
                               flag the slots that the support reaches (0 with more slots) */
