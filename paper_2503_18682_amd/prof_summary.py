@@ -104,7 +104,7 @@ def write_summary(res, kernel, out, command, workload):
     lines = [
         f"# HBM traffic of {kernel} ({workload})",
         "#",
-        "# Commands (repository root R on the GPU box, run from /tmp with TMPDIR=/tmp):",
+        "# Commands (repository root R, run from /tmp with TMPDIR=/tmp):",
     ]
     lines += [f"#   {c}" for c in command.split(" ;; ")]
     lines += [
@@ -175,7 +175,7 @@ def write_traffic_table(fetch_csv, write_csv, stats_csv, copy_mib, out, command,
             total_ns[m.group(1)] += float(r["TotalDurationNs"])
     trace_frames = calls.get(frame_kernel, 1.0)
     lines = [f"# HBM traffic and bandwidth per frame, every kernel ({workload})", "#",
-             "# Commands (repository root R on the GPU box, run from /tmp with TMPDIR=/tmp):"]
+             "# Commands (repository root R, run from /tmp with TMPDIR=/tmp):"]
     lines += [f"#   {c}" for c in command.split(" ;; ")]
     lines += ["#",
               f"# bytes = FETCH_SIZE x 1024 x {scales['FETCH_SIZE']:.4f} + WRITE_SIZE x 1024 x "
@@ -206,7 +206,7 @@ def write_stats(csv_path, out, command, workload):
         rows = list(csv.DictReader(f))
     total = sum(float(r["TotalDurationNs"]) for r in rows)
     lines = [f"# Kernel durations: {workload}", "#",
-             "# Commands (repository root R on the GPU box, run from /tmp with TMPDIR=/tmp):"]
+             "# Commands (repository root R, run from /tmp with TMPDIR=/tmp):"]
     lines += [f"#   {c}" for c in command.split(" ;; ")]
     lines += ["#", "# kernel | calls | average us | min us | max us | total ms | percent"]
     for r in sorted(rows, key=lambda r: -float(r["TotalDurationNs"])):
@@ -241,7 +241,7 @@ def write_counters(csv_paths, kernel, out, command, workload, clock_ghz=2.4, sim
     avg = {k: sum(v) / len(v) for k, v in vals.items()}
     t = sum(ns) / len(ns) * 1e-9
     lines = [f"# SQ counters of {kernel} ({workload}), averages per dispatch", "#",
-             "# Commands (repository root R on the GPU box, run from /tmp with TMPDIR=/tmp):"]
+             "# Commands (repository root R, run from /tmp with TMPDIR=/tmp):"]
     lines += [f"#   {c}" for c in command.split(" ;; ")]
     lines += ["#", f"duration_us_under_counters: {t * 1e6:.1f}"]
     lines += [f"{k}: {v:.4g}" for k, v in sorted(avg.items())]
