@@ -170,8 +170,10 @@ hipError_t emit_and_sort(const uint32_t *order, const uint32_t *offsets, uint32_
 // (separate memory lines, so their atomics do not serialise on one
 // address); workgroup b takes queue b % min(grid, kQueues) and queue q hands
 // out the work-order slots q, q + nq, q + 2 nq, ...
-constexpr int kQueues = 8;
-constexpr int kQueueStride = 1024;
+// 8, 16 and 32 heads: 1280x720 frame 47.5, 41.9 and 42.6 us of compositing, 1920x1080 105, 103 and 104
+// us, 8 views of 3M Gaussians 3330, 3223 and 3250 us.
+constexpr int kQueues = 16;
+constexpr int kQueueStride = 512;
 
 // Tile ranges of the `*counters` sorted instances plus the compositing work
 // order: work items tile << 2 | part (0 whole tile; 1, 2 the first and
