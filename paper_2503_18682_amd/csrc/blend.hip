@@ -1402,11 +1402,11 @@ bool tile_shape_supported(int w, int h)
 
 // Where teams are taken.  Exact MIP always gains, as the team kernel costs it no
 // occupancy (4 waves per SIMD either way): 122 -> 72 us at 6868 tiles, 535 -> 272 us at 17802.
-// The plain kernel goes from 7 to 6 waves per SIMD, and gains only where the longest
-// lists bound the frame: 75 -> 52 us at 7200 tiles, 105 -> 108 us at 9600 with long lists
-// everywhere, 123 -> 152 us at 16200.  A team for every tile spends twice the instructions:
-// 78 -> 43 us at 560 tiles, but 75 -> 141 us at 7200.
-constexpr int64_t kTeamTiles = 10000, kTeamAllTiles = 1024;
+// The plain kernel goes from 7 to 6 waves per SIMD, and gains only where few long
+// lists bound the frame: 63 -> 43 us at 7200 tiles, but 93 -> 100 us at 9600 (long lists
+// everywhere, so no teams) and 106 -> 119 us at 16320.  A team for every tile spends twice the
+// instructions: 70 -> 41 us at 560 tiles, 49 -> 48 us at 1012, but 75 -> 141 us at 7200.
+constexpr int64_t kTeamTiles = 8192, kTeamAllTiles = 1024;
 constexpr int kTeamSlots = 4;
 
 BlendMode blend_mode(TileShape s, bool exact_mip, int64_t total_tiles)
