@@ -1115,6 +1115,10 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 // state that the others leave it.  The second test costs a fifth more: 302 -> 197 us;
 // with lists from 24 entries on 218 us, from 72 on 195 us, from 128 on 230 us.
 constexpr uint32_t kTeamBackwardLen = 64;
+// Smallest transmittance behind a shared list.  A share's product is at most the inverse of it, and the colour term's
+// sum that times the upstream gradient; behind an opaque stack and without a stopping threshold the
+// transmittance underflows, the product overflows and 0 inf is not a number.
+constexpr float kTeamBackwardT = 1e-9f;
 
 template <int TW, int TH>
 __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict__ ranges,
@@ -1203,7 +1207,13 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
             lds_wave_sync();
         };
         int from = 0, to = maxlast;  // the wave's share of the list
-        if (team) {
+        float least = T[0];
+#pragma unroll
+        for (int k = 1; k < PPL; ++k) least = fminf(least, T[k]);
+        if (team && __ballot(!(least >= kTeamBackwardT)) != 0) {
+            team = false;  // (alike in the four waves) the first takes the whole list
+            to = __builtin_amdgcn_readfirstlane(wave == 0 ? maxlast : 0);
+        } else if (team) {
             const int share = (maxlast + 3) >> 2;
             from = __builtin_amdgcn_readfirstlane(min(wave * share, maxlast));
             to = min(from + share, maxlast);
