@@ -1108,12 +1108,17 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 //   [22..24] colour.
 // Most of its 200 instructions per slot are the chain above, where products and sums
 // fuse: 337 -> 302 us for two views of 801x533.  Then the longest lists
-// bound it (1.7 waves per SIMD on average), so as long as the lists, which come in
-// decreasing length, are no shorter than kTeamBackwardLen and the average work of a wave, the four waves
-// of a workgroup share a list: each takes a quarter, first only for the product of
-// 1 / (1 - alpha) and the sum of the colour term over it, from which follows the
-// state that the others leave it.  The second test costs a fifth more: 302 -> 197 us;
-// with lists from 24 entries on 218 us, from 72 on 195 us, from 128 on 230 us.
+// bound it (1.7 waves per SIMD on average), so at first the four waves of a workgroup share a list: each
+// takes a quarter, first only for the product of 1 / (1 - alpha) and the sum of the colour term over it, from which
+// follows the state that the others leave it.  The second test costs a third of the walk.
+// With A the list entries of all items by the waves of the launch, sharing can pay only where a list takes a wave
+// well beyond A: no list is shared where the longest is shorter than 3/2 A, and otherwise each workgroup shares lists, which
+// come in decreasing length, until one is shorter than kTeamBackwardLen or 2/3 A.  Every list by one wave -> each
+// workgroup's first list and those above 57, 1746 and 944 entries shared -> this rule:
+//   two views of 801x533, A 91, longest 516                     302 ->  187 ->  185 us
+//   three of 653x541 full of needles, A 3734, longest 2999     3460 -> 4320 -> 3200 us
+//   one of 1000x1000 with 16x16 tiles, A 2208, longest 1836     800 ->  857 ->  675 us
+// The two views with 80 in place of 64 185 us, with A in place of 2/3 A 200 us.
 constexpr uint32_t kTeamBackwardLen = 64;
 // Smallest transmittance behind a shared list.  A share's product is at most the inverse of it, and the colour term's
 // sum that times the upstream gradient; behind an opaque stack and without a stopping threshold the
@@ -1143,19 +1148,23 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
     __shared__ float2 s_share[4][PPL][64];
     __shared__ uint32_t s_ticket;
     const int64_t n_items = *n_items_p;
-    const uint32_t team_len = max(kTeamBackwardLen, n_items_p[2]);
-    bool begun = false, team = true;  // the whole workgroup is on one item, as long as the lists are long
+    const uint32_t average =
+        (uint32_t)(*reinterpret_cast<const unsigned long long *>(n_items_p + 2) / (4u * gridDim.x));
+    const uint32_t team_len = max(kTeamBackwardLen, average / 3u * 2u);
+    bool begun = false, team = n_items_p[4] >= average / 2u * 3u;  // the whole workgroup is on one item
+    const int takers = team ? 1 : 4;                               // of a workgroup
     for (;;) {
         int64_t slot;
         if (team) {
             __syncthreads();
             if (wave == 0) s_ticket = begun ? next_ticket(head, q, nq, 1, n_items) : first_ticket(nq, 1, 0);
-            begun = true;
             __syncthreads();
             slot = q + (int64_t)nq * (uint32_t)__builtin_amdgcn_readfirstlane(s_ticket);
         } else {
-            slot = q + (int64_t)nq * next_ticket(head, q, nq, 1, n_items);
+            const uint32_t ticket = begun ? next_ticket(head, q, nq, takers, n_items) : first_ticket(nq, 4, wave);
+            slot = q + (int64_t)nq * (uint32_t)__builtin_amdgcn_readfirstlane(ticket);
         }
+        begun = true;
         if (slot >= n_items) break;
         const uint32_t item = work_order[slot];
         const int tile = (int)(item >> 2);

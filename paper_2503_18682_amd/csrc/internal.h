@@ -184,14 +184,14 @@ constexpr int kQueueStride = 512;
 // `ranges` and `sched` must be zero (emit_and_sort clears them).  `sched` holds
 // sched_words() uint32: the forward queue heads from word 0, the backward
 // heads from sched_backward_heads(), bucket histograms, and at
-// sched_item_count() the number of work items, of those of split tiles, and the
-// listed instances by wave.
+// sched_item_count() the number of work items, of those of split tiles, and, with `sums`, the
+// list entries of all items (64 bits) and the longest list.
 size_t sched_words();
 size_t sched_backward_heads();
 size_t sched_item_count();
 hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counters, int64_t capacity,
-                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, uint2 *ranges,
-                              uint32_t *sched, uint32_t *work_order, hipStream_t stream);
+                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, bool sums,
+                              uint2 *ranges, uint32_t *sched, uint32_t *work_order, hipStream_t stream);
 
 // Shortest list composited as two half-tile work items, or by a team (for tile
 // shapes with at least two pixel slots per lane).  Teams: a 1280x720 frame took 75 us

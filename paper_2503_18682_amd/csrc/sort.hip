@@ -1256,20 +1256,40 @@ __device__ __forceinline__ uint32_t work_parts(uint32_t len, uint32_t split_len)
     return (split_len != 0u && len >= split_len) ? 2u : 1u;
 }
 
+// Adds a tile's list to the sums in n_items[2..4] (all zero before): the entries of all items' lists (64 bits) and
+// the longest list.  All lanes of the wave take part.
+__device__ __forceinline__ void count_entries(uint32_t len, uint32_t parts, uint32_t *n_items)
+{
+    unsigned long long sum = (unsigned long long)len * parts;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        sum += __shfl_xor(sum, d, 64);
+        len = max(len, (uint32_t)__shfl_xor((int)len, d, 64));
+    }
+    if ((threadIdx.x & 63) == 0 && len != 0u) {
+        atomicAdd(reinterpret_cast<unsigned long long *>(n_items + 2), sum);
+        atomicMax(n_items + 4, len);
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void k_sched_hist(const uint2 *__restrict__ ranges, int64_t total_tiles,
                                                          const int64_t *__restrict__ listed, uint32_t split_min,
-                                                         uint32_t waves, uint32_t *__restrict__ hist)
+                                                         uint32_t waves, uint32_t *__restrict__ hist,
+                                                         uint32_t *__restrict__ sums)
 {
     const uint32_t split_len = split_length(listed, split_min, waves);
     __shared__ uint32_t cnt[kSchedBuckets];
     cnt[threadIdx.x] = 0;
     __syncthreads();
     const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    uint32_t len = 0u, parts = 0u;
     if (t < total_tiles) {
         const uint2 r = ranges[t];
-        const uint32_t parts = work_parts(r.y - r.x, split_len);
-        atomicAdd(&cnt[work_bucket(r.y - r.x, parts)], parts);
+        len = r.y - r.x;
+        parts = work_parts(len, split_len);
+        atomicAdd(&cnt[work_bucket(len, parts)], parts);
     }
+    if (sums) count_entries(len, parts, sums);
     __syncthreads();
     if (cnt[threadIdx.x]) atomicAdd(&hist[threadIdx.x], cnt[threadIdx.x]);
 }
@@ -1292,10 +1312,7 @@ __global__ __launch_bounds__(kThreads) void k_sched_scatter(const uint2 *__restr
     base[kSchedBuckets - 1 - threadIdx.x] = before;
     cnt[threadIdx.x] = 0;
     if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) {
-            n_items[0] = tot;
-            n_items[2] = wave_share(listed, waves);
-        }
+        if (threadIdx.x == 0) n_items[0] = tot;
         if (threadIdx.x == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
     }
     __syncthreads();
@@ -1324,7 +1341,7 @@ constexpr int kSmallTiles = 1024;
 __global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint2 *__restrict__ ranges, int total_tiles,
                                                              const int64_t *__restrict__ listed, uint32_t split_min,
                                                              uint32_t waves, uint32_t *__restrict__ n_items,
-                                                             uint32_t *__restrict__ work_order)
+                                                             uint32_t *__restrict__ work_order, bool sums)
 {
     __shared__ uint32_t base[kSchedBuckets];
     __shared__ uint32_t smem[kSmallTiles / 64];
@@ -1337,16 +1354,14 @@ __global__ __launch_bounds__(kSmallTiles) void k_sched_small(const uint2 *__rest
     const uint32_t len = r.y - r.x, parts = t < total_tiles ? work_parts(len, split_len) : 0u;
     const uint32_t b = work_bucket(len, parts);
     const uint32_t rank = parts ? atomicAdd(&base[b], parts) : 0u;
+    if (sums) count_entries(len, parts, n_items);
     __syncthreads();
     // buckets in decreasing order, as in k_sched_scatter
     const uint32_t hb = t < kSchedBuckets ? base[kSchedBuckets - 1 - t] : 0u;
     uint32_t tot;
     const uint32_t before = block_inclusive_scan<kSmallTiles / 64>(hb, smem, &tot) - hb;
     if (t < kSchedBuckets) base[kSchedBuckets - 1 - t] = before;
-    if (t == 0) {
-        n_items[0] = tot;
-        n_items[2] = wave_share(listed, waves);
-    }
+    if (t == 0) n_items[0] = tot;
     if (t == kSplitBuckets - 1) n_items[1] = before + hb;  // those of split tiles
     __syncthreads();
     if (parts == 1u) work_order[base[b] + rank] = (uint32_t)t << 2;
@@ -1603,12 +1618,13 @@ hipError_t launch_copy_i64(const int64_t *src, int64_t *dst, hipStream_t stream)
 
 size_t sched_backward_heads() { return (size_t)kQueues * kQueueStride; }
 size_t sched_item_count() { return 2 * sched_backward_heads() + 2 * kSchedBuckets; }
-size_t sched_words() { return sched_item_count() + 4; }
+size_t sched_words() { return sched_item_count() + 6; }
 
 hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counters, int64_t capacity,
-                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, uint2 *ranges,
-                              uint32_t *sched, uint32_t *work_order, hipStream_t stream)
+                              int64_t total_tiles, int tile_bits, uint32_t split_min, uint32_t waves, bool sums,
+                              uint2 *ranges, uint32_t *sched, uint32_t *work_order, hipStream_t stream)
 {
+    uint32_t *const n_items = sched + sched_item_count();
     // the ranges, queue heads and scheduling histograms were cleared by k_emit; a tile sort
     // of one pass has written the ranges
     // a grid-stride loop over the listed instances (a grid sized for the whole
@@ -1618,15 +1634,16 @@ hipError_t launch_tile_ranges(const uint32_t *inst_tiles, const int64_t *counter
         k_tile_ranges<<<grid, kThreads, 0, stream>>>(inst_tiles, counters, capacity, total_tiles, ranges);
     }
     if (total_tiles <= kSmallTiles) {
-        k_sched_small<<<1, kSmallTiles, 0, stream>>>(ranges, (int)total_tiles, counters, split_min, waves,
-                                                     sched + sched_item_count(), work_order);
+        k_sched_small<<<1, kSmallTiles, 0, stream>>>(ranges, (int)total_tiles, counters, split_min, waves, n_items,
+                                                     work_order, sums);
         return hipGetLastError();
     }
     const unsigned nb = (unsigned)((total_tiles + kThreads - 1) / kThreads);
     uint32_t *hist = sched + 2 * sched_backward_heads(), *cursor = hist + kSchedBuckets;
-    k_sched_hist<<<nb, kThreads, 0, stream>>>(ranges, total_tiles, counters, split_min, waves, hist);
+    k_sched_hist<<<nb, kThreads, 0, stream>>>(ranges, total_tiles, counters, split_min, waves, hist,
+                                              sums ? n_items : nullptr);
     k_sched_scatter<<<nb, kThreads, 0, stream>>>(ranges, total_tiles, counters, split_min, waves, hist, cursor,
-                                                 sched + sched_item_count(), work_order);
+                                                 n_items, work_order);
     return hipGetLastError();
 }
 

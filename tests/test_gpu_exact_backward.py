@@ -81,3 +81,47 @@ def test_gradients_behind_opaque_stacks(r, n, alpha_max, tile, views):
         top = float(want[k].abs().max())
         assert bool(torch.isfinite(got[k]).all()), k
         assert top > 0 and float((got[k] - want[k]).abs().max()) <= tol * top, k
+
+
+def _lists(kind):
+    """A view and Gaussians with: lists that are few, but long beside the average; lists alike; fewer lists than workgroups."""
+    rng = np.random.default_rng(17)
+    w, h, n, spread = {"few": (701, 533, 3000, 0.03), "alike": (701, 533, 40000, 0.6), "small": (131, 93, 9000, 0.5)}[kind]
+    z = rng.uniform(2.0, 8.0, n)
+    xy = (rng.normal(0.0, spread, (2, n)) if kind == "few" else rng.uniform(-spread, spread, (2, n))) * z
+    g = _dev(dict(means=np.stack([xy[0], xy[1], z]), log_scales=np.log(0.03 * z)[None] + rng.normal(0, 0.3, (3, n)),
+                  quats=rng.standard_normal((4, n)), opacity_logits=rng.normal(-4.5, 0.5, n),
+                  sh=rng.uniform(-1.0, 1.0, (1, 3, n))))
+    return g, _cam(w, h)
+
+
+@pytest.mark.parametrize("tile", [(8, 8), (8, 16), (16, 16), (32, 32)])
+@pytest.mark.parametrize("kind", ["few", "alike", "small"])
+def test_shared_lists_equal_single_walk(r, kind, tile):
+    """Gradients as the kernel deals the lists against those of a walk by one wave, which an entry of 1e-12 in the
+    final transmittance of one pixel of each 8x8 block asks for; that pixel has no upstream gradient in either."""
+    from paper_2503_18682_amd import _lib as L
+
+    say(f"case shared lists {kind} tile {tile}")
+    g, cam = _lists(kind)
+    opts = dict(mip=2, tile_w=tile[0], tile_h=tile[1])
+    outs, (buf, ws) = r.render(g, [cam], opts, flags=L.RGS_WS_BACKWARD, keep_workspace=True)
+    T, n = outs[0]["final_T"], int(outs[0]["n_contrib"].max())
+    assert float(T.min()) > 1e-4 and n > 192
+    up = 0.5 + 0.5 * torch.rand(3, cam["height"], cam["width"], generator=torch.Generator().manual_seed(3)).cuda()
+    up[:, ::8, ::8] = 0.0
+    a = r.backward(g, [cam], outs, [up], ws, opts)
+    T[::8, ::8] = 1e-12
+    b = r.backward(g, [cam], outs, [up], ws, opts)
+    # The same terms, all positive in a colour's gradient, with up to n roundings of 2^-24 in T and in the
+    # colour behind, in another association, and in another order of the up to 250 partial sums of a record
+    tol = 2 * (n + 250) * 2.0 ** -24
+    ca, cb = a["sh"][0], b["sh"][0]
+    assert bool((cb >= 0).all()) and float(cb.max()) > 0
+    assert float(((ca - cb).abs() - tol * cb).max()) <= 0
+    # dL/d(logit) sums a (T rgd - S / (1 - a)), each part at most a T (largest colour) (sum of the upstream gradient)
+    most = 2 * tol * (0.5 + 0.2820948) * (cb / 0.2820948).sum(0)
+    assert float(((a["opacity_logits"] - b["opacity_logits"]).abs() - most).max()) <= 0
+    for k in KEYS:
+        top = float(b[k].abs().max())
+        assert top > 0 and float((a[k] - b[k]).abs().max()) <= 20 * tol * top, k
