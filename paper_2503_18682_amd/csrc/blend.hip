@@ -210,6 +210,7 @@ struct PlainModel {
         put_test_form(dst, r, x0, y0, log2_pmin);
     }
     __device__ static Rec load(const float4 *p) { return load_trec(p); }
+    __device__ static Rec load_whole(const float4 *p) { return load_trec(p); }
     __device__ static float3 colour(const float4 *p)
     {
         const float4 d = p[3];
@@ -332,6 +333,19 @@ struct ExactMipModel {
     __device__ static Rec load(const float4 *p)
     {
         const float4 a = p[0], b = p[1], c = p[2], d = p[3], e = p[4], f = p[5], g = p[6], h = p[7];
+        return XRec{a.x, a.y, a.z, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w, d.x, d.y, d.z, d.w,
+                    e.x, e.y, e.z, e.w, f.x, f.y, f.z, f.w, g.x, g.y, g.z, g.w, h.x, h.y, h.z, h.w,
+                    __float_as_uint(a.w)};
+    }
+    // The same, with every read whole and before any branch on the record.  With one slot to a tile the compiler
+    // otherwise reads a record in pieces behind its branches, one wait after the other: 318 against 355 us
+    // for 60k needles at 1000x1000; with more slots the reads are shared by them, and this is slower (264 -> 296 us).
+    __device__ static Rec load_whole(const float4 *p)
+    {
+        using f4 = __attribute__((ext_vector_type(4))) float;
+        const f4 *const w = reinterpret_cast<const f4 *>(p);
+        f4 a = w[0], b = w[1], c = w[2], d = w[3], e = w[4], f = w[5], g = w[6], h = w[7];
+        asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e), "+v"(f), "+v"(g), "+v"(h));
         return XRec{a.x, a.y, a.z, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w, d.x, d.y, d.z, d.w,
                     e.x, e.y, e.z, e.w, f.x, f.y, f.z, f.w, g.x, g.y, g.z, g.w, h.x, h.y, h.z, h.w,
                     __float_as_uint(a.w)};
@@ -516,7 +530,7 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
             nid = inst_ids[min(base + 128 + lane, rg.y - 1u)];
             lds_wave_sync();
             for (uint32_t j = 0; j < nb; ++j) {
-                const typename M::Rec R = M::load(s_rec[j]);
+                const typename M::Rec R = PPL == 1 ? M::load_whole(s_rec[j]) : M::load(s_rec[j]);
                 const RowSpan span = row_span(R.rows, ty * TH);
                 const uint32_t bands = __builtin_amdgcn_readfirstlane(R.rows);
 #pragma unroll
