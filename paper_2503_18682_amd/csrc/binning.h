@@ -73,6 +73,14 @@ __device__ inline double fast_rcp(double x)
     return y;
 }
 
+// The same for any x.  Scales are accepted up to the ends of the double range, and the geometry forms products of four of
+// them: outside the range of the estimate and its steps the library's square root and division, as a branch
+// that waves do not take (0.8 of 41 us of preprocessing for 500k Gaussians, none for more views).
+__device__ inline bool plain_range(double x) { return x > 1e-290 && x < 1e290; }
+__device__ inline double any_rsqrt(double x) { return plain_range(x) ? fast_rsqrt(x) : 1.0 / sqrt(x); }
+__device__ inline double any_sqrt(double x) { return plain_range(x) ? x * fast_rsqrt(x) : sqrt(x); }
+__device__ inline double any_rcp(double x) { return plain_range(x) ? fast_rcp(x) : 1.0 / x; }
+
 __device__ inline ConicFrame conic_frame(const Conic &C)
 {
 #pragma clang fp contract(off)

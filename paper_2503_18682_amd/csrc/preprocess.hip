@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
             if (!(c2 > kappa)) break;
 
             // Sec. 4.1: whitened unit centre, b, R_{mu^ <- v} (App. A.1)
-            const double ic = c2 < 1e300 ? fast_rsqrt(c2) : 0.0, ic2 = ic * ic;
+            const double ic = any_rsqrt(c2), ic2 = ic * ic;
             const double muh[3] = {mw[0] * ic, mw[1] * ic, mw[2] * ic};
             const double b2 = 1.0 - kappa * ic2;
             double Rv[9];
@@ -390,14 +390,14 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
             // closed-form top eigenvector u1 of the 2x2 B; u0 = u1 turned by +90 degrees
             const double mean = 0.5 * (Ba + Bd);
             const double rad2 = 0.25 * (Ba - Bd) * (Ba - Bd) + Bh * Bh;
-            const double rad = rad2 > 1e-290 ? rad2 * fast_rsqrt(rad2) : 0.0;
+            const double rad = any_sqrt(rad2);
             const double lmax = mean + rad;
             double u1x = 1.0, u1y = 0.0;
             if (!(2.0 * rad <= 1e-6 * lmax)) {
                 const double v1x = Bh, v1y = lmax - Ba, v2x = lmax - Bd, v2y = Bh;
                 const double n1 = v1x * v1x + v1y * v1y, n2 = v2x * v2x + v2y * v2y;
                 const bool first = n1 >= n2;
-                const double inv = fast_rsqrt(first ? n1 : n2);
+                const double inv = any_rsqrt(first ? n1 : n2);
                 u1x = (first ? v1x : v2x) * inv;
                 u1y = (first ? v1y : v2y) * inv;
             }
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(256) void k_preprocess(const float *__restrict__ me
                 const double Vx = QU[0] * z0 + QU[1] * z1 + mu[0];
                 const double Vy = QU[2] * z0 + QU[3] * z1 + mu[1];
                 const double Vz = QU[4] * z0 + QU[5] * z1 + mu[2];
-                const double iz = fast_rcp(Vz);
+                const double iz = any_rcp(Vz);
                 const double u = V.fx * Vx * iz + V.cx;
                 const double vv = V.fy * Vy * iz + V.cy;
                 umin = fmin(umin, u);
