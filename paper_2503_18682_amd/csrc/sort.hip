@@ -813,9 +813,10 @@ __global__ __launch_bounds__(THREADS) void k_order_small(
     static_assert(THREADS >= kBins, "a thread per digit");
     __shared__ uint32_t s_key[ROUNDS * THREADS];
     __shared__ uint16_t s_id[ROUNDS * THREADS];
-    __shared__ uint16_t s_cnt[WAVES][kBins];
+    __shared__ uint32_t s_cnt_words[WAVES * kBins / 2];  // digit counts of each wave, 16 bits each, cleared by words
     __shared__ uint32_t s_wave[WAVES];
     __shared__ unsigned long long s_sum[2][WAVES];
+    uint16_t(*const s_cnt)[kBins] = reinterpret_cast<uint16_t(*)[kBins]>(s_cnt_words);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int at0 = wave * ROUNDS * 64 + lane;  // item r of the thread is at0 + 64 r
     uint32_t key[ROUNDS], id[ROUNDS];
@@ -838,8 +839,7 @@ __global__ __launch_bounds__(THREADS) void k_order_small(
     int count = n;  // items, after the first pass the kept ones
     for (int p = 0; p < passes; ++p) {
         __syncthreads();
-        for (int i = tid; i < WAVES * kBins / 2; i += THREADS)
-            reinterpret_cast<uint32_t *>(s_cnt)[i] = 0u;
+        for (int i = tid; i < WAVES * kBins / 2; i += THREADS) s_cnt_words[i] = 0u;
         __syncthreads();
         const int shift = p * width;
         uint32_t digit[ROUNDS], rank[ROUNDS];
