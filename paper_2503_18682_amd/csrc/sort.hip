@@ -28,6 +28,7 @@ constexpr int kMaxBins = 1 << kMaxDigitBits;
 constexpr int kHistWordsLog = 12;  // counters of a histogram block (all copies of all bins)
 constexpr int kHistWords = 1 << kHistWordsLog;
 constexpr int kEmitThreads = 512;  // 8 waves (emit_plan)
+constexpr int kLargeTile = 4096;   // items of a block of a large sort: its workgroups take several blocks
 
 // Element count of a device-sized array: a frame whose instance count
 // overflowed the capacity is treated as empty downstream (its status reports
@@ -157,11 +158,27 @@ __device__ __forceinline__ Digit pass_digit(const RadixPass &P)
 // order leave every line shared by several XCDs, each writing its part to
 // memory).  At least 8 runs per XCD even out blocks of different work: the first in
 // depth order have the widest tile rows.  Returns nb or more when there is none.
-__device__ __forceinline__ int xcd_block(int nb)
+// A launch of a large sort has at most kMaxGrid workgroups, a multiple of 8, and each takes every grid-th place
+// `at`: blocks are as many as the capacity can need, and a workgroup that finds none costs as much as the wait for
+// the count.  20000 Gaussians at 640x480 in a workspace for 80M instances took 269 us with a workgroup for each
+// possible block and take 174 us; full sorts lose up to 1 % (with 3072 workgroups 167 us, and 3 %).  The emission's
+// blocks are of unequal work, and rounds of them even out worse: twice as many workgroups.
+__device__ __forceinline__ int xcd_run(int nb)  // log2 of the run: nb / 64, up to 64
 {
-    const int lrun = nb >= 4096 ? 6 : nb >= 64 ? 25 - __builtin_clz((unsigned)nb) : 0;  // log2 of the run: nb / 64, up to 64
-    const int k = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7u);
+    return nb >= 4096 ? 6 : nb >= 64 ? 25 - __builtin_clz((unsigned)nb) : 0;
+}
+
+__device__ __forceinline__ int xcd_block(int nb, int at)
+{
+    const int lrun = xcd_run(nb), k = at >> 3, xcd = at & 7;
     return ((((k >> lrun) << 3) + xcd) << lrun) + (k & ((1 << lrun) - 1));
+}
+
+// Places that hold the nb blocks (the last round of runs may be partly empty).
+__device__ __forceinline__ int xcd_places(int nb)
+{
+    const int round = 8 << xcd_run(nb);
+    return (nb + round - 1) & -round;
 }
 
 // Entries of a block's histogram row in the block-major layout: 16-bit counts
@@ -187,7 +204,7 @@ template <int THREADS, int ITEMS, bool SELF>
 __global__ __launch_bounds__(THREADS) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t n_max,
                                                         const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
                                                         uint32_t drop_key, uint32_t *__restrict__ hist, int nblocks,
-                                                        const uint32_t *__restrict__ part_max, int n_parts,
+                                                        int grid, const uint32_t *__restrict__ part_max, int n_parts,
                                                         uint32_t *__restrict__ kmax_out)
 {
     constexpr int TILE = THREADS * ITEMS;
@@ -221,28 +238,37 @@ __global__ __launch_bounds__(THREADS) void k_radix_hist(const uint32_t *__restri
         load(base, (int)min(n_max - base, (int64_t)TILE));
     }
     const int64_t n = clamp_count(n_dev, n_max);
-    const int nb = (int)((n + TILE - 1) / TILE), block = SELF ? (int)blockIdx.x : xcd_block(nb);
-    if (block >= nb) return;  // uniform per block
-    const int64_t base = (int64_t)block * TILE;
-    const int left = (int)min(n - base, (int64_t)TILE);
-    if constexpr (!SELF) load(base, left);
-    const Digit D = pass_digit(pass);
-    const int bins = 1 << D.bits;
-    const int cshift = min(3, kHistWordsLog - D.bits);  // log2 of the copies
-    for (int i = tid; i < bins << cshift; i += THREADS) cnt[i] = 0u;
-    __syncthreads();
-    const uint32_t copy = tid & ((1u << cshift) - 1u);
+    constexpr bool ROUNDS = TILE == kLargeTile;
+    const int nb = (int)((n + TILE - 1) / TILE), end = SELF ? nb : xcd_places(nb);
+    for (int at = (int)blockIdx.x; at < end; at += grid) {
+        const int block = SELF ? at : xcd_block(nb, at);
+        if (block >= nb) {  // uniform per block
+            if constexpr (!ROUNDS) return;
+            continue;
+        }
+        const int64_t base = (int64_t)block * TILE;
+        const int left = (int)min(n - base, (int64_t)TILE);
+        if constexpr (!SELF) load(base, left);
+        const Digit D = pass_digit(pass);
+        const int bins = 1 << D.bits;
+        const int cshift = min(3, kHistWordsLog - D.bits);  // log2 of the copies
+        for (int i = tid; i < bins << cshift; i += THREADS) cnt[i] = 0u;
+        __syncthreads();
+        const uint32_t copy = tid & ((1u << cshift) - 1u);
 #pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-        if (j * THREADS + tid < left && !(drop && key[j] == drop_key))
-            atomicAdd(&cnt[(D.of(key[j]) << cshift) + copy], 1u);
-    __syncthreads();
-    const int row = SELF ? hist_row(bins) : bins;
-    for (int d = tid; d < row; d += THREADS) {
-        uint32_t x = 0;
-        if (d < bins)
-            for (int c = 0; c < 1 << cshift; ++c) x += cnt[(d << cshift) + c];
-        put_count<SELF>(hist, bins, nblocks, block, d, x);
+        for (int j = 0; j < ITEMS; ++j)
+            if (j * THREADS + tid < left && !(drop && key[j] == drop_key))
+                atomicAdd(&cnt[(D.of(key[j]) << cshift) + copy], 1u);
+        __syncthreads();
+        const int row = SELF ? hist_row(bins) : bins;
+        for (int d = tid; d < row; d += THREADS) {
+            uint32_t x = 0;
+            if (d < bins)
+                for (int c = 0; c < 1 << cshift; ++c) x += cnt[(d << cshift) + c];
+            put_count<SELF>(hist, bins, nblocks, block, d, x);
+        }
+        if constexpr (!ROUNDS) return;
+        __syncthreads();
     }
 }
 
@@ -305,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void k_radix_scan_rows(uint32_t *__restri
 // with a workgroup for each block and takes 210 us; a frame that lists three quarters
 // would lose (59 -> 63 us).
 template <int THREADS, int ITEMS, bool SELF, bool SEG>
-__global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
+__global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 6) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
     uint32_t *__restrict__ vals_out, int64_t n_max, const int64_t *__restrict__ n_dev, RadixPass pass, bool drop,
     uint32_t drop_key, int64_t *__restrict__ kept_out, const uint32_t *__restrict__ hist,
@@ -324,8 +350,7 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     uint16_t *const wave_cnt = reinterpret_cast<uint16_t *>(s_mem);
     uint32_t *const s_keys = s_mem, *const s_vals = s_mem + TILE;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int at0 = wave * (TILE / WAVES) + lane;
+    int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, at0 = wave * (TILE / WAVES) + lane;
     uint32_t key[ITEMS], val[ITEMS];
     auto load = [&](int64_t base, int left) {
 #pragma unroll
@@ -348,219 +373,233 @@ __global__ __launch_bounds__(THREADS, SELF || SEG ? 4 : 5) void k_radix_scatter(
     const int64_t n = clamp_count(n_dev, n_max);
     const Digit D = pass_digit(pass);
     const int nb = SEG ? emit_plan(n_dev, n_max, __builtin_ctz(TILE)).blocks : (int)((n + TILE - 1) / TILE);
-    int block = SELF ? (int)blockIdx.x : xcd_block(nb);
-    if (block >= nb) {  // uniform per block
-        if (kept_out && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
-        return;
-    }
-    int64_t base = (int64_t)block * TILE;
-    int todo = (int)min(n - base, (int64_t)TILE);  // items of the block
-    // (SEG) the workgroup's segments, from `block` on, `segs` of them: lane s
-    // holds segment s of the window of kWindow that `block` lies in
-    constexpr int kWindow = 16;
-    uint2 part = make_uint2(0u, 0u);
-    int seg0 = 0, segs = 1;
-    if constexpr (SEG) {
-        const int first = block & ~(kWindow - 1), here = min(nb - first, kWindow);
-        if (lane < here) part = seg[first + lane];
-        seg0 = block - first;
-        todo = (int)__builtin_amdgcn_readlane(part.y, seg0);
-        const int all = (int)__builtin_amdgcn_readlane(wave_inclusive_scan(part.y), kWindow - 1);
-        if (2 * (int64_t)all <= (int64_t)here * TILE) {
-            int group = -1, held = 0;
-            const int want = seg0;
-            segs = todo = 0;
-            for (int s = 0; s < here; ++s) {
-                const int c = (int)__builtin_amdgcn_readlane(part.y, s);
-                if (s == 0 || held + c > TILE) {
-                    ++group;
-                    held = 0;
+    if (kept_out && nb == 0 && blockIdx.x == 0 && tid == 0) *kept_out = 0;
+    constexpr bool ROUNDS = TILE == kLargeTile;
+    const int end = SELF ? nb : xcd_places(nb);
+    for (int place = (int)blockIdx.x; place < end; place += (int)gridDim.x) {
+        if constexpr (ROUNDS) {  // (nothing of one round is kept in registers for the next)
+            asm volatile("" : "+v"(tid));
+            lane = tid & 63, wave = tid >> 6, at0 = wave * (TILE / WAVES) + lane;
+        }
+        int block = SELF ? place : xcd_block(nb, place);
+        if (block >= nb) {  // uniform per block
+            if constexpr (!ROUNDS) return;
+            continue;
+        }
+        int64_t base = (int64_t)block * TILE;
+        int todo = (int)min(n - base, (int64_t)TILE);  // items of the block
+        // (SEG) the workgroup's segments, from `block` on, `segs` of them: lane s
+        // holds segment s of the window of kWindow that `block` lies in
+        constexpr int kWindow = 16;
+        uint2 part = make_uint2(0u, 0u);
+        int seg0 = 0, segs = 1;
+        if constexpr (SEG) {
+            const int first = block & ~(kWindow - 1), here = min(nb - first, kWindow);
+            if (lane < here) part = seg[first + lane];
+            seg0 = block - first;
+            todo = (int)__builtin_amdgcn_readlane(part.y, seg0);
+            const int all = (int)__builtin_amdgcn_readlane(wave_inclusive_scan(part.y), kWindow - 1);
+            if (2 * (int64_t)all <= (int64_t)here * TILE) {
+                int group = -1, held = 0;
+                const int want = seg0;
+                segs = todo = 0;
+                for (int s = 0; s < here; ++s) {
+                    const int c = (int)__builtin_amdgcn_readlane(part.y, s);
+                    if (s == 0 || held + c > TILE) {
+                        ++group;
+                        held = 0;
+                    }
+                    held += c;
+                    if (group == want) {
+                        if (segs == 0) seg0 = s;
+                        ++segs;
+                        todo = held;
+                    }
                 }
-                held += c;
-                if (group == want) {
-                    if (segs == 0) seg0 = s;
-                    ++segs;
-                    todo = held;
+                if (segs == 0) {  // uniform per block
+                    if constexpr (!ROUNDS) return;
+                    continue;
                 }
+                block = first + seg0;
             }
-            if (segs == 0) return;  // uniform per block
-            block = first + seg0;
+            base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(part.x, seg0);
         }
-        base = (int64_t)(uint32_t)__builtin_amdgcn_readlane(part.x, seg0);
-    }
-    // items [from, from + TILE) of the workgroup's
-    auto load_items = [&](int from) {
-        const int left = min(todo - from, TILE);
-        if (!SEG || segs == 1) {
-            load(base + from, left);
-            return;
-        }
-        uint32_t src[ITEMS];
-        uint32_t start = 0;  // items before the segment
-        for (int s = seg0; s < seg0 + segs; ++s) {
-            const uint32_t delta = (uint32_t)__builtin_amdgcn_readlane(part.x, s) - start;
-#pragma unroll
-            for (int r = 0; r < ITEMS; ++r) {
-                const uint32_t i = (uint32_t)(from + min(at0 + r * 64, max(left - 1, 0)));
-                if (s == seg0 || i >= start) src[r] = i + delta;
+        // items [from, from + TILE) of the workgroup's
+        auto load_items = [&](int from) {
+            const int left = min(todo - from, TILE);
+            if (!SEG || segs == 1) {
+                load(base + from, left);
+                return;
             }
-            start += (uint32_t)__builtin_amdgcn_readlane(part.y, s);
-        }
+            uint32_t src[ITEMS];
+            uint32_t start = 0;  // items before the segment
+            for (int s = seg0; s < seg0 + segs; ++s) {
+                const uint32_t delta = (uint32_t)__builtin_amdgcn_readlane(part.x, s) - start;
 #pragma unroll
-        for (int r = 0; r < ITEMS; ++r) key[r] = keys_in[src[r]];
+                for (int r = 0; r < ITEMS; ++r) {
+                    const uint32_t i = (uint32_t)(from + min(at0 + r * 64, max(left - 1, 0)));
+                    if (s == seg0 || i >= start) src[r] = i + delta;
+                }
+                start += (uint32_t)__builtin_amdgcn_readlane(part.y, s);
+            }
 #pragma unroll
-        for (int r = 0; r < ITEMS; ++r) val[r] = vals_in[src[r]];
-    };
-    int from = 0;
-    if constexpr (!kEarly) load_items(0);
-    const int bins = 1 << D.bits;
+            for (int r = 0; r < ITEMS; ++r) key[r] = keys_in[src[r]];
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) val[r] = vals_in[src[r]];
+        };
+        int from = 0;
+        if constexpr (!kEarly) load_items(0);
+        const int bins = 1 << D.bits;
 
-    // output position of each digit's first item of this block
-    if constexpr (SELF) {
-        // each thread sums eight neighbouring digits over every groups-th row
-        const int row = hist_row(bins), octs = row >> 3;
-        const int oct = tid & (octs - 1), group = tid / octs, groups = THREADS / octs;
-        uint32_t all[8] = {}, pre[8] = {};
-        constexpr int kStep = 8;
-        const uint4 *src = reinterpret_cast<const uint4 *>(hist) + oct;
-        for (int r0 = group; r0 < nb; r0 += groups * kStep) {
-            uint4 x[kStep];
+        // output position of each digit's first item of this block
+        if constexpr (SELF) {
+            // each thread sums eight neighbouring digits over every groups-th row
+            const int row = hist_row(bins), octs = row >> 3;
+            const int oct = tid & (octs - 1), group = tid / octs, groups = THREADS / octs;
+            uint32_t all[8] = {}, pre[8] = {};
+            constexpr int kStep = 8;
+            const uint4 *src = reinterpret_cast<const uint4 *>(hist) + oct;
+            for (int r0 = group; r0 < nb; r0 += groups * kStep) {
+                uint4 x[kStep];
 #pragma unroll
-            for (int j = 0; j < kStep; ++j) x[j] = src[(size_t)(min(r0 + j * groups, nb - 1) * octs)];
+                for (int j = 0; j < kStep; ++j) x[j] = src[(size_t)(min(r0 + j * groups, nb - 1) * octs)];
 #pragma unroll
-            for (int j = 0; j < kStep; ++j) {
-                const int r = r0 + j * groups;
-                const uint32_t in = r < nb ? ~0u : 0u, before = r < block ? ~0u : 0u;
-                const uint32_t w[4] = {x[j].x & in, x[j].y & in, x[j].z & in, x[j].w & in};
+                for (int j = 0; j < kStep; ++j) {
+                    const int r = r0 + j * groups;
+                    const uint32_t in = r < nb ? ~0u : 0u, before = r < block ? ~0u : 0u;
+                    const uint32_t w[4] = {x[j].x & in, x[j].y & in, x[j].z & in, x[j].w & in};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t lo = w[q] & 0xffffu, hi = w[q] >> 16;
-                    all[2 * q] += lo;
-                    all[2 * q + 1] += hi;
-                    pre[2 * q] += lo & before;
-                    pre[2 * q + 1] += hi & before;
+                    for (int q = 0; q < 4; ++q) {
+                        const uint32_t lo = w[q] & 0xffffu, hi = w[q] >> 16;
+                        all[2 * q] += lo;
+                        all[2 * q + 1] += hi;
+                        pre[2 * q] += lo & before;
+                        pre[2 * q + 1] += hi & before;
+                    }
                 }
             }
-        }
-        // partial sums [group][digit], all of them and then those before the block
+            // partial sums [group][digit], all of them and then those before the block
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            s_mem4[2 * tid + q] = make_uint4(all[4 * q], all[4 * q + 1], all[4 * q + 2], all[4 * q + 3]);
-            s_mem4[2 * THREADS + 2 * tid + q] = make_uint4(pre[4 * q], pre[4 * q + 1], pre[4 * q + 2], pre[4 * q + 3]);
-        }
-        __syncthreads();
-    }
-    uint32_t dig_carry = 0;
-#pragma unroll 1
-    for (int d0 = 0; d0 < bins; d0 += THREADS) {
-        const int d = d0 + tid;
-        uint32_t pre = 0, all = 0;
-        if (d < bins) {
-            if constexpr (SELF) {
-                const int row = hist_row(bins), groups = 8 * THREADS / row;
-                for (int g = 0; g < groups; ++g) {
-                    all += s_mem[g * row + d];
-                    pre += s_mem[8 * THREADS + g * row + d];
-                }
-            } else {
-                all = row_total[d];
-                pre = hist[(size_t)d * nblocks + block];
+            for (int q = 0; q < 2; ++q) {
+                s_mem4[2 * tid + q] = make_uint4(all[4 * q], all[4 * q + 1], all[4 * q + 2], all[4 * q + 3]);
+                s_mem4[2 * THREADS + 2 * tid + q] = make_uint4(pre[4 * q], pre[4 * q + 1], pre[4 * q + 2], pre[4 * q + 3]);
             }
+            __syncthreads();
         }
-        uint32_t dig_tot;
-        const uint32_t dig_base = dig_carry + block_inclusive_scan<WAVES>(all, smem, &dig_tot) - all;
-        dig_carry += dig_tot;
-        if (d < bins) s_base[d] = dig_base + pre;
-        if (SEG && ranges && block == 0 && d < bins && all != 0u) ranges[d] = make_uint2(dig_base, dig_base + all);
-    }
-    if (kept_out && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
-    const uint32_t n32 = (uint32_t)n;
-    for (;;) {
-        const int left = min(todo - from, TILE);
-        __syncthreads();
-        for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
-        __syncthreads();
-
-        // position of each item among the items of its digit in its wave
-        uint16_t *const cnt = wave_cnt + wave * bins;
-        uint32_t rank[ITEMS];
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const bool valid = at0 + r * 64 < left && !(drop && key[r] == drop_key);
-            const uint32_t d = D.of(key[r]);
-            const uint64_t some = __ballot(valid);
-            uint32_t lo = (uint32_t)some, hi = (uint32_t)(some >> 32);  // lanes of the same digit
-            for (int b = 0; b < D.bits; ++b) {
-                const int32_t bit = (int32_t)(d << (31 - b)) >> 31;  // 0 or all ones
-                const uint64_t m = __ballot(bit != 0);
-                lo &= ~((uint32_t)m ^ (uint32_t)bit);
-                hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
-            }
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-            const uint32_t prior = cnt[d];
-            wave_sync();
-            if (valid && below == 0) cnt[d] = (uint16_t)(prior + (uint32_t)(__popc(lo) + __popc(hi)));
-            wave_sync();
-            rank[r] = valid ? prior + below : 0xffffffffu;
-        }
-        __syncthreads();
-
-        // per digit: prefix over the waves, block-local start
-        uint32_t carry = 0;
+        uint32_t dig_carry = 0;
 #pragma unroll 1
         for (int d0 = 0; d0 < bins; d0 += THREADS) {
             const int d = d0 + tid;
-            uint32_t run = 0;
-            if (d < bins)
-#pragma unroll
-                for (int w = 0; w < WAVES; ++w) {
-                    const uint32_t c = wave_cnt[w * bins + d];
-                    wave_cnt[w * bins + d] = (uint16_t)run;
-                    run += c;
-                }
-            uint32_t tot;
-            const uint32_t start = carry + block_inclusive_scan<WAVES>(run, smem, &tot) - run;
-            carry += tot;
+            uint32_t pre = 0, all = 0;
             if (d < bins) {
-                s_start[d] = (uint16_t)start;
-                s_base[d] -= start;
-            }
-        }
-        const int count = (int)carry;  // items of this tile that stay in the sort
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r)
-            if (rank[r] != 0xffffffffu) {
-                const uint32_t d = D.of(key[r]);
-                rank[r] += (uint32_t)s_start[d] + cnt[d];
-            }
-        __syncthreads();  // the counters give way to the staged items
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r)
-            if (rank[r] != 0xffffffffu) {
-                s_keys[rank[r]] = key[r];
-                s_vals[rank[r]] = val[r];
-            }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const int p = r * THREADS + tid;
-            if (p < count) {
-                const uint32_t k = s_keys[p];
-                const uint32_t dst = s_base[D.of(k)] + (uint32_t)p;
-                if (dst < n32) {
-                    keys_out[dst] = k;
-                    vals_out[dst] = s_vals[p];
+                if constexpr (SELF) {
+                    const int row = hist_row(bins), groups = 8 * THREADS / row;
+                    for (int g = 0; g < groups; ++g) {
+                        all += s_mem[g * row + d];
+                        pre += s_mem[8 * THREADS + g * row + d];
+                    }
+                } else {
+                    all = row_total[d];
+                    pre = hist[(size_t)d * nblocks + block];
                 }
             }
+            uint32_t dig_tot;
+            const uint32_t dig_base = dig_carry + block_inclusive_scan<WAVES>(all, smem, &dig_tot) - all;
+            dig_carry += dig_tot;
+            if (d < bins) s_base[d] = dig_base + pre;
+            if (SEG && ranges && block == 0 && d < bins && all != 0u) ranges[d] = make_uint2(dig_base, dig_base + all);
         }
-        from += TILE;
-        if (!SEG || from >= todo) break;  // uniform per block
-        load_items(from);
-        // the digits' next positions: past this tile's items
+        if (kept_out && block == 0 && tid == 0) *kept_out = (int64_t)dig_carry;
+        const uint32_t n32 = (uint32_t)n;
+        for (;;) {
+            const int left = min(todo - from, TILE);
+            __syncthreads();
+            for (int i = tid; i < WAVES * bins / 2; i += THREADS) s_mem[i] = 0u;
+            __syncthreads();
+
+            // position of each item among the items of its digit in its wave
+            uint16_t *const cnt = wave_cnt + wave * bins;
+            uint32_t rank[ITEMS];
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) {
+                const bool valid = at0 + r * 64 < left && !(drop && key[r] == drop_key);
+                const uint32_t d = D.of(key[r]);
+                const uint64_t some = __ballot(valid);
+                uint32_t lo = (uint32_t)some, hi = (uint32_t)(some >> 32);  // lanes of the same digit
+                for (int b = 0; b < D.bits; ++b) {
+                    const int32_t bit = (int32_t)(d << (31 - b)) >> 31;  // 0 or all ones
+                    const uint64_t m = __ballot(bit != 0);
+                    lo &= ~((uint32_t)m ^ (uint32_t)bit);
+                    hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)bit);
+                }
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+                const uint32_t prior = cnt[d];
+                wave_sync();
+                if (valid && below == 0) cnt[d] = (uint16_t)(prior + (uint32_t)(__popc(lo) + __popc(hi)));
+                wave_sync();
+                rank[r] = valid ? prior + below : 0xffffffffu;
+            }
+            __syncthreads();
+
+            // per digit: prefix over the waves, block-local start
+            uint32_t carry = 0;
+#pragma unroll 1
+            for (int d0 = 0; d0 < bins; d0 += THREADS) {
+                const int d = d0 + tid;
+                uint32_t run = 0;
+                if (d < bins)
+#pragma unroll
+                    for (int w = 0; w < WAVES; ++w) {
+                        const uint32_t c = wave_cnt[w * bins + d];
+                        wave_cnt[w * bins + d] = (uint16_t)run;
+                        run += c;
+                    }
+                uint32_t tot;
+                const uint32_t start = carry + block_inclusive_scan<WAVES>(run, smem, &tot) - run;
+                carry += tot;
+                if (d < bins) {
+                    s_start[d] = (uint16_t)start;
+                    s_base[d] -= start;
+                }
+            }
+            const int count = (int)carry;  // items of this tile that stay in the sort
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r)
+                if (rank[r] != 0xffffffffu) {
+                    const uint32_t d = D.of(key[r]);
+                    rank[r] += (uint32_t)s_start[d] + cnt[d];
+                }
+            __syncthreads();  // the counters give way to the staged items
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r)
+                if (rank[r] != 0xffffffffu) {
+                    s_keys[rank[r]] = key[r];
+                    s_vals[rank[r]] = val[r];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) {
+                const int p = r * THREADS + tid;
+                if (p < count) {
+                    const uint32_t k = s_keys[p];
+                    const uint32_t dst = s_base[D.of(k)] + (uint32_t)p;
+                    if (dst < n32) {
+                        keys_out[dst] = k;
+                        vals_out[dst] = s_vals[p];
+                    }
+                }
+            }
+            from += TILE;
+            if (!SEG || from >= todo) break;  // uniform per block
+            load_items(from);
+            // the digits' next positions: past this tile's items
+            __syncthreads();
+            for (int d = tid; d < bins; d += THREADS)
+                s_base[d] += d + 1 < bins ? (uint32_t)s_start[d + 1] : (uint32_t)count;
+        }
+        if constexpr (!ROUNDS) return;
         __syncthreads();
-        for (int d = tid; d < bins; d += THREADS)
-            s_base[d] += d + 1 < bins ? (uint32_t)s_start[d + 1] : (uint32_t)count;
     }
 }
 
@@ -1057,119 +1096,128 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit(
         for (int64_t i = at; i < clear_b_words; i += stride) clear_b[i] = 0u;
     }
     const EmitPlan P = emit_plan(counters, capacity, __builtin_ctz(TILE));
-    const int block = SELF ? (int)blockIdx.x : xcd_block(P.blocks);
-    if (block >= P.blocks) return;  // uniform per block
-    const Digit D = pass_digit(pass);
-    const int bins = 1 << D.bits;
-    for (int i = tid; i < bins; i += kEmitThreads) cnt[i] = 0u;
-    const uint32_t kept = (uint32_t)counters[4];
-    const uint32_t row_first = (uint32_t)block * (uint32_t)P.rows;
-    const uint32_t row_end = (uint32_t)min((int64_t)row_first + P.rows, P.rows_all);
-    const int sshift = __builtin_ctz((unsigned)P.step);
-    // box offset of the block's first row
-    const uint2 start = steps[row_first >> sshift];
-    const uint2 start_box = sorted_boxes[start.x];
-    const uint32_t base =
-        offsets[start.x] + start.y * ((start_box.x >> 16 >> LW) - ((start_box.x & 0xffffu) >> LW) + 1u);
-    __syncthreads();
-    uint32_t(*const G)[64] = s_g[wave];
-    uint32_t(*const Rw)[64] = s_r[wave];
-    uint32_t *const slots = s_slots[wave];
-    uint32_t out = 0u;
-    int turn = 0;
-    for (uint32_t r0 = row_first; r0 < row_end; r0 += WAVES * P.step, turn ^= 1) {
-        const uint32_t mine = r0 + (uint32_t)(wave * P.step);  // first row of the wave's step
-        const int n_rows = mine < row_end ? min(P.step, (int)(row_end - mine)) : 0;
-        uint32_t listed = 0u;
-        if (n_rows) {
-            // the Gaussian-views of the step's rows, from the one that its first row belongs to
-            const uint2 first = steps[mine >> sshift];
-            const uint32_t k = min(first.x + (uint32_t)lane, kept - 1u);
-            const uint32_t id = order[k];
-            const uint2 box = sorted_boxes[k];
-            const uint32_t skip = lane == 0 ? first.y : 0u;
-            const uint32_t rows = first.x + lane < kept ? (box.y >> 16 >> LH) - ((box.y & 0xffffu) >> LH) + 1u - skip : 0u;
-            const uint32_t g_start = wave_inclusive_scan(rows) - rows;
-            G[0][lane] = id;
-            G[1][lane] = box.x;
-            G[2][lane] = box.y;
-            G[3][lane] = skip - g_start;  // row of the box = row of the step + this
-            const int g = unit_owner(g_start, rows, 0u, 0, slots);
-            if (lane < n_rows) {
-                const uint32_t gid = G[0][g];
-                const Conic C = conics[gid];
-                const PixelBox pb = unpack_box(make_uint2(G[1][g], G[2][g]));
-                const int ty = (pb.y0 >> LH) + (int)(lane + G[3][g]);
-                const DevView &V = views[gid / (uint32_t)n];
-                const uint32_t tile0 = (uint32_t)V.tile_base + (uint32_t)(ty * V.tiles_x);
-                const ConicFrame F = conic_frame(C);
-                BandRanges B;
-                band_ranges(C, F, pb, ty, TW, TH, B);
-                int pa, pe;
-                pixel_extent(B.row_xl, B.row_xr, C.u0, pb.x0, pb.x1, pa, pe);
-                const int ta = max(pb.x0, pa) >> LW, tb = min(pb.x1, pe) >> LW;
-                if (B.row_valid && pa <= pb.x1 && pe >= pb.x0 && ta <= tb) {
-                    listed = (uint32_t)(tb - ta + 1);
-                    Rw[0][lane] = tile0 + (uint32_t)ta;
-                    Rw[1][lane] = gid;
+    constexpr bool ROUNDS = TILE == kLargeTile;
+    const int end = SELF ? P.blocks : xcd_places(P.blocks);
+    for (int place = (int)blockIdx.x; place < end; place += (int)gridDim.x) {
+        const int block = SELF ? place : xcd_block(P.blocks, place);
+        if (block >= P.blocks) {  // uniform per block
+            if constexpr (!ROUNDS) return;
+            continue;
+        }
+        const Digit D = pass_digit(pass);
+        const int bins = 1 << D.bits;
+        for (int i = tid; i < bins; i += kEmitThreads) cnt[i] = 0u;
+        const uint32_t kept = (uint32_t)counters[4];
+        const uint32_t row_first = (uint32_t)block * (uint32_t)P.rows;
+        const uint32_t row_end = (uint32_t)min((int64_t)row_first + P.rows, P.rows_all);
+        const int sshift = __builtin_ctz((unsigned)P.step);
+        // box offset of the block's first row
+        const uint2 start = steps[row_first >> sshift];
+        const uint2 start_box = sorted_boxes[start.x];
+        const uint32_t base =
+            offsets[start.x] + start.y * ((start_box.x >> 16 >> LW) - ((start_box.x & 0xffffu) >> LW) + 1u);
+        __syncthreads();
+        uint32_t(*const G)[64] = s_g[wave];
+        uint32_t(*const Rw)[64] = s_r[wave];
+        uint32_t *const slots = s_slots[wave];
+        uint32_t out = 0u;
+        int turn = 0;
+        for (uint32_t r0 = row_first; r0 < row_end; r0 += WAVES * P.step, turn ^= 1) {
+            const uint32_t mine = r0 + (uint32_t)(wave * P.step);  // first row of the wave's step
+            const int n_rows = mine < row_end ? min(P.step, (int)(row_end - mine)) : 0;
+            uint32_t listed = 0u;
+            if (n_rows) {
+                // the Gaussian-views of the step's rows, from the one that its first row belongs to
+                const uint2 first = steps[mine >> sshift];
+                const uint32_t k = min(first.x + (uint32_t)lane, kept - 1u);
+                const uint32_t id = order[k];
+                const uint2 box = sorted_boxes[k];
+                const uint32_t skip = lane == 0 ? first.y : 0u;
+                const uint32_t rows = first.x + lane < kept ? (box.y >> 16 >> LH) - ((box.y & 0xffffu) >> LH) + 1u - skip : 0u;
+                const uint32_t g_start = wave_inclusive_scan(rows) - rows;
+                G[0][lane] = id;
+                G[1][lane] = box.x;
+                G[2][lane] = box.y;
+                G[3][lane] = skip - g_start;  // row of the box = row of the step + this
+                const int g = unit_owner(g_start, rows, 0u, 0, slots);
+                if (lane < n_rows) {
+                    const uint32_t gid = G[0][g];
+                    const Conic C = conics[gid];
+                    const PixelBox pb = unpack_box(make_uint2(G[1][g], G[2][g]));
+                    const int ty = (pb.y0 >> LH) + (int)(lane + G[3][g]);
+                    const DevView &V = views[gid / (uint32_t)n];
+                    const uint32_t tile0 = (uint32_t)V.tile_base + (uint32_t)(ty * V.tiles_x);
+                    const ConicFrame F = conic_frame(C);
+                    BandRanges B;
+                    band_ranges(C, F, pb, ty, TW, TH, B);
+                    int pa, pe;
+                    pixel_extent(B.row_xl, B.row_xr, C.u0, pb.x0, pb.x1, pa, pe);
+                    const int ta = max(pb.x0, pa) >> LW, tb = min(pb.x1, pe) >> LW;
+                    if (B.row_valid && pa <= pb.x1 && pe >= pb.x0 && ta <= tb) {
+                        listed = (uint32_t)(tb - ta + 1);
+                        Rw[0][lane] = tile0 + (uint32_t)ta;
+                        Rw[1][lane] = gid;
+#pragma unroll
+                        for (int q = 0; q < NR; ++q) {
+                            // slot columns [lo, hi) from tile ta's first on
+                            uint32_t cols = 0u;
+                            if ((B.valid >> q) & 1u) {
+                                int qa = pa, qe = pe;
+                                if (NR > 1) pixel_extent(B.xl[q], B.xr[q], C.u0, pb.x0, pb.x1, qa, qe);
+                                if (qa <= pb.x1 && qe >= pb.x0) {
+                                    const int c0 = max(max(pb.x0, qa) >> LC, ta * BX);
+                                    const int c1 = min(min(pb.x1, qe) >> LC, tb * BX + BX - 1);
+                                    if (c0 <= c1) cols = (uint32_t)(c0 - ta * BX) | (uint32_t)(c1 + 1 - ta * BX) << 16;
+                                }
+                            }
+                            Rw[2 + q][lane] = cols;
+                        }
+                    }
+                }
+            }
+            const uint32_t r_end = wave_inclusive_scan(listed), r_start = r_end - listed;
+            const uint32_t n_listed = __builtin_amdgcn_readlane(r_end, 63);
+            if (lane == 0) s_listed[turn][wave] = n_listed;
+            __syncthreads();
+            uint32_t at = base + out;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const uint32_t x = s_listed[turn][w];
+                at += w < wave ? x : 0u;
+                out += x;
+            }
+            int r_before = 0;
+            for (uint32_t ebase = 0; ebase < n_listed; ebase += 64u) {
+                const int r = unit_owner(r_start, listed, ebase, r_before, slots);
+                r_before = __builtin_amdgcn_readlane(r, 63);
+                const uint32_t e = ebase + lane;
+                const uint32_t j = e - (uint32_t)__shfl((int)r_start, r, 64);
+                if (e < n_listed) {
+                    const uint32_t tile = Rw[0][r] + j;
+                    uint32_t bands = 0u;
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
-                        // slot columns [lo, hi) from tile ta's first on
-                        uint32_t cols = 0u;
-                        if ((B.valid >> q) & 1u) {
-                            int qa = pa, qe = pe;
-                            if (NR > 1) pixel_extent(B.xl[q], B.xr[q], C.u0, pb.x0, pb.x1, qa, qe);
-                            if (qa <= pb.x1 && qe >= pb.x0) {
-                                const int c0 = max(max(pb.x0, qa) >> LC, ta * BX);
-                                const int c1 = min(min(pb.x1, qe) >> LC, tb * BX + BX - 1);
-                                if (c0 <= c1) cols = (uint32_t)(c0 - ta * BX) | (uint32_t)(c1 + 1 - ta * BX) << 16;
-                            }
+                        const uint32_t cols = Rw[2 + q][r], lo = cols & 0xffffu, hi = cols >> 16;
+#pragma unroll
+                        for (int c = 0; c < BX; ++c) {
+                            const uint32_t col = j * BX + c;
+                            if (col >= lo && col < hi) bands |= 1u << (q * BX + c);
                         }
-                        Rw[2 + q][lane] = cols;
                     }
+                    inst_tiles[at + e] = tile;
+                    inst_ids[at + e] = Rw[1][r] | (SL.bits ? bands << kIdBits : 0u);
+                    atomicAdd(&cnt[D.of(tile)], 1u);
                 }
             }
         }
-        const uint32_t r_end = wave_inclusive_scan(listed), r_start = r_end - listed;
-        const uint32_t n_listed = __builtin_amdgcn_readlane(r_end, 63);
-        if (lane == 0) s_listed[turn][wave] = n_listed;
         __syncthreads();
-        uint32_t at = base + out;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            const uint32_t x = s_listed[turn][w];
-            at += w < wave ? x : 0u;
-            out += x;
-        }
-        int r_before = 0;
-        for (uint32_t ebase = 0; ebase < n_listed; ebase += 64u) {
-            const int r = unit_owner(r_start, listed, ebase, r_before, slots);
-            r_before = __builtin_amdgcn_readlane(r, 63);
-            const uint32_t e = ebase + lane;
-            const uint32_t j = e - (uint32_t)__shfl((int)r_start, r, 64);
-            if (e < n_listed) {
-                const uint32_t tile = Rw[0][r] + j;
-                uint32_t bands = 0u;
-#pragma unroll
-                for (int q = 0; q < NR; ++q) {
-                    const uint32_t cols = Rw[2 + q][r], lo = cols & 0xffffu, hi = cols >> 16;
-#pragma unroll
-                    for (int c = 0; c < BX; ++c) {
-                        const uint32_t col = j * BX + c;
-                        if (col >= lo && col < hi) bands |= 1u << (q * BX + c);
-                    }
-                }
-                inst_tiles[at + e] = tile;
-                inst_ids[at + e] = Rw[1][r] | (SL.bits ? bands << kIdBits : 0u);
-                atomicAdd(&cnt[D.of(tile)], 1u);
-            }
-        }
+        if (tid == 0) seg[block] = make_uint2(base, out);
+        const int row = SELF ? hist_row(bins) : bins;
+        for (int d = tid; d < row; d += kEmitThreads)
+            put_count<SELF>(hist, bins, nblocks, block, d, d < bins ? cnt[d] : 0u);
+        if constexpr (!ROUNDS) return;
+        __syncthreads();
     }
-    __syncthreads();
-    if (tid == 0) seg[block] = make_uint2(base, out);
-    const int row = SELF ? hist_row(bins) : bins;
-    for (int d = tid; d < row; d += kEmitThreads)
-        put_count<SELF>(hist, bins, nblocks, block, d, d < bins ? cnt[d] : 0u);
 }
 
 // ------------------------------------------------------------ tile ranges
@@ -1383,7 +1431,7 @@ namespace {
 // kMidMax blocks stay small, so that there are enough of them (1.5M tile ids: 42
 // us, 49 us at twice the items); above, larger blocks write longer runs (22.5M depth keys
 // and 66M tile ids: 1.44 ms, 1.66 ms at half the items).
-constexpr int kSortThreads = 512, kSmallItems = 4, kLargeItems = 8;
+constexpr int kSortThreads = 512, kSmallItems = 4, kLargeItems = kLargeTile / kSortThreads;
 constexpr int64_t kSelfMax = int64_t(1) << 19, kMidMax = int64_t(1) << 23;
 
 int block_items(int64_t n_max) { return kSortThreads * (n_max <= kMidMax ? kSmallItems : kLargeItems); }
@@ -1393,9 +1441,10 @@ int tile_shift(int64_t n_max) { return __builtin_ctz((unsigned)block_items(n_max
 }  // namespace
 
 namespace {
-// Workgroups that reach every block of xcd_block for any nb up to nblocks: its
+// Places that reach every block of xcd_block for any nb up to nblocks: its
 // last round of runs may be partly empty (8 runs of at most 64 or nb / 64 blocks).
 int xcd_grid(int nblocks) { return (nblocks + std::min(512, nblocks / 8) + 15) & ~7; }
+constexpr int kMaxGrid = 4096, kMaxEmitGrid = 8192;  // of a large sort
 
 // The widest digit of any pass of a sort on `bits` bits; with a key range the
 // first pass has kFirstBits bits and the others up to the widest.
@@ -1425,14 +1474,15 @@ void radix_pass(const uint32_t *ki, const uint32_t *vi, uint32_t *ko, uint32_t *
                 const RadixRange *top, const uint2 *seg, uint2 *ranges, uint32_t *scratch, hipStream_t stream)
 {
     constexpr int tile = TH * IT;
-    const int nblocks = (int)((n_max + tile - 1) / tile), grid = xcd_grid(nblocks);
+    const int nblocks = (int)((n_max + tile - 1) / tile), all = xcd_grid(nblocks);
+    const int grid = tile == kLargeTile ? std::min(all, kMaxGrid) : all;
     uint32_t *const hist = scratch, *const row_total = scratch + (size_t)wide * nblocks;
     // the first histogram launch also finds the largest key, in one more
     // workgroup; the emission has made the histogram of its segments
     if (!seg)
         k_radix_hist<TH, IT, SELF><<<grid + (top ? 1 : 0), TH, 0, stream>>>(
-            ki, n_max, pn, pass, drop, drop_key, hist, nblocks, top ? top->part_max : nullptr, top ? top->n_parts : 0,
-            top ? top->kmax : nullptr);
+            ki, n_max, pn, pass, drop, drop_key, hist, nblocks, grid, top ? top->part_max : nullptr,
+            top ? top->n_parts : 0, top ? top->kmax : nullptr);
     if (!SELF) k_radix_scan_rows<<<wide, kThreads, 0, stream>>>(hist, nblocks, n_max, pn, pass, tile, seg != nullptr,
                                                                row_total);
     const auto scatter = seg ? &k_radix_scatter<TH, IT, SELF, true> : &k_radix_scatter<TH, IT, SELF, false>;
@@ -1570,7 +1620,8 @@ hipError_t emit_and_sort(const uint32_t *order, const uint32_t *offsets, uint32_
     if (!emit)
         return sort_passes(tiles, ids, tiles_alt, ids_alt, capacity, counters, tile_bits, nullptr, false, 0u, listed,
                            false, seg, ranges, hist, stream);
-    const int nblocks = (int)emit_blocks(capacity), grid = xcd_grid(nblocks);
+    const int nblocks = (int)emit_blocks(capacity), all = xcd_grid(nblocks);
+    const int grid = capacity > kMidMax ? std::min(all, kMaxEmitGrid) : all;
     const RadixPass pass{nullptr, 0u, tile_bits, 0, radix_passes(tile_bits)};
     // runs even with no Gaussian: it clears the ranges and scheduling words
 #define RGS_EMIT_SEG(W, H, SEG, SELF)                                                                                 \

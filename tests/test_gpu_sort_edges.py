@@ -1,5 +1,6 @@
 """Depth and tile sorts on both sides of the sizes where a launch changes shape: 2^19 items (above, histograms are
-scanned in a launch of their own) and 2^23 (above, blocks of 4096 items), and more than 2^22 tiles (ids of three digits)."""
+scanned in a launch of their own) and 2^23 (above, blocks of 4096 items), more than 2^22 tiles (ids of three digits),
+and more blocks of either sort than its launches have workgroups."""
 import pytest
 import torch
 
@@ -13,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,depths,w,h,views", [((1 << 19) - 1, "wide", 640, 480, 1), (1 << 19, "wide", 640, 480, 1),
                                                 ((1 << 19) + 1, "linear", 640, 480, 1), (1 << 21, "wide", 320, 240, 4),
                                                 (((1 << 23) + 1) // 3, "wide", 320, 240, 3),
-                                                (3000, "linear", 16384, 16384, 1)])
+                                                (3000, "linear", 16384, 16384, 1),
+                                                # more blocks than a launch has workgroups
+                                                (2_900_001, "wide", 320, 240, 6)])
 def test_depth_sort_and_tile_digits(r, n, depths, w, h, views):  # noqa: F811
     base.test_sorted_order_and_lists(r, n, depths, w, h, views)
 
@@ -25,7 +28,7 @@ def test_lists_by_capacity(r):  # noqa: F811
                height=480)
     opts = dict(tile_w=8, tile_h=8)
     want = None
-    for cap in (1 << 19, (1 << 19) + 1, 1 << 23, (1 << 23) + 1):
+    for cap in (1 << 19, (1 << 19) + 1, 1 << 23, (1 << 23) + 1, 1 << 26):
         say(f"case lists at capacity {cap}")
         buf, ws = r.new_workspace(20000, [cam], cap, 0, opts)
         r.render_into(g, [cam], r.allocate_outputs([cam]), ws, opts)
