@@ -1126,12 +1126,14 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 // takes a quarter, first only for the product of 1 / (1 - alpha) and the sum of the colour term over it, from which
 // follows the state that the others leave it.  The second test costs a third of the walk.
 // With A the list entries of all items by the waves of the launch, sharing can pay only where a list takes a wave
-// well beyond A: no list is shared where the longest is shorter than 3/2 A, and otherwise each workgroup shares lists, which
+// well beyond A: no list is shared where the longest is shorter than 3/2 A and kTeamBackwardLen more (a shared item's
+// barriers and second reads cost as much as some tens of entries), and otherwise each workgroup shares lists, which
 // come in decreasing length, until one is shorter than kTeamBackwardLen or 2/3 A.  Every list by one wave -> each
-// workgroup's first list and those above 57, 1746 and 944 entries shared -> this rule:
+// workgroup's first list and those above 57, 1746, 944 and 64 entries shared -> this rule:
 //   two views of 801x533, A 91, longest 516                     302 ->  187 ->  185 us
 //   three of 653x541 full of needles, A 3734, longest 2999     3460 -> 4320 -> 3200 us
 //   one of 1000x1000 with 16x16 tiles, A 2208, longest 1836     800 ->  857 ->  675 us
+//   one of 1221x787 with 16x32 tiles, A 58, longest 90           440 ->  537 ->  350 us
 // The two views with 80 in place of 64 185 us, with A in place of 2/3 A 200 us.
 constexpr uint32_t kTeamBackwardLen = 64;
 // Smallest transmittance behind a shared list.  A share's product is at most the inverse of it, and the colour term's
@@ -1165,8 +1167,9 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
     const uint32_t average =
         (uint32_t)(*reinterpret_cast<const unsigned long long *>(n_items_p + 2) / (4u * gridDim.x));
     const uint32_t team_len = max(kTeamBackwardLen, average / 3u * 2u);
-    bool begun = false, team = n_items_p[4] >= average / 2u * 3u;  // the whole workgroup is on one item
-    const int takers = team ? 1 : 4;                               // of a workgroup
+    // the whole workgroup is on one item
+    bool begun = false, team = n_items_p[4] >= average / 2u * 3u + kTeamBackwardLen;
+    const int takers = team ? 1 : 4;  // of a workgroup
     for (;;) {
         int64_t slot;
         if (team) {
