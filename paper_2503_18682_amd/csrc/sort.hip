@@ -1282,10 +1282,14 @@ constexpr int kSchedBuckets = 256;
 constexpr int kSplitBuckets = 64;  // the buckets of split tiles, above those of all others
 constexpr int64_t kRangeBlocks = 4096;
 
+// Lists of whole tiles: steps of 4 entries up to 512, then of 32 up to 2560.  In dense frames only lists above the
+// average work of a wave are split, and with one bucket for all whole tiles above 764 entries the longest came in
+// any order: six views of up to 2209x2179, lists of up to 2826 entries, 2600 us of compositing, 2030 us with these.
 __device__ __forceinline__ uint32_t work_bucket(uint32_t len, uint32_t parts)
 {
-    return parts == 2u ? (uint32_t)(kSchedBuckets - kSplitBuckets) + min(len >> 5, (uint32_t)(kSplitBuckets - 1))
-                       : min(len >> 2, (uint32_t)(kSchedBuckets - kSplitBuckets - 1));
+    if (parts == 2u)
+        return (uint32_t)(kSchedBuckets - kSplitBuckets) + min(len >> 5, (uint32_t)(kSplitBuckets - 1));
+    return len < 512u ? len >> 2 : min(128u + ((len - 512u) >> 5), (uint32_t)(kSchedBuckets - kSplitBuckets - 1));
 }
 
 // average work of a wave
