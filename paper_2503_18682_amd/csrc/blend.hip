@@ -1125,16 +1125,20 @@ __global__ __launch_bounds__(256) void k_blend_bwd(const uint2 *__restrict__ ran
 // bound it (1.7 waves per SIMD on average), so at first the four waves of a workgroup share a list: each
 // takes a quarter, first only for the product of 1 / (1 - alpha) and the sum of the colour term over it, from which
 // follows the state that the others leave it.  The second test costs a third of the walk.
-// With A the list entries of all items by the waves of the launch, sharing can pay only where a list takes a wave
-// well beyond A: no list is shared where the longest is shorter than 3/2 A and kTeamBackwardLen more (a shared item's
-// barriers and second reads cost as much as some tens of entries), and otherwise each workgroup shares lists, which
-// come in decreasing length, until one is shorter than kTeamBackwardLen or 2/3 A.  Every list by one wave -> each
-// workgroup's first list and those above 57, 1746, 944 and 64 entries shared -> this rule:
-//   two views of 801x533, A 91, longest 516                     302 ->  187 ->  185 us
-//   three of 653x541 full of needles, A 3734, longest 2999     3460 -> 4320 -> 3200 us
-//   one of 1000x1000 with 16x16 tiles, A 2208, longest 1836     800 ->  857 ->  675 us
-//   one of 1221x787 with 16x32 tiles, A 58, longest 90           440 ->  537 ->  350 us
-// The two views with 80 in place of 64 185 us, with A in place of 2/3 A 200 us.
+// With A the list entries of all items by the waves of the launch: a wave that is left alone with the longest list goes
+// about three times as fast as among others, so it ends last only where that list is several times A.  With more
+// items than waves, lists are shared where the longest is at least 4 A, down to 2/3 A; with fewer, waves would
+// stand idle, and all lists from kTeamBackwardLen entries on are shared where the longest is above 3/2 A and 24
+// entries more (a shared item's barriers and second reads).  Every list by one wave -> shared:
+//   items by waves 0.06, 131x133 pixels, longest 77 A            512 ->  260 us
+//   0.49, 606x320, 2.3 A                                         154 ->  123 us
+//   2.0, four views of 747x647, 20 A                             138 ->   72 us
+//   2.3, two views of 801x533, 5.7 A                             299 ->  185 us
+//   1.7, two views of 1191x731, 2.5 A                            432 ->  500 us
+//   1.8, one view of 1102x807, 2.3 A                            1265 -> 1600 us
+//   3.3, three views of 653x541 full of needles, 0.8 A          3320 -> 3720 us
+//   6.9, three views of 1600x1100, 3.9 A                        2313 -> 2433 us
+// The two views of 801x533 with lists down to 80 in place of 64 185 us, down to A 200 us.
 constexpr uint32_t kTeamBackwardLen = 64;
 // Smallest transmittance behind a shared list.  A share's product is at most the inverse of it, and the colour term's
 // sum that times the upstream gradient; behind an opaque stack and without a stopping threshold the
@@ -1164,11 +1168,12 @@ __global__ __launch_bounds__(256) void k_blend_bwd_exact(const uint2 *__restrict
     __shared__ float2 s_share[4][PPL][64];
     __shared__ uint32_t s_ticket;
     const int64_t n_items = *n_items_p;
-    const uint32_t average =
-        (uint32_t)(*reinterpret_cast<const unsigned long long *>(n_items_p + 2) / (4u * gridDim.x));
-    const uint32_t team_len = max(kTeamBackwardLen, average / 3u * 2u);
-    // the whole workgroup is on one item
-    bool begun = false, team = n_items_p[4] >= average / 2u * 3u + kTeamBackwardLen;
+    // the whole workgroup is on one item: as the lists' lengths are, see above
+    const unsigned long long entries = *reinterpret_cast<const unsigned long long *>(n_items_p + 2);
+    const uint32_t waves = 4u * gridDim.x, average = (uint32_t)(entries / waves);
+    const bool few = n_items <= waves;
+    const uint32_t team_len = max(kTeamBackwardLen, few ? 0u : average / 3u * 2u);
+    bool begun = false, team = n_items_p[4] >= (few ? average / 2u * 3u + 24u : 4u * average);
     const int takers = team ? 1 : 4;  // of a workgroup
     for (;;) {
         int64_t slot;
