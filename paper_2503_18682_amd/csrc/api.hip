@@ -568,8 +568,8 @@ rgs_status enqueue_forward(rgs_context *ctx, const rgs_gaussians &g, int n_views
     const uint32_t split_min = slot_layout(s.w, s.h).slots >= 2 ? (mode.team ? kTeamSplitLen : kSplitLen) : 0u;
     const int blend_blocks = ctx->grid_fwd[mode.kernel()][shape_index(s)];
     const uint32_t waves = (uint32_t)(mode.waves() * blend_blocks);
-    // (read by the exact MIP backward pass)
-    const bool sums = opts.mip == 2 && L.record_grads != 0;
+    // (read by the exact MIP passes)
+    const bool sums = opts.mip == 2;
     RGS_HIP(ctx, launch_tile_ranges(inst_tiles, listed, L.capacity, L.total_tiles, L.tile_bits, split_min, waves, sums,
                                     ranges, sched, at<uint32_t>(ws, L.tile_order), stream));
     tm.mark(ST_RANGES);

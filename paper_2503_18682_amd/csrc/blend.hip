@@ -176,7 +176,7 @@ __device__ __forceinline__ void put_test_form(float4 *dst, const float4 (&r)[4],
 // record above (with or without the approximate MIP of eq. 17, which only
 // changes the record's values); ExactMipModel evaluates the exact MIP weight.
 struct PlainModel {
-    static constexpr bool kPriority = true;
+    static constexpr bool kPriority = true, kTeamRule = false;
     static constexpr int kRaw = 4, kStaged = 4;
     using Rec = TRec;
     using F = Frag;
@@ -263,6 +263,7 @@ struct XFrag {
 };
 
 struct ExactMipModel {
+    static constexpr bool kTeamRule = true;
     static constexpr bool kPriority = false;  // 329 us with, 313 us without, for two views of 1032x1104
     static constexpr int kRaw = 7, kStaged = 8;
     using Rec = XRec;
@@ -644,9 +645,15 @@ __global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) v
     // Units of work: the split tiles, and all the others after them if asked for.  Teams shorten
     // the few longest lists, so no more of them than half the workgroups (two views of 1032x1104
     // with exact MIP, 1217 split tiles of 17802: 272 us; 289 with as many as workgroups, 319 with all), and
-    // none where most lists are long alike (a wall close by, 1770 tiles: 52 us, with teams 72).
+    // none where most lists are long alike (a wall close by, 1770 tiles: 52 us, with teams 72), or, with exact MIP, where
+    // the longest is below three times the average work of a wave (2.7 times, 1400x1000: 161 -> 144 us; without
+    // teams at 4.1 times 165 -> 195 us).
     int64_t n_split = n_items_p[1] >> 1;
     const int64_t most = (gridDim.x + 1) / 2;
+    if (M::kTeamRule && !all_tiles) {
+        const unsigned long long entries = *reinterpret_cast<const unsigned long long *>(n_items_p + 2);
+        if ((unsigned long long)n_items_p[4] * (kTeamWaves * gridDim.x) < 3u * entries) n_split = 0;
+    }
     if (!all_tiles && n_split > most) n_split = 2 * n_split > P.total_tiles ? 0 : most;
     const int64_t n_units = all_tiles ? (int64_t)n_items_p[0] - n_split : n_split;
     const bool composer = wave < PPL, stager = wave == kTeamWaves - 1 && lane < B;
@@ -699,6 +706,9 @@ __global__ __launch_bounds__(kTeamThreads, (team_waves_per_simd<TW, TH, M>())) v
         // step: all that a step writes is read in the next one, and written again
         // in the one after that.
         int rb = 0;  // record buffer of batch b
+        // (two views of 801x533 with exact MIP take 65 us with the loop's code 8 or 16 bytes past a multiple of 32, 74 us
+        // at 0 or 24)
+        if constexpr (PPL > 1) asm volatile(".p2align 5\ns_nop 0\ns_nop 0");
         for (int b = 0; b <= n_batches; ++b) {
             __syncthreads();
             uint32_t live = 0u;
