@@ -615,7 +615,8 @@ __device__ __forceinline__ void blend_items(const uint2 *__restrict__ ranges, co
 // Four waves that took turns (alphas, barrier, compositing) came to 39 us at 128x128.
 constexpr int kTeamThreads = 512, kTeamWaves = kTeamThreads / 64;
 
-// Two workgroups on a CU, or three where at most six registers spill for it (plain model, two slots: 88 -> 80).
+// Two workgroups on a CU, or three where few registers spill for it (plain model: 7 of 88 with two slots, 32 bytes
+// of scratch a lane; 4 with one).
 template <int TW, int TH, class M>
 constexpr int team_waves_per_simd()
 {
@@ -1451,11 +1452,15 @@ bool tile_shape_supported(int w, int h)
 
 #define RGS_SHAPES(X) X(8, 8) X(8, 16) X(8, 32) X(16, 8) X(16, 16) X(16, 32) X(32, 8) X(32, 16) X(32, 32)
 
-// Where teams are taken.  Exact MIP always gains, as the team kernel costs it no
-// occupancy (4 waves per SIMD either way): 122 -> 72 us at 6868 tiles, 535 -> 272 us at 17802.
+// Where the team kernel is taken.  With exact MIP always: it holds 4 waves per SIMD, as k_blend does with two pixel
+// slots (5 with one, 3 with four): 122 -> 72 us at 6868 tiles, 535 -> 272 us at 17802; one slot, 1000x1000 pixels,
+// 159 -> 142 and 353 -> 318 us.  Where lists are alike it forms no teams (see there).  Frames that are nearly empty
+// pay: six views of 2452x2465 with 1069 Gaussians, 8x32 tiles, 611 -> 665 us.
 // The plain kernel goes from 7 to 6 waves per SIMD, and gains only where few long
 // lists bound the frame: 63 -> 43 us at 7200 tiles, but 93 -> 100 us at 9600 (long lists
-// everywhere, so no teams) and 106 -> 119 us at 16320.  A team for every tile spends twice the
+// everywhere, so no teams) and 106 -> 119 us at 16320.  The number of tiles only stands in for that: with thin
+// Gaussians all over 1000x1000 pixels, lists alike, 8x16 tiles (7875) take 87 -> 105 us, 16x16 (3969) 112 -> 128.
+// A team for every tile spends twice the
 // instructions: 70 -> 41 us at 560 tiles, 49 -> 48 us at 1012, but 75 -> 141 us at 7200.
 constexpr int64_t kTeamTiles = 8192, kTeamAllTiles = 1024;
 constexpr int kTeamSlots = 4;

@@ -184,8 +184,8 @@ constexpr int kQueueStride = 512;
 // `ranges` and `sched` must be zero (emit_and_sort clears them).  `sched` holds
 // sched_words() uint32: the forward queue heads from word 0, the backward
 // heads from sched_backward_heads(), bucket histograms, and at
-// sched_item_count() the number of work items, of those of split tiles, and, with `sums`, the
-// list entries of all items (64 bits) and the longest list.
+// sched_item_count() the number of work items, of those of split tiles, and, with `sums` (for
+// exact MIP compositing), the list entries of all items (64 bits) and the longest list.
 size_t sched_words();
 size_t sched_backward_heads();
 size_t sched_item_count();
@@ -202,8 +202,9 @@ constexpr uint32_t kSplitLen = 256, kTeamSplitLen = 128;
 
 // How the tiles of a frame are composited.
 //   per wave   a wave takes whole tiles and halves (k_blend)
-//   teams      the workgroups first take the split tiles, all waves of a
-//              workgroup on one tile, then go on as above (k_blend_team)
+//   teams      the workgroups first take split tiles, all waves of a
+//              workgroup on one tile, then go on as above (k_blend_team, which
+//              decides by the frame's lists how many)
 //   all teams  every tile by a workgroup
 // A team needs about twice the instructions of a wave, but a third of
 // its time per list entry.
