@@ -96,3 +96,39 @@ def test_team_gradients(r, n, logit, tile):
     for k in ("means", "log_scales", "quats", "opacity_logits", "sh"):
         top = float(a[k].abs().max())
         assert top > 0 and float((a[k] - b[k]).abs().max()) <= tol * top, k
+
+
+# Frames of more tiles than all teams take, with lists that are split
+@pytest.mark.parametrize("tile", [(8, 16), (16, 16), (8, 32)])
+def test_alike_lists_equal_teams(r, tile):
+    """Exact MIP with lists that are nearly alike (no teams) and beside a view of few, far longer lists (teams): the same
+    bits."""
+    from gpu_helpers import instance_lists, render_with_ws
+
+    say(f"case alike lists tile {tile}")
+    rng = np.random.default_rng(23)
+    n, w, h = 40000, 701, 533
+    z = rng.uniform(2.0, 8.0, n)
+    xy = np.stack([rng.uniform(-0.6, 0.6, n), rng.uniform(-0.48, 0.48, n)]) * z
+    g = dict(means=np.stack([xy[0], xy[1], z]), log_scales=np.log(0.02 * z)[None] + rng.normal(0, 0.3, (3, n)),
+             quats=rng.standard_normal((4, n)), opacity_logits=rng.normal(-3.0, 0.5, n),
+             sh=rng.normal(0, 0.5, (1, 3, n)))
+    g = {k: np.ascontiguousarray(v, dtype=np.float32) for k, v in g.items()}
+    g["sh_degree"] = 0
+    cam, far = _cam(w, h, 0.9 * w), _cam(512, 512, 12.0)
+    opts = dict(tile_w=tile[0], tile_h=tile[1], mip=2)
+
+    def first(cams):
+        outs, buf, _, lay, _ = render_with_ws(r, g, cams, opts)
+        count = np.bincount(instance_lists(buf, lay)[0])
+        # two workgroups of eight waves on a CU; lists of 128 and more count twice, unless the average work is larger
+        waves = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+        split = count >= max(128, -(-int(count.sum()) // waves))
+        return outs[0], count.max() * waves / (count.sum() + count[split].sum()), int(split.sum())
+
+    alone, ratio, split = first([cam])
+    assert ratio < 3 and split > 100
+    beside, ratio, split = first([cam, far])
+    assert ratio > 3 and split > 100
+    for k in ("rgb", "final_T", "n_contrib"):
+        assert np.array_equal(alone[k], beside[k])
